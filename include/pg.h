@@ -376,7 +376,7 @@ int pg_ibs_distance(const uint32_t* ibs0, const uint32_t* ibs1, const uint32_t* 
                     int64_t count, double* dist, void* stream);
 
 /* Workspace bytes pg_ibs_cluster needs for m samples (an m x m double
- * working matrix plus per-sample state). */
+ * working matrix, two of them up to 24,576 samples, plus per-sample state). */
 int pg_cluster_workspace_bytes(int64_t m, size_t* bytes);
 
 /*
@@ -386,10 +386,12 @@ int pg_cluster_workspace_bytes(int64_t m, size_t* bytes);
  * distance (largest member-to-member distance) merge; ties go to the pair
  * with the smallest a, then the smallest b.  merges (device, m - 1 records)
  * receives the merge sequence in order; the result is exactly determined by
- * the counts.  Below 3,200 samples one block runs the merge loop; from
- * 3,200 on, each merge is two kernel launches over the chip (the stream
- * receives 2 (m - 1) launches).  Stages for pg_profile_events: 1 =
- * distances and nearest neighbours, 2 = the merge loop.
+ * the counts.  Up to 24,576 samples all mutually nearest pairs merge in a
+ * round, and one cooperative launch runs the rounds.  Larger cohorts, and
+ * calls on a stream that is being captured, merge one pair at a time: below
+ * 3,200 samples in one block's loop, from 3,200 on in two kernel launches per
+ * merge (the stream receives 2 (m - 1) launches).  Stages for
+ * pg_profile_events: 1 = distances and nearest neighbours, 2 = the merge loop.
  */
 int pg_ibs_cluster(const uint32_t* ibs0, const uint32_t* ibs1, const uint32_t* nonmiss,
                    int64_t m, pg_merge* merges, void* workspace, size_t workspace_bytes,

@@ -811,7 +811,8 @@ int plan_cluster(int64_t m, ClusterPlan& p) {
   p.off_nnj = c.take(m * 4);
   p.off_ctl = c.take(16);
   p.off_rows = c.take(m * 4);
-  p.bytes = c.off;
+  // the rounds use the workspace from its start instead
+  p.bytes = c.off > cluster_rounds_bytes(m) ? c.off : cluster_rounds_bytes(m);
   return PG_OK;
 }
 }  // namespace

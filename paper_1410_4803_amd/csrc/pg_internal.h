@@ -401,10 +401,14 @@ int launch_genome(const uint32_t* D, int64_t wn, int64_t nv, int64_t rows_pad, d
                   const uint32_t* nm, int64_t count, double* z0, double* z1, double* z2,
                   double* pi, hipStream_t st);
 // D: m x m doubles; nn_d: m doubles; nn_j: m ints; ctl: 4 ints (the first two
-// count the rows to rescan); rows: m ints.  From kClusterSplitMin samples on,
-// each merge runs as two launches over the chip (the pair and the fold; the
-// rescans) instead of one block's loop.
+// count the rows to rescan); rows: m ints.  Where the merges do not run in
+// rounds: from kClusterSplitMin samples on, each merge runs as two launches
+// over the chip (the pair and the fold; the rescans) instead of one block's
+// loop.
 constexpr int64_t kClusterSplitMin = 3200;
+// D also starts the workspace of the merge rounds (cluster_rounds_bytes, 0
+// when m is too large for them).
+int64_t cluster_rounds_bytes(int64_t m);
 int launch_ibs_cluster(const uint32_t* i0, const uint32_t* i1, const uint32_t* nm, int64_t m,
                        double* D, double* nn_d, int* nn_j, int* ctl, int* rows,
                        pg_merge* merges, hipStream_t st);
