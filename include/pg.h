@@ -321,26 +321,30 @@ int pg_ld_prune(const pg_genotypes* g, const int32_t* sample_idx, int64_t n_sel,
  * every pair.  For samples i, j of the selection:
  *   N[i,j] = markers counted,  A[i,j] = (sum of increments) / N[i,j]
  * (NaN when N[i,j] = 0).  The diagonal uses the same increments with i = j.
- * The sums are formed in IEEE double (fp64 matrix cores, increments factored
- * as z_i z_j with z = (x - 2p) / sqrt(2p(1-p))); they match a sequential
- * double sum of the per-pair increments to within the rounding of a length-V
- * double dot product (about V * 2^-53 times the sum of |increments|).
+ * The sums are formed exactly from increments held to 2^-53 (int8 matrix
+ * cores, digit by digit), or in IEEE double (fp64 matrix cores, increments
+ * factored as z_i z_j with z = (x - 2p) / sqrt(2p(1-p))), by size; either way
+ * they match a sequential double sum of the per-pair increments to within the
+ * rounding of a length-V double dot product (about V * 2^-53 times the sum of
+ * |increments|).
  */
 
-/* Workspace bytes pg_grm_matrix needs for this shape: the operand, the
- * per-marker tables, and, on cohorts of fewer than 512 tiles of 128 samples,
- * the partial sums and counts of the variant ranges each tile is split into
- * (196,608 bytes per tile and range). */
+/* Workspace bytes pg_grm_matrix needs for this shape: the operand (twice for
+ * the int8 path), the per-marker tables, and the partial sums and counts of
+ * the variant ranges that tiles are split into (196,608 bytes per tile of
+ * 16,384 pairs and range): every tile on cohorts of fewer than 512, else, on
+ * the int8 path, those of the last round of 512. */
 int pg_grm_workspace_bytes(const pg_genotypes* g, int64_t n_sel, int64_t v_begin,
                            int64_t v_end, size_t* bytes);
 
 /*
  * Relationship matrix over the selected samples and variants.
  *   out_layout  PG_FULL (m x m, diagonal included) or PG_TRI_UPPER
- *   path        PG_PATH_AUTO or PG_PATH_MFMA (fp64 matrix cores); bits 8-15
- *               select the kernel variant: 0 the library's default (= 2),
- *               1 four waves of 64 x 64 per 128 x 128 tile, 2 eight waves of
- *               32 x 64, 3 sixteen waves of 32 x 32 (all give the same sums)
+ *   path        PG_PATH_AUTO or PG_PATH_MFMA (matrix cores); bits 8-15
+ *               select the kernel variant: 0 the library's default (int8 by
+ *               digits where it is the faster, else 2); fp64: 1 four waves
+ *               of 64 x 64 per 128 x 128 tile, 2 eight waves of 32 x 64, 3
+ *               sixteen waves of 32 x 32 (these give the same sums)
  *   grm         device double array of the layout's size (A)
  *   n_used      device uint32 array of the same size (N)
  * Stages for pg_profile_events: 1 = operand layout and per-marker tables,

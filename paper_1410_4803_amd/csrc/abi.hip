@@ -8,6 +8,7 @@
 
 #include <mutex>
 
+#include "grm_int.h"
 #include "pg_internal.h"
 
 namespace pg {
@@ -338,6 +339,8 @@ int plan_prune(const Sel& s, int32_t window, int32_t step, int path_arg, PrunePl
 struct GrmPlan {
   int64_t rows_pad, words;
   int64_t off_T, off_z, off_used, off_part, bytes;
+  bool can_int;      // the int8 path takes the default variant
+  GrmIntPlan gi;
 };
 
 int plan_grm(const Sel& s, GrmPlan& p) {
@@ -351,6 +354,9 @@ int plan_grm(const Sel& s, GrmPlan& p) {
   p.off_used = c.take(p.words * 4);
   p.off_part = c.take(grm_part_bytes(p.rows_pad, p.words));
   p.bytes = c.off;
+  // one query serves every variant: both paths share T, then go their own way
+  p.can_int = grm_int_plan(s.m, s.nv, p.rows_pad, p.words, p.off_z, p.gi);
+  if (p.can_int && p.gi.bytes > p.bytes) p.bytes = p.gi.bytes;
   return PG_OK;
 }
 
@@ -713,6 +719,9 @@ int pg_grm_matrix(const pg_genotypes* g, const int32_t* sample_idx, int64_t n_se
   uint32_t* T = (uint32_t*)(ws + p.off_T);
   mark_stage(0, st);
   rc = launch_sample_major_2bit(s, T, p.rows_pad, p.words, st);
+  if (rc == PG_OK && p.can_int && (variant == 0 || variant > 3))
+    return launch_grm_int(p.gi, ws, T, s.m, p.rows_pad, p.words, grm, n_used,
+                          out_layout == PG_FULL, st);
   if (rc == PG_OK)
     rc = launch_grm(s, T, p.rows_pad, p.words, (double*)(ws + p.off_z),
                     (uint32_t*)(ws + p.off_used), (double*)(ws + p.off_part), grm, n_used,

@@ -1,0 +1,39 @@
+// Relationship matrix on the int8 matrix cores (grm_int.hip): plan and launch.
+#pragma once
+
+#include "tiles.h"
+
+namespace pg {
+
+// Where the int8 kernels are the path; elsewhere their fixed cost (the digit
+// tables and the operand, 120 us a call) is not earned back.  Measured, us
+// per call, int8 / fp64 (samples x variants):
+//   work (samples^2 x variants) from 8e9 on: 1,500 x 4,000 256 / 262, 800 x
+//   16,000 263 / 306, 2,500 x 2,000 273 / 335; below: 1,200 x 4,000 223 / 196,
+//   1,700 x 2,000 227 / 208, 500 x 16,000 228 / 194;
+//   long panels: 64 x 64,000 237 / 614, 300 x 64,000 295 / 638;
+//   small cohorts on 800 to 8,192 variants, where the fp64 kernel's ranges of
+//   1,024 variants leave the chip idle: 100 x 1,000 122 / 171, 800 x 4,000
+//   181 / 186; shorter: 100 x 500 122 / 100.
+constexpr double kGrmIntMinWork = 8e9;
+constexpr int64_t kGrmIntLong = 32768;
+constexpr int64_t kGrmIntSmall = 1024, kGrmIntShortMin = 800, kGrmIntShortMax = 8192;
+
+struct GrmIntPlan {
+  int64_t nch;              // chunks of 64 variants
+  int64_t tiles, nj;        // tiles, column strips
+  int64_t blocks32;         // 32-sample blocks of G
+  int64_t head;             // tiles run whole; the others in n_split ranges
+  int64_t n_split, cps;     //   of cps chunks
+  int64_t off_G, off_tab, off_cnt, off_stat, off_marks, off_top, off_part_s, off_part_n;
+  int64_t bytes;
+};
+// Plans the int8 path for m samples and nv variants over the sample-major
+// operand T (rows_pad x wp words), scratch from workspace offset `base` on;
+// false where the fp64 kernel is the path.
+bool grm_int_plan(int64_t m, int64_t nv, int64_t rows_pad, int64_t wp, int64_t base,
+                  GrmIntPlan& p);
+int launch_grm_int(const GrmIntPlan& p, char* ws, const uint32_t* T, int64_t m, int64_t rows_pad,
+                   int64_t wp, double* grm, uint32_t* n_used, int full, hipStream_t st);
+
+}  // namespace pg
