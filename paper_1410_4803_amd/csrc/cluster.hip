@@ -878,16 +878,22 @@ __global__ __launch_bounds__(kClT) void k_cl_rounds(ClRounds p) {
         if (tid == 0) {
           for (int w = 1; w < kClWaves; ++w) take_min(v, at, s_pv[0][w], s_pi[0][w]);
           p.found[lab[l] - 1] = pg_merge{lab[k], lab[l], nn_d[k]};
-          nn_d[k] = v;
-          nn_j[k] = at;
-          nn_j[l] = -1;
+          nn_d2[k] = v;
+          nn_j2[k] = at;
+          nn_j2[l] = -1;
         }
       }
       // the pairs' columns in the other rows, a wave each; a row is scanned
-      // again when its neighbour retired, or merged and moved away
+      // again when its neighbour retired, or merged and moved away.  Every
+      // neighbour goes to the other buffer: a slower block may still be
+      // reading this round's
       for (int x = wave * (int)nb + (int)blockIdx.x; x < A; x += (int)nb * kClWaves) {
         const unsigned nx = s_nn[x];
-        if (nx == kClNone || s_nn[nx] == (unsigned)x) continue;
+        if (nx == kClNone) {
+          if (lane == 0) nn_j2[x] = -1;
+          continue;
+        }
+        if (s_nn[nx] == (unsigned)x) continue;
         double* row = D + (int64_t)x * ld;
         const double near = nn_d[x];
         bool moved = false;
@@ -898,17 +904,21 @@ __global__ __launch_bounds__(kClT) void k_cl_rounds(ClRounds p) {
           row[l] = nan;
           moved |= l == (int)nx || (k == (int)nx && y > near);
         }
+        double v = near;
+        int at = (int)nx;
         if (__any(moved)) {
           __threadfence_block();   // the other lanes' columns
-          double v = inf;
-          int at = -1;
+          v = inf;
+          at = -1;
           cl_scan_row(row, A, lane, v, at);
-          if (lane == 0) {
-            nn_d[x] = v;
-            nn_j[x] = at;
-          }
+        }
+        if (lane == 0) {
+          nn_d2[x] = v;
+          nn_j2[x] = at;
         }
       }
+      cl_swap(nn_d, nn_d2);
+      cl_swap(nn_j, nn_j2);
     }
     bar.wait(nb);
     // one block per kClPerBlock slots is enough; the others are done
