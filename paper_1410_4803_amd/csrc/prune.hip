@@ -6,7 +6,9 @@
 //   still kept are visited in increasing a, then b; when r^2 > t, the variant
 //   with the lower minor allele frequency is dropped (b on a tie).
 //
-// GPU plan.  The LD pair kernel (window W - 1, emission test r^2 > t) marks
+// GPU plan.  The pass runs in rounds that decide every pair whose earlier
+// rivals are decided (below); what follows is the sequential form, which
+// small calls take and the rounds fall back to.  The LD pair kernel (window W - 1, emission test r^2 > t) marks
 // every pair above the threshold in its per-row bitmap.  A pair (a, b) first
 // shares a window in window w(b) -- the first window whose end passes b --
 // and is then visited there if a >= w(b)*S; in later windows both variants
@@ -231,7 +233,9 @@ __device__ __forceinline__ void apply_pairs(const uint2* buf, int n, uint32_t* r
 __global__ __launch_bounds__(256) void k_prune_dropbits(const uint32_t* __restrict__ bitmap,
                                                         int64_t bm_words, int64_t nv,
                                                         const int2* __restrict__ stats,
-                                                        uint32_t* __restrict__ drop) {
+                                                        uint32_t* __restrict__ drop,
+                                                        const uint32_t* __restrict__ settled) {
+  if (settled && *settled) return;
   const int64_t total = nv * bm_words;
   for (int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; e < total;
        e += (int64_t)gridDim.x * blockDim.x) {
@@ -255,7 +259,9 @@ __global__ __launch_bounds__(256) void k_prune_dropbits(const uint32_t* __restri
 __global__ __launch_bounds__(256) void k_prune_cellcount(const uint32_t* __restrict__ bitmap,
                                                          int64_t bm_words, PruneGeom g,
                                                          int64_t n_windows, int64_t n_pad,
-                                                         uint16_t* __restrict__ cc) {
+                                                         uint16_t* __restrict__ cc,
+                                                         const uint32_t* __restrict__ settled) {
+  if (settled && *settled) return;
   const int64_t n_cells = n_windows * g.W;
   for (int64_t c = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; c < n_pad;
        c += (int64_t)gridDim.x * blockDim.x) {
@@ -279,7 +285,9 @@ __global__ __launch_bounds__(kPT) void k_prune_greedy(const uint32_t* __restrict
                                                       PruneGeom g, int64_t n_windows,
                                                       const uint16_t* __restrict__ cc,
                                                       uint8_t* __restrict__ keep,
-                                                      int64_t* __restrict__ n_kept) {
+                                                      int64_t* __restrict__ n_kept,
+                                                      const uint32_t* __restrict__ settled) {
+  if (settled && *settled) return;
   __shared__ uint32_t ring[kRingBits / 32];
   __shared__ uint2 buf[kPBuf];
   __shared__ int wsum[kPT / 64];
@@ -432,6 +440,310 @@ int64_t prune_cells_padded(int64_t nv, int64_t window, int64_t step) {
   return round_up(n_windows * window, kPPass);
 }
 
+// ---- the greedy pass in rounds -------------------------------------------------
+// A pair acts (drops its variant x) iff neither of its variants was dropped by
+// an earlier pair.  So with key(e) the place of pair e in the visiting order,
+// M[v] the smallest key among the undecided pairs that would drop v, and T[v]
+// the key of the pair that dropped v (all ones while none has):
+//   T[a] or T[b] below key(e): e does nothing;
+//   else M[a] and M[b] not below key(e): every earlier pair that could have
+//     dropped a or b is decided, and none did: e acts, T[x] = key(e).
+// Every pair that satisfies one of the two is decided at once, and the lowest
+// undecided key always does.  The outcome is the sequential one, in as many
+// rounds as the longest chain of pairs waiting for each other: 3 to 24 on
+// founder mosaics of 500 to 1,000 samples.
+//
+// The key needs no sorting: (window, row in the window, b - a).  A round is
+// one launch over the list of pairs; M for the next round is built by the
+// pairs that stay undecided, in three buffers taken in turn (this round's,
+// the next one's, the one cleared meanwhile).  Once at most kPFew pairs are
+// left, one block finishes with them in registers; if that point is not
+// reached in kPRounds rounds, that block finds a long chain, or the list
+// overflows, the sequential kernels run instead (they return at once
+// otherwise).
+// Bound: launch latency (under 2 us a round, most of them empty).  Greedy pass
+// and all, against the sequential kernel's whole call: 10,000 x 88,025, window
+// 700, 2.53 -> 1.28 ms; 400 x 100,000, window 50, t = 0.5, 1.43 -> 0.23 ms, t =
+// 0.2 9.2 -> 0.61 ms; window 200, four founders, t = 0.2 (0.8 of the list left
+// per round) 18.9 -> 1.79 ms with 26 rounds, 20.6 with 16.  What it costs where
+// it gives up: one chain of 20,000 pairs 2.65 -> 2.77 ms, every pair offending
+// 14.5 -> 14.6 ms.
+constexpr int kPRounds = 26;
+constexpr int kPFew = 8192;
+constexpr int kPTurns = 16;                // the last block gives up on a list that loses
+                                           // less than an eighth in this many rounds
+constexpr int64_t kPRoundsMinPasses = 4;   // below: the sequential kernel is as fast
+constexpr int kPBuildWords = 8;            // bitmap words per thread of the build
+constexpr uint32_t kPDropA = 1u << 17, kPDecided = 1u << 18;
+
+struct PruneRounds {
+  unsigned long long* M[3];   // nv each
+  unsigned long long* T;      // nv
+  uint2* list;                // {a, (b - a) | kPDropA | kPDecided}
+  int64_t cap;                // entries of the list
+  uint32_t* few[2];           // kPFew list indices of the undecided pairs
+  unsigned long long* left;   // [r]: pairs undecided before round r, r <= kPRounds
+  uint32_t* settled;          // T is final
+  unsigned long long* kept;   // caller's count (NULL: none)
+  int64_t nv, W, S;
+};
+
+__device__ __forceinline__ unsigned long long prune_key(const PruneRounds& p, int64_t a, int64_t b,
+                                                        bool& visited) {
+  const int64_t w = b < p.W ? 0 : (b - p.W) / p.S + 1;
+  const int64_t r = a - w * p.S;
+  visited = r >= 0;
+  return (unsigned long long)w << 32 | (unsigned long long)(r & 0xFFFF) << 16 |
+         (unsigned long long)(b - a);
+}
+
+__global__ __launch_bounds__(256) void k_prune_clear(PruneRounds p) {
+  const int64_t i0 = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  for (int64_t v = i0; v < p.nv; v += (int64_t)gridDim.x * blockDim.x)
+    p.M[0][v] = p.M[1][v] = p.T[v] = ~0ull;
+  if (i0 <= kPRounds) p.left[i0] = 0ull;
+  if (i0 == 0) {
+    *p.settled = 0u;
+    if (p.kept) *p.kept = 0ull;
+  }
+}
+
+// Exclusive scan of one count per thread of a 256-thread block, and where the
+// block's run starts in a list counted by *counter.
+__device__ __forceinline__ int64_t block_place(uint32_t v, unsigned long long* counter,
+                                               unsigned long long* sh) {
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  uint32_t x = v;
+  for (int d = 1; d < 64; d <<= 1) {
+    const uint32_t y = __shfl_up(x, d, 64);
+    if (lane >= d) x += y;
+  }
+  if (lane == 63) sh[wave] = x;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    const unsigned long long n = sh[0] + sh[1] + sh[2] + sh[3];
+    sh[4] = n ? atomicAdd(counter, n) : 0ull;
+  }
+  __syncthreads();
+  int64_t at = (int64_t)sh[4] + x - v;
+  for (int w = 0; w < wave; ++w) at += (int64_t)sh[w];
+  __syncthreads();
+  return at;
+}
+
+__global__ __launch_bounds__(256) void k_prune_list(const uint32_t* __restrict__ bitmap,
+                                                    int64_t bm_words, PruneRounds p,
+                                                    const int2* __restrict__ stats) {
+  __shared__ unsigned long long sh[5];
+  const int64_t words = p.nv * bm_words;
+  const int64_t e0 = ((int64_t)blockIdx.x * 256 + threadIdx.x) * kPBuildWords;
+  uint32_t bits[kPBuildWords];
+#pragma unroll
+  for (int q = 0; q < kPBuildWords; ++q) bits[q] = e0 + q < words ? bitmap[e0 + q] : 0u;
+  uint32_t n = 0;
+#pragma unroll
+  for (int q = 0; q < kPBuildWords; ++q) {
+    uint32_t rest = bits[q];
+    if (!rest) continue;
+    const int64_t a = (e0 + q) / bm_words, b0 = a + 1 + (e0 + q - a * bm_words) * 32;
+    while (rest) {
+      const int t = __builtin_ctz(rest);
+      rest &= rest - 1;
+      bool visited;
+      (void)prune_key(p, a, b0 + t, visited);
+      if (!visited) bits[q] &= ~(1u << t);
+    }
+    n += __builtin_popcount(bits[q]);
+  }
+  int64_t at = block_place(n, &p.left[0], sh);
+  if (n == 0) return;
+#pragma unroll
+  for (int q = 0; q < kPBuildWords; ++q) {
+    if (!bits[q]) continue;
+    const int64_t a = (e0 + q) / bm_words, b0 = a + 1 + (e0 + q - a * bm_words) * 32;
+    const int2 sa = stats[a];
+    for (uint32_t rest = bits[q]; rest; rest &= rest - 1, ++at) {
+      const int64_t b = b0 + __builtin_ctz(rest);
+      const int2 sb = stats[b];
+      const bool drop_a = (int64_t)sa.x * sb.y < (int64_t)sb.x * sa.y;
+      bool visited;
+      const unsigned long long key = prune_key(p, a, b, visited);
+      if (at >= p.cap) continue;
+      p.list[at] = make_uint2((uint32_t)a, (uint32_t)(b - a) | (drop_a ? kPDropA : 0u));
+      if (at < kPFew) p.few[0][at] = (uint32_t)at;
+      atomicMin(&p.M[0][drop_a ? a : b], key);
+    }
+  }
+}
+
+__device__ __forceinline__ unsigned long long prune_peek(unsigned long long* q) {
+  return __hip_atomic_load(q, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// Decides pair e if it can be: true once it is.
+__device__ __forceinline__ bool prune_decide(const PruneRounds& p, unsigned long long* M, int64_t a,
+                                             int64_t b, int64_t x, unsigned long long key) {
+  const unsigned long long ta = prune_peek(&p.T[a]), tb = prune_peek(&p.T[b]);
+  const unsigned long long ma = prune_peek(&M[a]), mb = prune_peek(&M[b]);
+  if (ta < key || tb < key) return true;
+  if (ma < key || mb < key) return false;
+  __hip_atomic_store(&p.T[x], key, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  return true;
+}
+
+// Round r.
+__global__ __launch_bounds__(256) void k_prune_round(PruneRounds p, int r) {
+  __shared__ unsigned long long sh[5];
+  const int64_t total = (int64_t)p.left[0];
+  if (p.left[r] <= (unsigned long long)kPFew || total > p.cap) return;   // uniform
+  unsigned long long *M = p.M[r % 3], *next = p.M[(r + 1) % 3], *clear = p.M[(r + 2) % 3];
+  const int64_t step = (int64_t)gridDim.x * blockDim.x;
+  for (int64_t v = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; v < p.nv; v += step)
+    clear[v] = ~0ull;
+  // decide first, then look at those that wait once more: many were dropped
+  // by the pairs that have just acted, and need not hold up the next round
+  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < total; i += step) {
+    const uint2 e = p.list[i];
+    if (e.y & kPDecided) continue;
+    const int64_t a = e.x, b = a + (e.y & 0x1FFFFu), x = e.y & kPDropA ? a : b;
+    bool visited;
+    if (prune_decide(p, M, a, b, x, prune_key(p, a, b, visited))) p.list[i].y = e.y | kPDecided;
+  }
+  for (int64_t i0 = (int64_t)blockIdx.x * blockDim.x; i0 < total; i0 += step) {
+    const int64_t i = i0 + threadIdx.x;
+    bool stays = false;
+    if (i < total) {
+      const uint2 e = p.list[i];
+      if (!(e.y & kPDecided)) {
+        const int64_t a = e.x, b = a + (e.y & 0x1FFFFu), x = e.y & kPDropA ? a : b;
+        bool visited;
+        const unsigned long long key = prune_key(p, a, b, visited);
+        stays = prune_peek(&p.T[a]) >= key && prune_peek(&p.T[b]) >= key;
+        if (stays)
+          atomicMin(&next[x], key);
+        else
+          p.list[i].y = e.y | kPDecided;
+      }
+    }
+    const int64_t at = block_place(stays ? 1u : 0u, &p.left[r + 1], sh);
+    if (stays && at < kPFew) p.few[(r + 1) & 1][at] = (uint32_t)i;
+  }
+}
+
+// The last pairs, in one block: eight per thread.
+__global__ __launch_bounds__(1024) void k_prune_finish(PruneRounds p) {
+  int r = 0;
+  while (r <= kPRounds && p.left[r] > (unsigned long long)kPFew) ++r;
+  if (r > kPRounds || (int64_t)p.left[0] > p.cap) return;      // not settled
+  const uint32_t n = (uint32_t)p.left[r];
+  unsigned long long* M = p.M[r % 3];
+  constexpr int kPer = kPFew / 1024;
+  __shared__ uint32_t s_left;
+  uint2 e[kPer];
+  bool open[kPer];
+#pragma unroll
+  for (int u = 0; u < kPer; ++u) {
+    const uint32_t i = threadIdx.x + 1024u * u;
+    open[u] = i < n;
+    e[u] = open[u] ? p.list[p.few[r & 1][i]] : make_uint2(0u, 1u);
+  }
+  uint32_t before = n;
+  for (int turn = 1;; ++turn) {
+    int waiting = 0;
+#pragma unroll
+    for (int u = 0; u < kPer; ++u) {
+      if (!open[u]) continue;
+      const int64_t a = e[u].x, b = a + (e[u].y & 0x1FFFFu), x = e[u].y & kPDropA ? a : b;
+      bool visited;
+      open[u] = !prune_decide(p, M, a, b, x, prune_key(p, a, b, visited));
+      waiting += open[u];
+    }
+    // every decision is made before M changes (the barrier also orders the
+    // block's accesses); then M holds the pairs that still wait
+    if (!__syncthreads_or(waiting)) break;
+    if (turn % kPTurns == 0) {   // a long chain: left to the sequential kernels
+      if (threadIdx.x == 0) s_left = 0u;
+      __syncthreads();
+      if (waiting) atomicAdd(&s_left, (uint32_t)waiting);
+      __syncthreads();
+      const uint32_t now = s_left;
+      if ((int64_t)now * 8 > (int64_t)before * 7) return;
+      before = now;
+    }
+#pragma unroll
+    for (int u = 0; u < kPer; ++u)
+      if (threadIdx.x + 1024u * u < n)
+        __hip_atomic_store(&M[e[u].y & kPDropA ? e[u].x : e[u].x + (e[u].y & 0x1FFFFu)], ~0ull,
+                           __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __syncthreads();
+#pragma unroll
+    for (int u = 0; u < kPer; ++u) {
+      if (!open[u]) continue;
+      const int64_t a = e[u].x, b = a + (e[u].y & 0x1FFFFu);
+      bool visited;
+      atomicMin(&M[e[u].y & kPDropA ? a : b], prune_key(p, a, b, visited));
+    }
+    __syncthreads();
+  }
+  if (threadIdx.x == 0) *p.settled = 1u;
+}
+
+__global__ __launch_bounds__(256) void k_prune_keep(PruneRounds p, uint8_t* __restrict__ keep) {
+  if (!*p.settled) return;
+  const int64_t v = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  const bool stays = v < p.nv && p.T[v] == ~0ull;
+  if (v < p.nv) keep[v] = stays ? 1 : 0;
+  if (!p.kept) return;
+  const int n = __syncthreads_count(stays);
+  if (threadIdx.x == 0 && n) atomicAdd(p.kept, (unsigned long long)n);
+}
+
+// Lays the rounds' scratch out in the count scratch; false when it is too
+// small (windows under 18 variants, or more than 3.5 million variants, leave
+// less than half an entry per variant for the list).
+static bool prune_rounds_plan(const LdScratch& sc, uint16_t* cc, int64_t cells, int64_t nv, int64_t window, int64_t step,
+                              int64_t* n_kept, PruneRounds& p) {
+  if (!cc || nv >= (int64_t)1 << 31 ||
+      prune_cells_padded(nv, window, step) < kPRoundsMinPasses * kPPass)
+    return false;
+  char* at = reinterpret_cast<char*>(cc);
+  char* const end = at + cells * 2;
+  auto take = [&](int64_t bytes) {
+    char* q = at;
+    at += round_up(bytes, 256);
+    return q;
+  };
+  for (auto& m : p.M) m = (unsigned long long*)take(nv * 8);
+  p.T = (unsigned long long*)take(nv * 8);
+  for (auto& f : p.few) f = (uint32_t*)take(kPFew * 4);
+  // not in the count scratch: the sequential kernels reuse that before they
+  // look at `settled`; the row offsets (at least 65) are not used here
+  p.left = reinterpret_cast<unsigned long long*>(sc.rowoff);
+  p.settled = reinterpret_cast<uint32_t*>(p.left + kPRounds + 1);
+  p.list = (uint2*)at;
+  p.cap = end > at ? (end - at) / 8 : 0;
+  if (p.cap > (int64_t)1 << 31) p.cap = (int64_t)1 << 31;
+  p.kept = (unsigned long long*)n_kept;
+  p.nv = nv;
+  p.W = window;
+  p.S = step;
+  return p.cap >= nv / 2 && p.cap >= kPFew;
+}
+
+static int launch_prune_rounds(const LdScratch& sc, const int2* stats, const PruneRounds& p,
+                               uint8_t* keep, hipStream_t st) {
+  const int64_t blocks = ceil_div(p.nv, 256) < 1024 ? ceil_div(p.nv, 256) : 1024;
+  hipLaunchKernelGGL(k_prune_clear, dim3((unsigned)blocks), dim3(256), 0, st, p);
+  hipLaunchKernelGGL(k_prune_list,
+                     dim3((unsigned)ceil_div(p.nv * sc.bm_words, 256 * kPBuildWords)), dim3(256), 0,
+                     st, sc.bitmap, sc.bm_words, p, stats);
+  for (int r = 0; r < kPRounds; ++r)
+    hipLaunchKernelGGL(k_prune_round, dim3((unsigned)blocks), dim3(256), 0, st, p, r);
+  hipLaunchKernelGGL(k_prune_finish, dim3(1), dim3(1024), 0, st, p);
+  hipLaunchKernelGGL(k_prune_keep, dim3((unsigned)ceil_div(p.nv, 256)), dim3(256), 0, st, p, keep);
+  return check_launch("prune_rounds");
+}
+
 int64_t prune_count_capacity(int64_t nv, int64_t window) {
   // step 1 has the most windows, at most nv of them
   const int64_t worst = round_up(nv * window, kPPass);
@@ -441,11 +753,19 @@ int64_t prune_count_capacity(int64_t nv, int64_t window) {
 int launch_prune_greedy(const LdScratch& sc, const int2* stats, uint32_t* drop, uint16_t* cc,
                         int64_t cc_capacity, int64_t nv, int64_t window, int64_t step,
                         uint8_t* keep, int64_t* n_kept, hipStream_t st) {
+  PruneRounds p;
+  const uint32_t* settled = nullptr;
+  int rc;
+  if (prune_rounds_plan(sc, cc, cc_capacity, nv, window, step, n_kept, p)) {
+    rc = launch_prune_rounds(sc, stats, p, keep, st);
+    if (rc != PG_OK) return rc;
+    settled = p.settled;
+  }
   const int64_t words = nv * sc.bm_words;
   const int64_t blocks = ceil_div(words, 256) < 65536 ? ceil_div(words, 256) : 65536;
   hipLaunchKernelGGL(k_prune_dropbits, dim3((unsigned)(blocks > 0 ? blocks : 1)), dim3(256), 0, st,
-                     sc.bitmap, sc.bm_words, nv, stats, drop);
-  int rc = check_launch("prune_dropbits");
+                     sc.bitmap, sc.bm_words, nv, stats, drop, settled);
+  rc = check_launch("prune_dropbits");
   if (rc != PG_OK) return rc;
   const int64_t n_windows = nv <= window ? 1 : ceil_div(nv - window, step) + 1;
   const PruneGeom g{nv, window, step};
@@ -454,12 +774,12 @@ int launch_prune_greedy(const LdScratch& sc, const int2* stats, uint32_t* drop, 
   if (n_pad > 0) {
     const int64_t cb = ceil_div(n_pad, 256) < 65536 ? ceil_div(n_pad, 256) : 65536;
     hipLaunchKernelGGL(k_prune_cellcount, dim3((unsigned)cb), dim3(256), 0, st, sc.bitmap,
-                       sc.bm_words, g, n_windows, n_pad, cc);
+                       sc.bm_words, g, n_windows, n_pad, cc, settled);
     rc = check_launch("prune_cellcount");
     if (rc != PG_OK) return rc;
   }
   hipLaunchKernelGGL(k_prune_greedy, dim3(1), dim3(kPT), 0, st, sc.bitmap, sc.bm_words, drop, g,
-                     n_windows, n_pad > 0 ? cc : nullptr, keep, n_kept);
+                     n_windows, n_pad > 0 ? cc : nullptr, keep, n_kept, settled);
   return check_launch("prune_greedy");
 }
 
