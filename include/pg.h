@@ -128,16 +128,16 @@ enum pg_path {
   PG_PATH_MFMA = 2, /* 2-bit codes expanded to indicator features (values
                        0, +-1) and contracted on the matrix cores.  Default
                        kernels (variant 0): fp4 (e2m1) operands with fp32
-                       sums, exact below 2^24 summed terms; beyond that
-                       (IBS: 2^24 variants, LD: 2^24 samples) int8 operands
-                       with int32 sums.  IBS variants: 1 int8 without
+                       sums while those are exact; beyond that (IBS: 2^24
+                       variants, LD: 2^24 / 9 samples) int8 operands with
+                       int32 sums.  IBS variants: 1 int8 without
                        scheduling hints, 2 unpipelined reference, 3 fp4
                        unpipelined, 4 fp4 from a replicated operand, 5/6
                        eight waves, 7 int8 pipelined, 8 fp4 pipelined (the
                        default), 9 int8 with hints, unpipelined.  LD
                        variants: 1 the int8 tile.  All give identical
                        counts. */
-  PG_PATH_SPARSE = 3 /* LD only: sum x_a x_b on the int8 matrix cores, the
+  PG_PATH_SPARSE = 3 /* LD only: sum x_a x_b on the matrix cores, the
                        other five sums from per-variant totals corrected at
                        the other variant's missing calls (section "Bit
                        population count": without missing calls only
@@ -146,7 +146,7 @@ enum pg_path {
                        one of its variants has more missing calls than a
                        list slot holds (max(64, ceil(m/16) rounded up to a
                        multiple of 8), at most 65,528, for m selected
-                       samples) or its 128 variants have more than 3m/8 in
+                       samples) or its 128 variants have more than m/4 in
                        all, and every tile does unless a quarter of the
                        64-variant groups pass these tests on their own
                        (then the extra sample-major operand pays).  Exact

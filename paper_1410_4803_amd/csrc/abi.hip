@@ -194,6 +194,7 @@ int plan_ibs(const Sel& s, int path_arg, IbsPlan& p) {
 struct LdPlan {
   int path, variant;
   int64_t rows_pad, words, bm_words;
+  int64_t off_E;   // nibble operand of the fp4 tiles (-1: none)
   int64_t off_D, off_bm, off_cnt, off_off, off_bsum, bytes;
   // correction path: sample-major operand (t_rows x t_words), lists, stats
   int64_t t_rows, t_words, off_T, off_lists, off_vst, off_gsum, off_gmax, off_any;
@@ -212,8 +213,8 @@ int plan_ld(const Sel& s, int32_t window, int path_arg, LdPlan& p) {
   if (path != PG_PATH_MFMA && path != PG_PATH_POPC && path != PG_PATH_SPARSE)
     return fail(PG_EINVAL, "unknown path %d", path);
   p.path = path;
-  // matrix-core kernel: fp4 by default (exact below 2^24 samples), int8 as
-  // variant 1 or beyond that
+  // matrix-core kernel: fp4 by default, int8 as variant 1 or beyond 2^24
+  // samples (from kLdFp4MaxSamples on the default runs the int8 tile too)
   if (path == PG_PATH_MFMA && (p.variant != kLdVariantInt8 && s.m < kFp4MaxVariants))
     p.variant = kLdVariantFp4;
   else if (path == PG_PATH_MFMA)
@@ -230,6 +231,9 @@ int plan_ld(const Sel& s, int32_t window, int path_arg, LdPlan& p) {
   }
   Carve c;
   p.off_D = c.take(operand_bytes);
+  const bool fp4 = s.m < kLdFp4MaxSamples &&
+      (path == PG_PATH_SPARSE || (path == PG_PATH_MFMA && p.variant == kLdVariantFp4));
+  p.off_E = fp4 ? c.take(2 * operand_bytes) : -1;
   p.off_bm = c.take(p.rows_pad * p.bm_words * 4);
   p.off_cnt = c.take(p.rows_pad * 4);
   p.off_off = c.take((p.rows_pad + 1) * 8);
@@ -251,17 +255,16 @@ int plan_ld(const Sel& s, int32_t window, int path_arg, LdPlan& p) {
 
 
 // Band tiles take the correction path when their two 64-variant groups hold
-// at most 3m/8 missing calls (m selected samples), and only once a quarter
+// at most m/4 missing calls (m selected samples), and only once a quarter
 // of the groups have a diagonal tile that does, so that the sample-major
-// operand is worth building.  Measured on 5,000 samples x 500,000 variants,
-// window 1,000, every tile forced onto the correction kernel: 4.1 ms without
-// missing calls, 5.4 ms at 0.25% (0.32m per tile), 6.1 ms at 0.5% (0.64m),
-// 7.3 ms at 1%, against 6.1-6.2 ms for the pipelined fp4 dense kernel.  Per
-// tile the two cost the same near 0.6m; the rule stops at 3m/8 so that the
-// tiles' savings also pay for building T and the longer statistics pass
-// (0.7 ms together at this size).
+// operand is worth building.  Whole calls on 300,000 variants, window 1,000,
+// every tile forced onto the correction kernel, against 3.5-3.6 ms for the
+// dense kernel at 5,000 samples: 2.36 ms without missing calls, 3.45 at 0.15%
+// (0.19m per tile), 3.68 at 0.25% (0.32m), 4.13 at 0.5%.  10,000 samples x
+// 100,000 variants, window 500: 0.99, 1.33, 1.44, 1.62 ms against 1.40-1.44.
+// The lines cross between 0.25m and 0.32m.
 int64_t ld_sparse_budget(const LdPlan& p, int64_t m) {
-  return p.variant & (kLdAllTiles | kLdDiag) ? INT64_MAX : 3 * m / 8;
+  return p.variant & (kLdAllTiles | kLdDiag) ? INT64_MAX : m / 4;
 }
 uint32_t ld_sparse_min_groups(const LdPlan& p) {
   const int64_t g = p.rows_pad / kLdTile;
@@ -281,13 +284,14 @@ int ld_pairs(const Sel& s, const LdPlan& p, char* ws, int32_t window, double r2_
     if (rc != PG_OK) return rc;
     return launch_ld_popc(D, p.words, s.nv, p.rows_pad, window, r2_min, sc, st);
   }
-  rc = launch_variant_major_2bit(s, D, p.rows_pad, p.words, st);
+  uint32_t* E = p.off_E >= 0 ? (uint32_t*)(ws + p.off_E) : nullptr;
+  rc = E ? launch_ld_layout(s, D, E, p.rows_pad, p.words, st)
+         : launch_variant_major_2bit(s, D, p.rows_pad, p.words, st);
   if (rc == PG_OK) rc = ld_clear(sc, p.rows_pad, st);
   if (p.path == PG_PATH_MFMA) {
     mark_stage(1, st);
     if (rc != PG_OK) return rc;
-    return launch_ld_mfma(D, p.words, s.nv, p.rows_pad, window, r2_min, sc, st, nullptr,
-                          p.variant == kLdVariantFp4);
+    return launch_ld_mfma(D, E, p.words, s.nv, p.rows_pad, window, r2_min, sc, st);
   }
   LdSparse sp{(uint32_t*)(ws + p.off_lists), (int4*)(ws + p.off_vst), (int64_t*)(ws + p.off_gsum),
               (int*)(ws + p.off_gmax), (uint32_t*)(ws + p.off_any), ld_sparse_min_groups(p),
@@ -309,7 +313,7 @@ int ld_pairs(const Sel& s, const LdPlan& p, char* ws, int32_t window, double r2_
   if (rc == PG_OK) rc = launch_ld_transpose(D, p.rows_pad, p.words, T, p.t_rows, p.t_words, sp, st);
   mark_stage(1, st);
   if (rc != PG_OK) return rc;
-  return launch_ld_sparse(D, p.words, T, p.t_rows, s.m, s.nv, p.rows_pad, window, r2_min, sc, sp,
+  return launch_ld_sparse(D, E, p.words, T, p.t_rows, s.m, s.nv, p.rows_pad, window, r2_min, sc, sp,
                           st, dbg, s.v0);
 }
 

@@ -35,6 +35,7 @@ struct BatchItem {
   int64_t tile_begin;    // first global tile index
   int64_t ntiles;
   const uint32_t* X;     // operand layout in the workspace
+  const uint32_t* E;     // LD: nibble operand of the fp4 tile (NULL: the int8 tile)
   int64_t words;         // K words of the operand
   int64_t rows_pad;
   int64_t nt;            // IBS: tiles per side; LD: row tiles
@@ -122,9 +123,9 @@ __global__ __launch_bounds__(256, kPart == kPartIbs ? 1 : 2) void k_batch_persis
       const int64_t J = I + local % it.n_band;
       if (J < it.nt) {
         if constexpr (kPart == kPartLdMfma) {
-          if (it.variant == kLdVariantFp4)
-            ld_fp4_tile_pipe(it.X, it.words, it.nv, I, J, it.window, it.r2_min, it.sc,
-                             (lds_t*)smem);
+          if (it.E)
+            ld_nib_tile(it.E, it.words / 4, it.nv, I, J, it.window, it.r2_min, it.sc,
+                        (lds_t*)smem);
           else
             ld_mfma_tile(it.X, it.words, it.nv, I, J, it.window, it.r2_min, it.sc, (lds_t*)smem);
         } else {
@@ -158,7 +159,7 @@ struct ProblemPlan {
   Sel s;
   int path, variant;
   int64_t rows_pad, words, nt, n_band, bm_words;
-  int64_t off_x, off_bm, off_cnt, off_off, off_bsum;
+  int64_t off_x, off_e, off_bm, off_cnt, off_off, off_bsum;
   int64_t ntiles;
   double tile_cost;
 };
@@ -243,6 +244,10 @@ int pg_batch_plan(const pg_problem* probs, int n_probs, pg_plan** out) {
         const int64_t bytes = q.path == PG_PATH_MFMA ? q.rows_pad * q.words * 4
                                                      : 3 * q.rows_pad * q.words * 4;
         q.off_x = take(off, bytes);
+        q.off_e = q.path == PG_PATH_MFMA && q.variant == kLdVariantFp4 &&
+                          q.s.m < kLdFp4MaxSamples
+                      ? take(off, 2 * bytes)
+                      : -1;
         q.off_bm = take(off, q.rows_pad * q.bm_words * 4);
         q.off_cnt = take(off, q.rows_pad * 4);
         q.off_off = take(off, (q.rows_pad + 1) * 8);
@@ -347,6 +352,7 @@ int pg_batch_upload(pg_plan* plan, void* workspace, size_t workspace_bytes, void
                     (q.p.out_layout & ~PG_COUNTS_U16) == PG_FULL,
                     (q.p.out_layout & PG_COUNTS_U16) ? 1 : 0};
     } else {
+      it.E = q.off_e >= 0 ? (const uint32_t*)(ws + q.off_e) : nullptr;
       it.window = q.p.window;
       it.n_band = q.n_band;
       it.nv = q.s.nv;
@@ -438,7 +444,9 @@ int pg_batch_launch(const pg_plan* plan, void* workspace, size_t workspace_bytes
     const ProblemPlan& q = plan->probs[k];
     if (q.p.kind != PG_KIND_LD) continue;
     uint32_t* X = (uint32_t*)(ws + q.off_x);
-    rc = q.path == PG_PATH_MFMA ? launch_variant_major_2bit(q.s, X, q.rows_pad, q.words, side)
+    rc = q.off_e >= 0
+             ? launch_ld_layout(q.s, X, (uint32_t*)(ws + q.off_e), q.rows_pad, q.words, side)
+         : q.path == PG_PATH_MFMA ? launch_variant_major_2bit(q.s, X, q.rows_pad, q.words, side)
                                 : launch_ld_planes(q.s, X, q.rows_pad, q.words, side);
     const LdScratch sc{(uint32_t*)(ws + q.off_bm), q.bm_words, (uint32_t*)(ws + q.off_cnt),
                        (int64_t*)(ws + q.off_off), (int64_t*)(ws + q.off_bsum)};

@@ -524,6 +524,84 @@ int launch_variant_major_2bit(const Sel& s, uint32_t* D, int64_t rows_pad, int64
   return check_launch("variant_major_2bit");
 }
 
+// ---- LD operands: 2-bit words D and nibbles E ------------------------------------
+// Sixteen codes to the fp4 nibbles of the LD tile (ld_nib_tile): homozygous A1
+// 1001, heterozygous 0001, homozygous A2 0011, missing 0000; even codes in
+// the first word, odd codes in the second.
+__device__ __forceinline__ uint2 ld_nibbles(uint32_t w) {
+  uint32_t n[2];
+#pragma unroll
+  for (int par = 0; par < 2; ++par) {
+    const uint32_t lo = (w >> (2 * par)) & 0x11111111u, hi = (w >> (2 * par + 1)) & 0x11111111u;
+    n[par] = (~(lo & ~hi) & 0x11111111u) | (lo & hi) << 1 | (~(lo | hi) & 0x11111111u) << 3;
+  }
+  return make_uint2(n[0], n[1]);
+}
+
+// D (rows_pad x wn words of 16 samples) and E: 64 variants x 64 samples in 512
+// words, [half of the samples][variant][4 words], the steps of a 64-variant
+// group in order.  A block takes 64 variants x 32 words: 128-byte runs of a
+// row in, the same of D out, and whole 2 KB steps of E by way of LDS (a step's
+// halves lie 260 words apart there, so the 16 a half-wave writes fall in
+// different banks).  kFromD: D is there already (a sample list's layout).
+constexpr int kLyRows = 64, kLyWords = 32;
+
+template <bool kFromD>
+__global__ __launch_bounds__(256) void k_ld_layout(Sel s, uint32_t* __restrict__ D,
+                                                   uint32_t* __restrict__ E, int64_t rows_pad,
+                                                   int64_t wn, int aligned) {
+  __shared__ uint32_t s_e[16 * 260];
+  const int64_t nb_w = ceil_div(wn, kLyWords);
+  const int64_t blk = xcd_swizzle(blockIdx.x, gridDim.x);
+  const int64_t G = blk / nb_w, w0 = blk % nb_w * kLyWords;
+  const int t = threadIdx.x, g = t & 31;
+  int64_t vr[8], gr[8];
+  uint32_t x[8];
+#pragma unroll
+  for (int u = 0; u < 8; ++u) {
+    vr[u] = G * kLyRows + (t >> 5) + 8 * u;
+    gr[u] = w0 + g;
+  }
+  if constexpr (kFromD) {
+#pragma unroll
+    for (int u = 0; u < 8; ++u) x[u] = gr[u] < wn ? D[vr[u] * wn + gr[u]] : kAllMissing16;
+  } else {
+    row_words16(s, vr, gr, aligned != 0, x);
+  }
+#pragma unroll
+  for (int u = 0; u < 8; ++u) {
+    if (!kFromD && gr[u] < wn) D[vr[u] * wn + gr[u]] = x[u];
+    const uint2 n = ld_nibbles(x[u]);
+    uint32_t* d = &s_e[(g >> 1) * 260 + ((t >> 5) + 8 * u) * 4 + 2 * (g & 1)];
+    d[0] = n.x;
+    d[1] = n.y;
+  }
+  __syncthreads();
+  const int64_t nsteps = wn / 4, step0 = w0 / 4;
+#pragma unroll
+  for (int u = 0; u < 4; ++u) {
+    const int o = u * 256 + t;             // 16-byte piece: step o / 128 of the block's eight
+    const int64_t step = step0 + (o >> 7);
+    if (step < nsteps)
+      *reinterpret_cast<uint4*>(E + (G * nsteps + step) * 512 + 4 * (o & 127)) =
+          *reinterpret_cast<const uint4*>(&s_e[(o >> 6) * 260 + 4 * (o & 63)]);
+  }
+}
+
+int launch_ld_layout(const Sel& s, uint32_t* D, uint32_t* E, int64_t rows_pad, int64_t wn,
+                     hipStream_t st) {
+  const dim3 grid((unsigned)(rows_pad / kLyRows * ceil_div(wn, kLyWords)));
+  if (!s.idx) {
+    hipLaunchKernelGGL(k_ld_layout<false>, grid, dim3(256), 0, st, s, D, E, rows_pad, wn,
+                       (int)rows_dword_aligned(s));
+    return check_launch("ld_layout");
+  }
+  int rc = launch_variant_major_2bit(s, D, rows_pad, wn, st);
+  if (rc != PG_OK) return rc;
+  hipLaunchKernelGGL(k_ld_layout<true>, grid, dim3(256), 0, st, s, D, E, rows_pad, wn, 0);
+  return check_launch("ld_layout");
+}
+
 // LD bit planes without a sample list, staged through LDS: a block owns 64
 // variants x 32 plane words (1,024 samples).  Lanes read consecutive dwords of
 // one variant row (coalesced), the three 16-bit half-planes of each dword go

@@ -10,7 +10,8 @@
 //   n   = m - c_a - c_b + |miss(a) and miss(b)|
 //   Sx  = t_a - sum over k in miss(b) of x_a[k],  Sxx = u_a - (same for x_a^2)
 //   Sy  = t_b - sum over k in miss(a) of x_b[k],  Syy = u_b - (same for x_b^2)
-// and Sxy is one int8 Gram over all samples on the matrix cores.  Every sum
+// and Sxy is one Gram over all samples on the matrix cores (fp4, int8 for
+// the largest cohorts).  Every sum
 // stays an exact integer.
 //
 // A correction reads one word per missing call and 16 variants: a word of
@@ -247,6 +248,11 @@ __device__ __forceinline__ void count_batch(const uint32_t (&words)[kSpBatch], u
   }
 }
 
+// kFp4: Sxy from the nibbles of E.  A whole nibble is v = x + 0.5 for a call
+// and 0 for a missing one, so one fp4 Gram without any expansion gives
+// G = <v_a, v_b> = Sxy + (Sx + Sy) / 2 + n / 4 over the samples where neither
+// is missing, exactly (kLdFp4MaxSamples); the cells hold 4 G.
+template <bool kFp4>
 __global__ __launch_bounds__(256, 3) void k_ld_sparse(
     const uint32_t* __restrict__ D, int64_t wn, const uint32_t* __restrict__ T, int64_t t_rows,
     const uint32_t* __restrict__ lists, const int4* __restrict__ vst,
@@ -276,7 +282,50 @@ __global__ __launch_bounds__(256, 3) void k_ld_sparse(
   // ---- Sxy: each wave takes a quarter of the samples for the whole tile
   // (2 x 2 blocks of 32 x 32); lane group g holds words 8q + 4g .. + 3 of its
   // rows, and A and B use the same word order, so K matches.
-  {
+  if constexpr (kFp4) {
+    // steps of 64 samples; a wave's load of 32 variants is two runs of 512
+    // bytes.  Four register sets, rotating: loads three steps ahead.
+    const int64_t nsteps = wn / 4;
+    const uint32_t* pa = D + I * nsteps * 512 + g * 256 + 4 * rl;
+    const uint32_t* pb = D + J * nsteps * 512 + g * 256 + 4 * rl;
+    const int64_t q0 = nsteps * wid / 4, q1 = nsteps * (wid + 1) / 4;
+    v16f acc00 = (v16f){0}, acc01 = (v16f){0}, acc10 = (v16f){0}, acc11 = (v16f){0};
+    uint4 r[4][4];
+    auto load = [&](uint4 (&x)[4], int64_t q) {
+      q = q < q1 ? q : q1 - 1;
+      x[0] = *reinterpret_cast<const uint4*>(pa + 512 * q);
+      x[1] = *reinterpret_cast<const uint4*>(pa + 512 * q + 128);
+      x[2] = *reinterpret_cast<const uint4*>(pb + 512 * q);
+      x[3] = *reinterpret_cast<const uint4*>(pb + 512 * q + 128);
+    };
+    auto step = [&](const uint4 (&x)[4]) {
+      const v8i a0 = nib_mask(x[0], ~0u), a1 = nib_mask(x[1], ~0u);
+      const v8i c0 = nib_mask(x[2], ~0u), c1 = nib_mask(x[3], ~0u);
+      acc00 = mfma_fp4(a0, c0, acc00);
+      acc01 = mfma_fp4(a0, c1, acc01);
+      acc10 = mfma_fp4(a1, c0, acc10);
+      acc11 = mfma_fp4(a1, c1, acc11);
+    };
+    if (q0 < q1) {
+#pragma unroll
+      for (int u = 0; u < 3; ++u) load(r[u], q0 + u);
+      for (int64_t q = q0; q < q1; q += 4) {
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+          load(r[(u + 3) & 3], q + u + 3);
+          if (q + u < q1) step(r[u]);
+        }
+      }
+    }
+#pragma unroll
+    for (int v = 0; v < 16; ++v) {
+      const int row = 8 * (v >> 2) + 4 * g + (v & 3);
+      atomicAdd(&s_cell[row * kSpS + rl], (uint32_t)(int)(4.0f * acc00[v]));
+      atomicAdd(&s_cell[row * kSpS + 32 + rl], (uint32_t)(int)(4.0f * acc01[v]));
+      atomicAdd(&s_cell[(32 + row) * kSpS + rl], (uint32_t)(int)(4.0f * acc10[v]));
+      atomicAdd(&s_cell[(32 + row) * kSpS + 32 + rl], (uint32_t)(int)(4.0f * acc11[v]));
+    }
+  } else {
     const uint32_t* pa = D + (I * kLdTile + rl) * wn + 4 * g;
     const uint32_t* pb = D + (J * kLdTile + rl) * wn + 4 * g;
     const int64_t off1 = 32 * wn;
@@ -441,7 +490,8 @@ __global__ __launch_bounds__(256, 3) void k_ld_sparse(
     const int64_t both = s_mcell[bl * kSpS + al];
     const int64_t n = m - sa.x - sb.x + both;
     const int64_t sx = sa.y - (a2 - a1), sy = sb.y - (b2 - b1);
-    const int64_t sxx = sa.z - (a2 + a1), syy = sb.z - (b2 + b1), sxy = xy[v];
+    const int64_t sxx = sa.z - (a2 + a1), syy = sb.z - (b2 + b1);
+    const int64_t sxy = kFp4 ? (xy[v] - 2 * (sx + sy) - n) / 4 : xy[v];
     if (dbg) {
       pg_ld_pair rec;
       rec.a = (int32_t)(v0 + a);
@@ -537,20 +587,21 @@ int launch_ld_transpose(const uint32_t* D, int64_t rows_pad, int64_t wn, uint32_
   return check_launch("ld_transpose");
 }
 
-int launch_ld_sparse(const uint32_t* D, int64_t wn, const uint32_t* T, int64_t t_rows, int64_t m,
+int launch_ld_sparse(const uint32_t* D, const uint32_t* E, int64_t wn, const uint32_t* T,
+                     int64_t t_rows, int64_t m,
                      int64_t nv, int64_t rows_pad, int32_t window, double r2_min,
                      const LdScratch& sc, const LdSparse& sp, hipStream_t st, pg_ld_pair* dbg,
                      int64_t v0) {
   int rc;
   // the dense kernel takes the tiles this path leaves
   if (!dbg) {
-    rc = launch_ld_mfma(D, wn, nv, rows_pad, window, r2_min, sc, st, &sp, m < kFp4MaxVariants);
+    rc = launch_ld_mfma(D, E, wn, nv, rows_pad, window, r2_min, sc, st, &sp);
     if (rc != PG_OK) return rc;
   }
   const int64_t n_row_tiles = rows_pad / kLdTile;
   const int64_t n_band = ((int64_t)window + kLdTile - 1) / kLdTile + 1;
-  hipLaunchKernelGGL(k_ld_sparse, dim3((unsigned)(n_row_tiles * n_band)), dim3(256), 0, st, D, wn,
-                     T, t_rows, sp.lists, sp.vst, sp.gsum, sp.gmax, sp.groups_ok, sp.min_groups,
+  hipLaunchKernelGGL(E ? k_ld_sparse<true> : k_ld_sparse<false>,
+                     dim3((unsigned)(n_row_tiles * n_band)), dim3(256), 0, st, E ? E : D, wn, T, t_rows, sp.lists, sp.vst, sp.gsum, sp.gmax, sp.groups_ok, sp.min_groups,
                      sp.cap, sp.budget, m, nv, n_row_tiles, n_band, window, r2_min, sc,
                      dbg, v0);
   rc = check_launch("ld_sparse");

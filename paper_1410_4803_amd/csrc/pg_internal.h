@@ -124,6 +124,12 @@ int launch_sample_major_jobs(const LayoutJob* jobs, int n_jobs, int64_t total_bl
 int launch_variant_major_2bit(const Sel& s, uint32_t* D, int64_t rows_pad, int64_t wn,
                               hipStream_t st);
 
+// The same, and beside it the nibble operand E of the fp4 LD tile: 64 variants
+// x 64 samples in 512 words (rows_pad * wn * 2 words in all; wn a multiple of
+// 16).
+int launch_ld_layout(const Sel& s, uint32_t* D, uint32_t* E, int64_t rows_pad, int64_t wn,
+                     hipStream_t st);
+
 // Variant-major bit planes for the popcount LD path: for 32-sample word w,
 // plane p (0 = homozygous A2, 1 = homozygous A1, 2 = non-missing) of selected
 // variant v at P[(w*3 + p)*rows_pad + v]; words_pad words.
@@ -301,14 +307,17 @@ inline int ld_sparse_cap(int64_t m) {
 
 // Clears the emission bitmap and row counts (stage 1 ends after this).
 int ld_clear(const LdScratch& sc, int64_t rows_pad, hipStream_t st);
+// Most selected samples whose sums the fp4 LD tile forms exactly (its
+// products are up to nine quarters).
+constexpr int64_t kLdFp4MaxSamples = ((int64_t)1 << 24) / 9;
 // Dense pair kernel over the band; with `sp`, tiles the correction path
-// takes are skipped (and stage 2 is left to that path).  fp4: the pipelined
-// fp4 tile (exact below 2^24 samples), else the int8 tile.
-int launch_ld_mfma(const uint32_t* D, int64_t wn, int64_t nv, int64_t rows_pad, int32_t window,
+// takes are skipped (and stage 2 is left to that path).  With E the fp4 tile
+// on it, else (NULL) the int8 tile on D.
+int launch_ld_mfma(const uint32_t* D, const uint32_t* E, int64_t wn, int64_t nv, int64_t rows_pad, int32_t window,
                    double r2_min, const LdScratch& sc, hipStream_t st,
-                   const LdSparse* sp = nullptr, bool fp4 = true);
-// Kernel variants of the LD matrix-core path: 0 (default) the pipelined fp4
-// tile, or the int8 tile (1) when sums could reach 2^24 (m >= 2^24).
+                   const LdSparse* sp = nullptr);
+// Kernel variants of the LD matrix-core path: 0 (default) the fp4 tile (from
+// kLdFp4MaxSamples samples on its int8 twin), or the int8 tile (1).
 constexpr int kLdVariantFp4 = 0;
 constexpr int kLdVariantInt8 = 1;
 // Correction path, first part: lists, counts and totals from D
@@ -327,7 +336,7 @@ int launch_ld_transpose(const uint32_t* D, int64_t rows_pad, int64_t wn, uint32_
 // the dense kernel is not run and each pair of a correction tile writes its
 // record to dbg[a * window + (b - a - 1)] (a, b local; the record holds
 // v0 + a, v0 + b) instead of the emission test.
-int launch_ld_sparse(const uint32_t* D, int64_t wn, const uint32_t* T, int64_t t_rows, int64_t m,
+int launch_ld_sparse(const uint32_t* D, const uint32_t* E, int64_t wn, const uint32_t* T, int64_t t_rows, int64_t m,
                      int64_t nv, int64_t rows_pad, int32_t window, double r2_min,
                      const LdScratch& sc, const LdSparse& sp, hipStream_t st,
                      pg_ld_pair* dbg = nullptr, int64_t v0 = 0);
@@ -460,9 +469,9 @@ __device__ __forceinline__ bool ld_r2_reaches(int64_t n, int64_t sx, int64_t sy,
                                               int64_t syy, int64_t sxy, double r2_min) {
   if (n < (1 << 15) && r2_min > 0.0) {
     const int32_t ni = (int32_t)n, x = (int32_t)sx, y = (int32_t)sy;
-    const float c = (float)(ni * (int32_t)sxy - x * y);
-    const float va = (float)(ni * (int32_t)sxx - x * x);
-    const float vb = (float)(ni * (int32_t)syy - y * y);
+    const float c = (float)(__mul24(ni, (int32_t)sxy) - __mul24(x, y));
+    const float va = (float)(__mul24(ni, (int32_t)sxx) - __mul24(x, x));
+    const float vb = (float)(__mul24(ni, (int32_t)syy) - __mul24(y, y));
     if (c * c < (float)r2_min * (va * vb) * (1.0f - 0x1p-16f)) return false;
   }
   if (n >= ((int64_t)1 << 26)) return ld_r2_wide(n, sx, sy, sxx, syy, sxy) >= r2_min;

@@ -1523,139 +1523,118 @@ __device__ __forceinline__ void ld_mfma_tile(const uint32_t* __restrict__ D, int
 }
 
 
-// Pipelined fp4 form of the banded matrix-core tile (the default LD kernel):
-// the same six Grams on v_mfma_f32_32x32x64_f8f6f4 with e2m1 operands
-// (m, x, h are 0 or +-1, exact; fp32 sums exact below 2^24 samples), and
-// the chunk schedule of ibs_fp4_tile_pipe: a chunk of 256 samples is four
-// steps of 64 per MFMA lane (two 2-bit words), chunk k + 2 is fetched and
-// stored to LDS at step 1 of chunk k, chunk k + 1 is read at steps 2 and 3,
-// and its first step expanded during step 3.  Waves without a pair in the
-// window run a loop that only stages, with the same barriers.
-// Expansion of one parity of a word (see ibs_fp4_tile_pipe for X, Y, K):
-//   m = K & (X | ~Y),  h = K & ~(X ^ Y),  x = h | (K & ~X & ~Y) << 2
-// (x = -1 for homozygous A1, +1 for homozygous A2, 0 otherwise).
-struct Fp4Feat3 {
-  v8i m, x, h;
-};
+// ---- banded fp4 matrix-core kernel --------------------------------------------------
+// The default LD tile: six Grams on v_mfma_f32_32x32x64_f8f6f4 with e2m1
+// operands taken from one nibble per call (operand E, launch_ld_layout):
+//   homozygous A1 1001, heterozygous 0001, homozygous A2 0011, missing 0000.
+// As e2m1 a whole nibble is v = -0.5, 0.5, 1.5 = x + 0.5 for a call (0 when
+// missing); its bit 0 alone is m = 0.5 and its bit 1 alone h = [homozygous A2].
+// So v costs nothing, m and h one AND each, and with G(f, g) = <f_a, g_b>
+//   n = 4 G(m, m),  Sx = 2 (G(v, m) - G(m, m)),  Sxx = 4 G(h, m) - Sx,
+//   Sy, Syy likewise,  Sxy = G(v, v) - G(v, m) - G(m, v) + G(m, m).
+// Products are multiples of 1/4 up to 9/4: sums are exact in fp32 below
+// kLdFp4MaxSamples samples (the int8 tile takes more).
+//
+// Block: 4 waves (2 x 2) over a 64 x 64 tile, one 32 x 32 block each.  E
+// stores 64 variants x 64 samples in 2 KB as [half][variant][16 bytes], so a
+// wave's 16-byte operand reads from LDS are contiguous, and chunks of four
+// such steps reach LDS by direct loads two chunks ahead of their use (48 KB in
+// three buffers: three blocks share a CU).  Waves without a pair in the window
+// only stage.
+// Bound: the matrix cores at the clock this load leaves (1.8 to 2.1 GHz; 69%
+// busy counted).  5,000 samples x 500,000 variants, window 1,000: 5.2 ms
+// against 5.9 ms for 2-bit codes expanded in the loop (two expansions a step,
+// 2.5 vector operations per matrix instruction against 0.7).  Four blocks a CU
+// (chunks of two steps, 32 KB) measure the same.
+constexpr int kLdNibChunk = 4;                       // steps of 64 samples
+constexpr int kLdNibBuf = 2 * kLdNibChunk * 512;     // words per buffer (two groups)
 
-__device__ __forceinline__ Fp4Feat3 ld_fp4_expand2(uint32_t w0, uint32_t w1) {
-  Fp4Feat3 f;
-  f.m = (v8i){0}; f.x = (v8i){0}; f.h = (v8i){0};
-  const uint32_t ws[2] = {w0, w1};
-#pragma unroll
-  for (int q = 0; q < 2; ++q) {
-#pragma unroll
-    for (int par = 0; par < 2; ++par) {
-      const uint32_t X = par ? ws[q] >> 2 : ws[q];
-      const uint32_t Y = par ? ws[q] >> 1 : ws[q] << 1;
-      const uint32_t h = __builtin_amdgcn_bitop3_b32(X, Y, kNibK, kB3Hom);
-      const uint32_t neg = __builtin_amdgcn_bitop3_b32(X, Y, kNibK, kB3A1);
-      f.m[2 * q + par] = (int)__builtin_amdgcn_bitop3_b32(X, Y, kNibK, kB3Mx);
-      f.h[2 * q + par] = (int)h;
-      f.x[2 * q + par] = (int)((neg << 2) | h);
-    }
-  }
+// Lane l's 16 bytes at `src` to LDS `dst` + 16 l (dst uniform over the wave).
+__device__ __forceinline__ void lds_from_global(const uint32_t* src, lds_t* dst) {
+  __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)src,
+                                   (__attribute__((address_space(3))) void*)dst, 16, 0, 0);
+}
+
+__device__ __forceinline__ v8i nib_mask(const uint4& w, uint32_t mask) {
+  v8i f = (v8i){0};
+  f[0] = (int)(w.x & mask);
+  f[1] = (int)(w.y & mask);
+  f[2] = (int)(w.z & mask);
+  f[3] = (int)(w.w & mask);
   return f;
 }
 
-__device__ __forceinline__ void ld_fp4_tile_pipe(const uint32_t* __restrict__ D, int64_t wn,
-                                                 int64_t nv, int64_t I, int64_t J, int32_t window,
-                                                 double r2_min, const LdScratch& sc, lds_t* smem) {
-  constexpr int kBuf = kL * kLStride;
-  lds_t* const sA = smem;
-  lds_t* const sB = smem + 2 * kBuf;
-  const int t = threadIdx.x;
-  const int lane = t & 63;
-  const int wid = t >> 6;
+__device__ __forceinline__ void ld_nib_tile(const uint32_t* __restrict__ E, int64_t nsteps,
+                                            int64_t nv, int64_t I, int64_t J, int32_t window,
+                                            double r2_min, const LdScratch& sc, lds_t* smem) {
+  const int lane = threadIdx.x & 63;
+  const int wid = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int wr = wid >> 1, wc = wid & 1;
-  const int g = lane >> 5;
-  const int rl = lane & 31;
   const int64_t a_lo = I * kL + wr * 32, b_lo = J * kL + wc * 32;
   const bool active = (b_lo + 31 > a_lo) && (b_lo - (a_lo + 31) <= window) && (b_lo < nv);
-
-  const int lrow = t >> 2;
-  const int lq = (t & 3) * 4;
-  const uint32_t* pa = D + (I * kL + lrow) * wn + lq;
-  const uint32_t* pb = D + (J * kL + lrow) * wn + lq;
-  uint4 ga, gb;
-  const int64_t nch = wn / kLW;
-  auto fetch = [&](int64_t c) {
-    const int64_t kc = (c < nch ? c : nch - 1) * kLW;
-    ga = *reinterpret_cast<const uint4*>(pa + kc);
-    gb = *reinterpret_cast<const uint4*>(pb + kc);
-  };
-  auto lstore = [&](int buf) {
-    lds_st4(&(sA + buf * kBuf)[lrow * kLStride + lq], ga);
-    lds_st4(&(sB + buf * kBuf)[lrow * kLStride + lq], gb);
-  };
-  fetch(0);
-  lstore(0);
-  fetch(1);
-  lstore(1);
-  fetch(2);
-  __syncthreads();
-  if (!active) {
-    for (int64_t k = 0; k < nch; ++k) {
-      __syncthreads();
-      lstore((int)(k & 1));
-      fetch(k + 3);
+  const int64_t nch = nsteps / kLdNibChunk;
+  // this wave stages step `wid` of a chunk, both groups
+  const uint32_t* pa = E + (I * nsteps + wid) * 512 + 4 * lane;
+  const uint32_t* pb = E + (J * nsteps + wid) * 512 + 4 * lane;
+  auto fetch = [&](int64_t c, int buf) {
+    const int64_t at = (c < nch ? c : nch - 1) * (kLdNibChunk * 512);
+    lds_t* const d = smem + buf * kLdNibBuf + wid * 512;
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      lds_from_global(pa + at + 256 * h, d + 256 * h);
+      lds_from_global(pb + at + 256 * h, d + kLdNibChunk * 512 + 256 * h);
     }
-    return;   // nothing after this point synchronises
-  }
-  uint32_t wa[8], wb[8];
-  auto lread = [&](int buf, int h) {
-    const uint4 a = lds_ld4(&(sA + buf * kBuf)[(wr * 32 + rl) * kLStride + g * 8 + 4 * h]);
-    const uint4 b = lds_ld4(&(sB + buf * kBuf)[(wc * 32 + rl) * kLStride + g * 8 + 4 * h]);
-    wa[4 * h] = a.x; wa[4 * h + 1] = a.y; wa[4 * h + 2] = a.z; wa[4 * h + 3] = a.w;
-    wb[4 * h] = b.x; wb[4 * h + 1] = b.y; wb[4 * h + 2] = b.z; wb[4 * h + 3] = b.w;
   };
-  v16f s_n = (v16f){0}, s_x = (v16f){0}, s_y = (v16f){0};
-  v16f s_xx = (v16f){0}, s_yy = (v16f){0}, s_xy = (v16f){0};
-  lread(0, 0);
-  lread(0, 1);
-  Fp4Feat3 fa = ld_fp4_expand2(wa[0], wa[1]), fb = ld_fp4_expand2(wb[0], wb[1]);
+  v16f s_mm = (v16f){0}, s_vm = (v16f){0}, s_mv = (v16f){0};
+  v16f s_hm = (v16f){0}, s_mh = (v16f){0}, s_vv = (v16f){0};
+  fetch(0, 0);
+  fetch(1, 1);
+  asm volatile("s_waitcnt vmcnt(4)\n\ts_barrier" ::: "memory");
+  int b0 = 0, b1 = 1, b2 = 2;
   for (int64_t k = 0; k < nch; ++k) {
-    const int buf = (int)(k & 1);
-    __syncthreads();
+    fetch(k + 2, b2);   // chunk k - 1's buffer: every wave is past it
+    if (active) {
+      const lds_t* ra = smem + b0 * kLdNibBuf + (lane >> 5) * 256 + (wr * 32 + (lane & 31)) * 4;
+      const lds_t* rb = smem + b0 * kLdNibBuf + kLdNibChunk * 512 + (lane >> 5) * 256 +
+                        (wc * 32 + (lane & 31)) * 4;
 #pragma unroll
-    for (int s = 0; s < kLW / 4; ++s) {
-      if (s == 1) {
-        lstore(buf);                                  // chunk k + 2
-        fetch(k + 3);
+      for (int s = 0; s < kLdNibChunk; ++s) {
+        const uint4 wa = lds_ld4(ra + s * 512), wb = lds_ld4(rb + s * 512);
+        const v8i va = nib_mask(wa, ~0u), vb = nib_mask(wb, ~0u);
+        const v8i ma = nib_mask(wa, 0x11111111u), mb = nib_mask(wb, 0x11111111u);
+        const v8i ha = nib_mask(wa, 0x22222222u), hb = nib_mask(wb, 0x22222222u);
+        s_vv = mfma_fp4(va, vb, s_vv);
+        s_mm = mfma_fp4(ma, mb, s_mm);
+        s_vm = mfma_fp4(va, mb, s_vm);
+        s_mv = mfma_fp4(ma, vb, s_mv);
+        s_hm = mfma_fp4(ha, mb, s_hm);
+        s_mh = mfma_fp4(ma, hb, s_mh);
       }
-      if (s == 2) lread(buf ^ 1, 0);                  // words 0-3 of chunk k + 1
-      if (s == 3) lread(buf ^ 1, 1);                  // words 4-7
-      const int sn = 2 * ((s + 1) & 3);
-      const Fp4Feat3 na = ld_fp4_expand2(wa[sn], wa[sn + 1]);
-      const Fp4Feat3 nb = ld_fp4_expand2(wb[sn], wb[sn + 1]);
-      s_n = mfma_fp4(fa.m, fb.m, s_n);
-      s_x = mfma_fp4(fa.x, fb.m, s_x);
-      s_y = mfma_fp4(fa.m, fb.x, s_y);
-      s_xx = mfma_fp4(fa.h, fb.m, s_xx);
-      s_yy = mfma_fp4(fa.m, fb.h, s_yy);
-      s_xy = mfma_fp4(fa.x, fb.x, s_xy);
-      if (s == 1) {
-        __builtin_amdgcn_sched_group_barrier(0x200, 2, 0);
-        __builtin_amdgcn_sched_group_barrier(0x020, 2, 0);
-      }
-      if (s >= 2) __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);
-#pragma unroll
-      for (int q = 0; q < 6; ++q) {
-        __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-        __builtin_amdgcn_sched_group_barrier(0x002, 7, 0);
-      }
-      fa = na;
-      fb = nb;
     }
+    // chunk k + 1 has arrived, chunk k is used up
+    asm volatile("s_waitcnt vmcnt(4) lgkmcnt(0)\n\ts_barrier" ::: "memory");
+    const int b = b0;
+    b0 = b1;
+    b1 = b2;
+    b2 = b;
   }
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+  if (!active) return;   // nothing after this point synchronises
   // 32x32 accumulator layout: register v of lane l holds row
   // 8*(v/4) + 4*(l/32) + v%4 and column l%32.
+  const int64_t b = b_lo + (lane & 31);
+  const int d0 = (int)(b - a_lo) - 4 * (lane >> 5);   // b - a of register 0
+  const unsigned lim = b < nv ? (unsigned)window : 0u;
+#pragma unroll
   for (int v = 0; v < 16; ++v) {
-    const int64_t a = a_lo + 8 * (v >> 2) + 4 * (lane >> 5) + (v & 3);
-    const int64_t b = b_lo + (lane & 31);
-    if (!(a < b && b - a <= window && b < nv)) continue;
-    ld_mark(sc, a, b, r2_min, (int64_t)(int)s_n[v], (int64_t)(int)s_x[v], (int64_t)(int)s_y[v],
-            (int64_t)(int)s_xx[v], (int64_t)(int)s_yy[v], (int64_t)(int)s_xy[v]);
+    const int ar = 8 * (v >> 2) + (v & 3);
+    if ((unsigned)(d0 - ar - 1) >= lim) continue;
+    // four times each Gram, exact integers; the differences are even
+    const int mm = (int)(4.0f * s_mm[v]), vm = (int)(4.0f * s_vm[v]), mv = (int)(4.0f * s_mv[v]);
+    const int hm = (int)(4.0f * s_hm[v]), mh = (int)(4.0f * s_mh[v]), vv = (int)(4.0f * s_vv[v]);
+    const int sx = (vm - mm) >> 1, sy = (mv - mm) >> 1;
+    ld_mark(sc, a_lo + ar + 4 * (lane >> 5), b, r2_min, mm, sx, sy, hm - sx, mh - sy,
+            (vv - vm - mv + mm) >> 2);
   }
 }
 
@@ -1664,10 +1643,8 @@ constexpr int kIbsMfmaSmem = 4 * kT * kLdsStride;
 constexpr int kIbsMfmaSimpleSmem = 2 * kT * kLdsStride;
 constexpr int kIbsPopcSmem = 2 * kPW * 3 * kP;
 constexpr int kLdPopcSmem = 2 * kLPW * 3 * kLP;
-constexpr int kLdMfmaSmem = 4 * kL * kLStride;
+constexpr int kLdMfmaSmem =
+    4 * kL * kLStride > 3 * kLdNibBuf ? 4 * kL * kLStride : 3 * kLdNibBuf;
 constexpr int kIbsRepSmem = 4 * kT * kRStride;
-constexpr int kMaxTileSmem = kIbsMfmaSmem;
-static_assert(kIbsMfmaSimpleSmem <= kMaxTileSmem && kIbsPopcSmem <= kMaxTileSmem &&
-              kLdPopcSmem <= kMaxTileSmem && kLdMfmaSmem <= kMaxTileSmem, "LDS budget");
 
 }  // namespace pg
