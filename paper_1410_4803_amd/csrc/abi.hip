@@ -285,9 +285,12 @@ int ld_pairs(const Sel& s, const LdPlan& p, char* ws, int32_t window, double r2_
     return launch_ld_popc(D, p.words, s.nv, p.rows_pad, window, r2_min, sc, st);
   }
   uint32_t* E = p.off_E >= 0 ? (uint32_t*)(ws + p.off_E) : nullptr;
-  rc = E ? launch_ld_layout(s, D, E, p.rows_pad, p.words, st)
-         : launch_variant_major_2bit(s, D, p.rows_pad, p.words, st);
-  if (rc == PG_OK) rc = ld_clear(sc, p.rows_pad, st);
+  if (E) {
+    rc = launch_ld_layout(s, D, E, p.rows_pad, p.words, sc, st);
+  } else {
+    rc = launch_variant_major_2bit(s, D, p.rows_pad, p.words, st);
+    if (rc == PG_OK) rc = ld_clear(sc, p.rows_pad, st);
+  }
   if (p.path == PG_PATH_MFMA) {
     mark_stage(1, st);
     if (rc != PG_OK) return rc;

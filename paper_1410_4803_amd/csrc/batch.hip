@@ -164,6 +164,15 @@ struct ProblemPlan {
   double tile_cost;
 };
 
+// LD problems whose operands one launch lays out.
+bool ld_layout_job(const ProblemPlan& q) {
+  return q.p.kind == PG_KIND_LD && q.off_e >= 0 && !q.s.idx;
+}
+LdScratch ld_scratch(const ProblemPlan& q, char* ws) {
+  return LdScratch{(uint32_t*)(ws + q.off_bm), q.bm_words, (uint32_t*)(ws + q.off_cnt),
+                   (int64_t*)(ws + q.off_off), (int64_t*)(ws + q.off_bsum)};
+}
+
 }  // namespace
 
 struct pg_plan {
@@ -176,6 +185,12 @@ struct pg_plan {
   // sample list run as one launch (LayoutJob table at off_jobs)
   int64_t off_jobs = 0, job_blocks = 0;
   int n_jobs = 0;
+  // the same for the LD problems with a nibble operand and no sample list
+  // (LdLayoutJob table), and the scans and emissions of every LD problem
+  // (LdFinishJob table: those on 2-bit words, then those on bit planes)
+  int64_t off_ld_jobs = 0, ld_job_blocks = 0, off_finish = 0;
+  int n_ld_jobs = 0, n_finish[2] = {0, 0};
+  int64_t max_capacity[2] = {0, 0};
   int grid[kParts] = {256, 256, 256};
   const void* uploaded_ws = nullptr;
   // the LD branch runs on a stream of the plan's own, forked from and
@@ -283,8 +298,19 @@ int pg_batch_plan(const pg_problem* probs, int n_probs, pg_plan** out) {
       ++plan->n_jobs;
       plan->job_blocks += sample_major_job_blocks(q.rows_pad, q.words);
     }
+    if (q.p.kind != PG_KIND_LD) continue;
+    if (ld_layout_job(q)) {
+      ++plan->n_ld_jobs;
+      plan->ld_job_blocks += ld_layout_blocks(q.rows_pad, q.words);
+    }
+    const int f = q.path == PG_PATH_POPC;   // `order` has the parts in this order
+    ++plan->n_finish[f];
+    plan->max_capacity[f] = std::max(plan->max_capacity[f], q.p.capacity);
   }
   plan->off_jobs = take(off, (int64_t)sizeof(LayoutJob) * std::max(plan->n_jobs, 1));
+  plan->off_ld_jobs = take(off, (int64_t)sizeof(LdLayoutJob) * std::max(plan->n_ld_jobs, 1));
+  plan->off_finish = take(off, (int64_t)sizeof(LdFinishJob) *
+                                   std::max(plan->n_finish[0] + plan->n_finish[1], 1));
   plan->off_counter = take(off, 8 * kCounters);   // tile counters: 8 (IBS) + 2 (LD)
   plan->bytes = off;
   // persistent grids: resident blocks of each kernel on this device
@@ -357,8 +383,7 @@ int pg_batch_upload(pg_plan* plan, void* workspace, size_t workspace_bytes, void
       it.n_band = q.n_band;
       it.nv = q.s.nv;
       it.r2_min = q.p.r2_min;
-      it.sc = LdScratch{(uint32_t*)(ws + q.off_bm), q.bm_words, (uint32_t*)(ws + q.off_cnt),
-                        (int64_t*)(ws + q.off_off), (int64_t*)(ws + q.off_bsum)};
+      it.sc = ld_scratch(q, ws);
     }
     items.push_back(it);
     t += q.ntiles;
@@ -378,17 +403,35 @@ int pg_batch_upload(pg_plan* plan, void* workspace, size_t workspace_bytes, void
     jobs.push_back(j);
     jb += sample_major_job_blocks(q.rows_pad, q.words);
   }
+  std::vector<LdLayoutJob> ld_jobs;
+  std::vector<LdFinishJob> finish;
+  jb = 0;
+  for (int k : plan->order) {
+    const ProblemPlan& q = plan->probs[k];
+    if (q.p.kind != PG_KIND_LD) continue;
+    uint32_t* X = (uint32_t*)(ws + q.off_x);
+    if (ld_layout_job(q)) {
+      ld_jobs.push_back(LdLayoutJob{q.s, X, (uint32_t*)(ws + q.off_e), q.words, jb,
+                                    ld_scratch(q, ws), rows_dword_aligned(q.s) ? 1 : 0});
+      jb += ld_layout_blocks(q.rows_pad, q.words);
+    }
+    finish.push_back(LdFinishJob{X, q.words, q.rows_pad, q.s.nv, q.s.v0, ld_scratch(q, ws),
+                                 q.p.out, q.p.capacity, q.p.n_out});
+  }
   hipStream_t st = (hipStream_t)stream;
+  auto upload = [&](int64_t at, const void* from, size_t bytes) {
+    return bytes == 0 ||
+           hipMemcpyAsync(ws + at, from, bytes, hipMemcpyHostToDevice, st) == hipSuccess;
+  };
   if (!plan->side &&
       (hipStreamCreateWithFlags(&plan->side, hipStreamNonBlocking) != hipSuccess ||
        hipEventCreateWithFlags(&plan->fork, hipEventDisableTiming) != hipSuccess ||
        hipEventCreateWithFlags(&plan->join, hipEventDisableTiming) != hipSuccess))
     return fail(PG_EDEVICE, "batch stream and events: %s", hipGetErrorString(hipGetLastError()));
-  if (hipMemcpyAsync(ws + plan->off_items, items.data(), sizeof(BatchItem) * items.size(),
-                     hipMemcpyHostToDevice, st) != hipSuccess ||
-      (!jobs.empty() &&
-       hipMemcpyAsync(ws + plan->off_jobs, jobs.data(), sizeof(LayoutJob) * jobs.size(),
-                      hipMemcpyHostToDevice, st) != hipSuccess) ||
+  if (!upload(plan->off_items, items.data(), sizeof(BatchItem) * items.size()) ||
+      !upload(plan->off_jobs, jobs.data(), sizeof(LayoutJob) * jobs.size()) ||
+      !upload(plan->off_ld_jobs, ld_jobs.data(), sizeof(LdLayoutJob) * ld_jobs.size()) ||
+      !upload(plan->off_finish, finish.data(), sizeof(LdFinishJob) * finish.size()) ||
       hipStreamSynchronize(st) != hipSuccess)
     return fail(PG_EDEVICE, "tile table upload failed: %s", hipGetErrorString(hipGetLastError()));
   plan->uploaded_ws = workspace;
@@ -439,18 +482,26 @@ int pg_batch_launch(const pg_plan* plan, void* workspace, size_t workspace_bytes
   }
   mark_stage(1, st);
   // LD branch on `side`: layouts and scratch clearing, the tile counters,
-  // the persistent kernels, the scans and emits
+  // the persistent kernels, the scans and emissions.  Layouts, scans and
+  // emissions are one launch each for all problems: 16 problems (8 LD of
+  // 200-5,000 x 2,000-20,000) took 1.04 ms with four launches of 4 to 14 us per
+  // problem after the tiles, and takes 0.72 ms with two in all.
+  rc = launch_ld_layout_jobs((const LdLayoutJob*)(ws + plan->off_ld_jobs), plan->n_ld_jobs,
+                             plan->ld_job_blocks, side);
+  if (rc != PG_OK) return rc;
   for (int k : plan->order) {
     const ProblemPlan& q = plan->probs[k];
-    if (q.p.kind != PG_KIND_LD) continue;
+    if (q.p.kind != PG_KIND_LD || ld_layout_job(q)) continue;
     uint32_t* X = (uint32_t*)(ws + q.off_x);
-    rc = q.off_e >= 0
-             ? launch_ld_layout(q.s, X, (uint32_t*)(ws + q.off_e), q.rows_pad, q.words, side)
-         : q.path == PG_PATH_MFMA ? launch_variant_major_2bit(q.s, X, q.rows_pad, q.words, side)
-                                : launch_ld_planes(q.s, X, q.rows_pad, q.words, side);
-    const LdScratch sc{(uint32_t*)(ws + q.off_bm), q.bm_words, (uint32_t*)(ws + q.off_cnt),
-                       (int64_t*)(ws + q.off_off), (int64_t*)(ws + q.off_bsum)};
-    if (rc == PG_OK) rc = ld_clear(sc, q.rows_pad, side);
+    const LdScratch sc = ld_scratch(q, ws);
+    if (q.off_e >= 0) {
+      rc = launch_ld_layout(q.s, X, (uint32_t*)(ws + q.off_e), q.rows_pad, q.words, sc, side);
+    } else {
+      rc = q.path == PG_PATH_MFMA
+               ? launch_variant_major_2bit(q.s, X, q.rows_pad, q.words, side)
+               : launch_ld_planes(q.s, X, q.rows_pad, q.words, side);
+      if (rc == PG_OK) rc = ld_clear(sc, q.rows_pad, side);
+    }
     if (rc != PG_OK) return rc;
   }
   if (pb[3] > pb[1]) {
@@ -467,13 +518,13 @@ int pg_batch_launch(const pg_plan* plan, void* workspace, size_t workspace_bytes
   if (rc != PG_OK) return rc;
   for (int k : plan->order) {
     const ProblemPlan& q = plan->probs[k];
-    if (q.p.kind != PG_KIND_LD) continue;
-    const LdScratch sc{(uint32_t*)(ws + q.off_bm), q.bm_words, (uint32_t*)(ws + q.off_cnt),
-                       (int64_t*)(ws + q.off_off), (int64_t*)(ws + q.off_bsum)};
-    rc = launch_ld_finish((uint32_t*)(ws + q.off_x), q.path == PG_PATH_POPC, q.words, q.rows_pad,
-                          q.s.nv, q.s.v0, sc, q.p.out, q.p.capacity, q.p.n_out, side, false);
+    if (q.p.kind != PG_KIND_LD || q.s.nv <= kLdScanJobRows) continue;
+    rc = scan_ld_rows(ld_scratch(q, ws), q.s.nv, q.p.n_out, side);
     if (rc != PG_OK) return rc;
   }
+  rc = launch_ld_finish_jobs((const LdFinishJob*)(ws + plan->off_finish), plan->n_finish[0],
+                             plan->n_finish[1], plan->max_capacity, side);
+  if (rc != PG_OK) return rc;
   // join: `st` continues once the LD branch is done
   if (hipEventRecord(plan->join, side) != hipSuccess ||
       hipStreamWaitEvent(st, plan->join, 0) != hipSuccess)

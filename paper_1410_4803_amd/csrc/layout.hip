@@ -543,18 +543,20 @@ __device__ __forceinline__ uint2 ld_nibbles(uint32_t w) {
 // group in order.  A block takes 64 variants x 32 words: 128-byte runs of a
 // row in, the same of D out, and whole 2 KB steps of E by way of LDS (a step's
 // halves lie 260 words apart there, so the 16 a half-wave writes fall in
-// different banks).  kFromD: D is there already (a sample list's layout).
+// different banks).  The blocks of a group also clear its rows of the emission
+// scratch.  kFromD: D is there already (a sample list's layout).
 constexpr int kLyRows = 64, kLyWords = 32;
 
 template <bool kFromD>
-__global__ __launch_bounds__(256) void k_ld_layout(Sel s, uint32_t* __restrict__ D,
-                                                   uint32_t* __restrict__ E, int64_t rows_pad,
-                                                   int64_t wn, int aligned) {
-  __shared__ uint32_t s_e[16 * 260];
+__device__ __forceinline__ void ld_layout_block(const Sel& s, uint32_t* __restrict__ D,
+                                                uint32_t* __restrict__ E, int64_t wn, bool aligned,
+                                                const LdScratch& sc, int64_t blk, uint32_t* s_e) {
   const int64_t nb_w = ceil_div(wn, kLyWords);
-  const int64_t blk = xcd_swizzle(blockIdx.x, gridDim.x);
   const int64_t G = blk / nb_w, w0 = blk % nb_w * kLyWords;
   const int t = threadIdx.x, g = t & 31;
+  const int64_t bits = kLyRows * sc.bm_words;
+  for (int64_t i = blk % nb_w * 256 + t; i < bits; i += nb_w * 256) sc.bitmap[G * bits + i] = 0u;
+  if (w0 == 0 && t < kLyRows) sc.rowcnt[G * kLyRows + t] = 0u;
   int64_t vr[8], gr[8];
   uint32_t x[8];
 #pragma unroll
@@ -566,7 +568,7 @@ __global__ __launch_bounds__(256) void k_ld_layout(Sel s, uint32_t* __restrict__
 #pragma unroll
     for (int u = 0; u < 8; ++u) x[u] = gr[u] < wn ? D[vr[u] * wn + gr[u]] : kAllMissing16;
   } else {
-    row_words16(s, vr, gr, aligned != 0, x);
+    row_words16(s, vr, gr, aligned, x);
   }
 #pragma unroll
   for (int u = 0; u < 8; ++u) {
@@ -588,17 +590,51 @@ __global__ __launch_bounds__(256) void k_ld_layout(Sel s, uint32_t* __restrict__
   }
 }
 
+template <bool kFromD>
+__global__ __launch_bounds__(256) void k_ld_layout(Sel s, uint32_t* __restrict__ D,
+                                                   uint32_t* __restrict__ E, int64_t wn,
+                                                   int aligned, LdScratch sc) {
+  __shared__ uint32_t s_e[16 * 260];
+  ld_layout_block<kFromD>(s, D, E, wn, aligned != 0, sc, xcd_swizzle(blockIdx.x, gridDim.x), s_e);
+}
+
+// Many problems in one launch, as k_sample_major_jobs.
+__global__ __launch_bounds__(256) void k_ld_layout_jobs(const LdLayoutJob* __restrict__ jobs,
+                                                        int n_jobs) {
+  __shared__ uint32_t s_e[16 * 260];
+  const int64_t b = blockIdx.x;
+  int lo = 0, hi = n_jobs - 1;
+  while (lo < hi) {   // the last job with block_begin <= b
+    const int mid = (lo + hi + 1) / 2;
+    if (jobs[mid].block_begin <= b) lo = mid; else hi = mid - 1;
+  }
+  const LdLayoutJob j = jobs[lo];
+  ld_layout_block<false>(j.s, j.D, j.E, j.wn, j.aligned != 0, j.sc, b - j.block_begin, s_e);
+}
+
+int64_t ld_layout_blocks(int64_t rows_pad, int64_t wn) {
+  return rows_pad / kLyRows * ceil_div(wn, kLyWords);
+}
+
+int launch_ld_layout_jobs(const LdLayoutJob* jobs, int n_jobs, int64_t total_blocks,
+                          hipStream_t st) {
+  if (n_jobs <= 0 || total_blocks <= 0) return PG_OK;
+  hipLaunchKernelGGL(k_ld_layout_jobs, dim3((unsigned)total_blocks), dim3(256), 0, st, jobs,
+                     n_jobs);
+  return check_launch("ld_layout_jobs");
+}
+
 int launch_ld_layout(const Sel& s, uint32_t* D, uint32_t* E, int64_t rows_pad, int64_t wn,
-                     hipStream_t st) {
-  const dim3 grid((unsigned)(rows_pad / kLyRows * ceil_div(wn, kLyWords)));
+                     const LdScratch& sc, hipStream_t st) {
+  const dim3 grid((unsigned)ld_layout_blocks(rows_pad, wn));
   if (!s.idx) {
-    hipLaunchKernelGGL(k_ld_layout<false>, grid, dim3(256), 0, st, s, D, E, rows_pad, wn,
-                       (int)rows_dword_aligned(s));
+    hipLaunchKernelGGL(k_ld_layout<false>, grid, dim3(256), 0, st, s, D, E, wn,
+                       (int)rows_dword_aligned(s), sc);
     return check_launch("ld_layout");
   }
   int rc = launch_variant_major_2bit(s, D, rows_pad, wn, st);
   if (rc != PG_OK) return rc;
-  hipLaunchKernelGGL(k_ld_layout<true>, grid, dim3(256), 0, st, s, D, E, rows_pad, wn, 0);
+  hipLaunchKernelGGL(k_ld_layout<true>, grid, dim3(256), 0, st, s, D, E, wn, 0, sc);
   return check_launch("ld_layout");
 }
 

@@ -124,12 +124,6 @@ int launch_sample_major_jobs(const LayoutJob* jobs, int n_jobs, int64_t total_bl
 int launch_variant_major_2bit(const Sel& s, uint32_t* D, int64_t rows_pad, int64_t wn,
                               hipStream_t st);
 
-// The same, and beside it the nibble operand E of the fp4 LD tile: 64 variants
-// x 64 samples in 512 words (rows_pad * wn * 2 words in all; wn a multiple of
-// 16).
-int launch_ld_layout(const Sel& s, uint32_t* D, uint32_t* E, int64_t rows_pad, int64_t wn,
-                     hipStream_t st);
-
 // Variant-major bit planes for the popcount LD path: for 32-sample word w,
 // plane p (0 = homozygous A2, 1 = homozygous A1, 2 = non-missing) of selected
 // variant v at P[(w*3 + p)*rows_pad + v]; words_pad words.
@@ -269,6 +263,24 @@ struct LdScratch {
 // Number of per-block partial sums the row-offset scan needs.
 int ld_scan_blocks(int64_t nv);
 
+// The LD operands: D as launch_variant_major_2bit, and beside it the nibble
+// operand E of the fp4 tile: 64 variants x 64 samples in 512 words (rows_pad *
+// wn * 2 words in all; wn a multiple of 16).  Clears sc's bitmap and counts.
+int launch_ld_layout(const Sel& s, uint32_t* D, uint32_t* E, int64_t rows_pad, int64_t wn,
+                     const LdScratch& sc, hipStream_t st);
+// The same for a device array of problems without a sample list, in one launch
+// (increasing block_begin, ld_layout_blocks each).
+struct LdLayoutJob {
+  Sel s;
+  uint32_t *D, *E;
+  int64_t wn, block_begin;
+  LdScratch sc;
+  int aligned;   // rows_dword_aligned(s)
+};
+int64_t ld_layout_blocks(int64_t rows_pad, int64_t wn);
+int launch_ld_layout_jobs(const LdLayoutJob* jobs, int n_jobs, int64_t total_blocks,
+                          hipStream_t st);
+
 constexpr int kLdPopcKWords = 16;     // 32-bit plane words per K chunk
 
 // Missing-call correction path (ldsparse.hip): per-variant missing-call
@@ -345,9 +357,25 @@ int launch_ld_popc(const uint32_t* P, int64_t words_pad, int64_t nv, int64_t row
 // Row-offset scan, *n_out, and the emit kernel.  X is the operand the pair
 // kernel used: 2-bit words (rows x words) or bit planes (planes == true).
 // `marks` records stage events 3 and 4 (one-problem calls only).
+// Scan and emission of many problems at once: a device array of them, the
+// first n_words on 2-bit words and the rest on bit planes; max_capacity[] of
+// the two parts.  Rows up to kLdScanJobRows; the others need scan_ld_rows
+// before.
+struct LdFinishJob {
+  const uint32_t* X;
+  int64_t words, rows_pad, nv, v0;
+  LdScratch sc;
+  pg_ld_pair* out;
+  int64_t capacity;
+  int64_t* n_out;
+};
+constexpr int64_t kLdScanJobRows = 131072;
+int scan_ld_rows(const LdScratch& sc, int64_t nv, int64_t* n_out, hipStream_t st);
+int launch_ld_finish_jobs(const LdFinishJob* jobs, int n_words, int n_planes,
+                          const int64_t* max_capacity, hipStream_t st);
 int launch_ld_finish(const uint32_t* X, bool planes, int64_t words, int64_t rows_pad, int64_t nv,
                      int64_t v0, const LdScratch& sc, pg_ld_pair* out, int64_t capacity,
-                     int64_t* n_out, hipStream_t st, bool marks = true);
+                     int64_t* n_out, hipStream_t st);
 
 // ---- LD pruning (prune.hip) -------------------------------------------------
 // Per selected variant: {minor allele count, non-missing calls (at least 1)}
