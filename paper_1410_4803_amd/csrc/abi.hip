@@ -126,9 +126,8 @@ int make_sel(const pg_genotypes* g, bool list, const int32_t* idx, int64_t n_sel
 // path wins on data with few missing calls from 5,000 samples and windows
 // of 500 (up to 1.52x at 20,000 samples, window 1,000) and the dense fp4
 // kernel everywhere else, so the missing rate decides: there AUTO takes the
-// correction path behind a sampled gate (kLdGated) that counts the missing
-// calls of about 4,096 variants and leaves the path off, for the cost of
-// that count, unless a tile would hold few enough of them on average.
+// correction path, which leaves itself off unless enough groups of variants
+// have few enough missing calls (kLdGated: half of them).
 int ibs_auto_path(int64_t m, int64_t nv) {
   (void)m;
   (void)nv;
@@ -141,9 +140,9 @@ int ld_auto_path(int64_t m, int64_t nv, int32_t window) {
 }
 
 // Variant bits of the correction path: every tile whose lists fit (1), the
-// diagnostic records (2, implies 1), the sampled gate (8; what AUTO sets).
+// diagnostic records (2, implies 1), on only if half of the groups qualify
+// instead of a quarter (8; what AUTO sets).
 constexpr int kLdAllTiles = 1, kLdDiag = 2, kLdGated = 8;
-constexpr int64_t kLdGateSamples = 4096;   // variants the gate samples (about)
 
 // Resolves the kernel variant: 0 (or an undefined code) is the default, the
 // pipelined fp4 kernel; fp4 variants fall back to the pipelined int8 kernel
@@ -194,7 +193,8 @@ int plan_ibs(const Sel& s, int path_arg, IbsPlan& p) {
 struct LdPlan {
   int path, variant;
   int64_t rows_pad, words, bm_words;
-  int64_t off_E;   // nibble operand of the fp4 tiles (-1: none)
+  int64_t off_E;      // nibble operand of the fp4 tiles (-1: none)
+  int64_t off_part;   // partial code counts of the layout (-1: bit planes)
   int64_t off_D, off_bm, off_cnt, off_off, off_bsum, bytes;
   // correction path: sample-major operand (t_rows x t_words), lists, stats
   int64_t t_rows, t_words, off_T, off_lists, off_vst, off_gsum, off_gmax, off_any;
@@ -234,6 +234,8 @@ int plan_ld(const Sel& s, int32_t window, int path_arg, LdPlan& p) {
   const bool fp4 = s.m < kLdFp4MaxSamples &&
       (path == PG_PATH_SPARSE || (path == PG_PATH_MFMA && p.variant == kLdVariantFp4));
   p.off_E = fp4 ? c.take(2 * operand_bytes) : -1;
+  p.off_part = path == PG_PATH_POPC
+                   ? -1 : c.take(p.rows_pad * ceil_div(p.words, kLdCountWords) * 4);
   p.off_bm = c.take(p.rows_pad * p.bm_words * 4);
   p.off_cnt = c.take(p.rows_pad * 4);
   p.off_off = c.take((p.rows_pad + 1) * 8);
@@ -247,7 +249,7 @@ int plan_ld(const Sel& s, int32_t window, int path_arg, LdPlan& p) {
     p.off_vst = c.take(p.rows_pad * 16);
     p.off_gsum = c.take(p.rows_pad / kLdTile * 8);
     p.off_gmax = c.take(p.rows_pad / kLdTile * 4);
-    p.off_any = c.take(16);   // groups_ok, then the gate's 64-bit count at +8
+    p.off_any = c.take(16);   // groups_ok
   }
   p.bytes = c.off;
   return PG_OK;
@@ -268,51 +270,46 @@ int64_t ld_sparse_budget(const LdPlan& p, int64_t m) {
 }
 uint32_t ld_sparse_min_groups(const LdPlan& p) {
   const int64_t g = p.rows_pad / kLdTile;
-  return p.variant & (kLdAllTiles | kLdDiag) ? 1u : (uint32_t)(g < 4 ? 1 : g / 4);
+  if (p.variant & (kLdAllTiles | kLdDiag)) return 1u;
+  const int64_t need = p.variant & kLdGated ? g / 2 : g / 4;
+  return (uint32_t)(need < 1 ? 1 : need);
 }
 
 // Operand layouts and the pair kernels of an LD plan, up to the emission
-// bitmap (stage events 1 and 2).
+// bitmap (stage events 1 and 2); with `stats` also the variants' allele counts.
 int ld_pairs(const Sel& s, const LdPlan& p, char* ws, int32_t window, double r2_min,
-             const LdScratch& sc, hipStream_t st, pg_ld_pair* dbg = nullptr) {
+             const LdScratch& sc, hipStream_t st, pg_ld_pair* dbg = nullptr,
+             int2* stats = nullptr) {
   uint32_t* D = (uint32_t*)(ws + p.off_D);
   int rc;
   if (p.path == PG_PATH_POPC) {
     rc = launch_ld_planes(s, D, p.rows_pad, p.words, st);
     if (rc == PG_OK) rc = ld_clear(sc, p.rows_pad, st);
     mark_stage(1, st);
+    if (rc == PG_OK && stats)
+      rc = launch_variant_stats(D, p.words, p.rows_pad, s.nv, stats, st);
     if (rc != PG_OK) return rc;
     return launch_ld_popc(D, p.words, s.nv, p.rows_pad, window, r2_min, sc, st);
   }
   uint32_t* E = p.off_E >= 0 ? (uint32_t*)(ws + p.off_E) : nullptr;
-  if (E) {
-    rc = launch_ld_layout(s, D, E, p.rows_pad, p.words, sc, st);
-  } else {
-    rc = launch_variant_major_2bit(s, D, p.rows_pad, p.words, st);
-    if (rc == PG_OK) rc = ld_clear(sc, p.rows_pad, st);
-  }
+  LdCounts cn{nullptr, nullptr};
+  if (stats || p.path == PG_PATH_SPARSE) cn.part = (uint32_t*)(ws + p.off_part);
+  if (p.path == PG_PATH_SPARSE) cn.any = (uint32_t*)(ws + p.off_any);
+  rc = launch_ld_layout(s, D, E, p.rows_pad, p.words, sc, cn, st);
   if (p.path == PG_PATH_MFMA) {
+    if (rc == PG_OK && stats)
+      rc = launch_ld_totals(cn, p.words, s.m, s.nv, p.rows_pad, stats, nullptr, st);
     mark_stage(1, st);
     if (rc != PG_OK) return rc;
     return launch_ld_mfma(D, E, p.words, s.nv, p.rows_pad, window, r2_min, sc, st);
   }
   LdSparse sp{(uint32_t*)(ws + p.off_lists), (int4*)(ws + p.off_vst), (int64_t*)(ws + p.off_gsum),
               (int*)(ws + p.off_gmax), (uint32_t*)(ws + p.off_any), ld_sparse_min_groups(p),
-              p.cap, ld_sparse_budget(p, s.m), nullptr, 0, 1};
-  if (p.variant & kLdGated) {
-    // on when the sampled variants' mean, times the 128 variants of a tile,
-    // is within the tile budget: count <= budget * n_samp / 128
-    sp.gate = (uint64_t*)(ws + p.off_any + 8);
-    sp.gate_stride = s.nv > kLdGateSamples ? s.nv / kLdGateSamples : 1;
-    const int64_t n_samp = ceil_div(s.nv, sp.gate_stride);
-    sp.gate_max = sp.budget == INT64_MAX
-                      ? UINT64_MAX
-                      : (uint64_t)(sp.budget / (2 * kLdTile) * n_samp +
-                                   sp.budget % (2 * kLdTile) * n_samp / (2 * kLdTile));
-  }
+              p.cap, ld_sparse_budget(p, s.m)};
   uint32_t* T = (uint32_t*)(ws + p.off_T);
-  if (rc == PG_OK) rc = launch_ld_sparse_stats(D, p.words, s.m, s.nv, p.rows_pad, sp, st);
-  // the sample-major operand only when the path is on
+  if (rc == PG_OK)
+    rc = launch_ld_totals(cn, p.words, s.m, s.nv, p.rows_pad, stats, &sp, st);
+  if (rc == PG_OK) rc = launch_ld_lists(D, p.words, s.m, s.nv, sp, st);
   if (rc == PG_OK) rc = launch_ld_transpose(D, p.rows_pad, p.words, T, p.t_rows, p.t_words, sp, st);
   mark_stage(1, st);
   if (rc != PG_OK) return rc;
@@ -667,16 +664,13 @@ int pg_ld_prune(const pg_genotypes* g, const int32_t* sample_idx, int64_t n_sel,
   hipStream_t st = (hipStream_t)stream;
   char* ws = (char*)workspace;
   const LdPlan& q = p.ld;
-  uint32_t* D = (uint32_t*)(ws + q.off_D);
   LdScratch sc{(uint32_t*)(ws + q.off_bm), q.bm_words, (uint32_t*)(ws + q.off_cnt),
                (int64_t*)(ws + q.off_off), (int64_t*)(ws + q.off_bsum)};
   int2* stats = (int2*)(ws + p.off_stats);
-  const bool planes = q.path == PG_PATH_POPC;
   // r2 > t  <=>  r2 >= the next double above t
   const double r2_min = nextafter(r2_threshold, INFINITY);
   mark_stage(0, st);
-  rc = ld_pairs(s, q, ws, window - 1, r2_min, sc, st);
-  if (rc == PG_OK) rc = launch_variant_stats(D, planes, q.words, q.rows_pad, s.nv, stats, st);
+  rc = ld_pairs(s, q, ws, window - 1, r2_min, sc, st, nullptr, stats);
   mark_stage(3, st);
   if (rc == PG_OK)
     rc = launch_prune_greedy(sc, stats, (uint32_t*)(ws + p.off_drop), (uint16_t*)(ws + p.off_cc),

@@ -164,9 +164,12 @@ struct ProblemPlan {
   double tile_cost;
 };
 
+uint32_t* nibbles(const ProblemPlan& q, char* ws) {
+  return q.off_e >= 0 ? (uint32_t*)(ws + q.off_e) : nullptr;
+}
 // LD problems whose operands one launch lays out.
 bool ld_layout_job(const ProblemPlan& q) {
-  return q.p.kind == PG_KIND_LD && q.off_e >= 0 && !q.s.idx;
+  return q.p.kind == PG_KIND_LD && q.path == PG_PATH_MFMA && !q.s.idx;
 }
 LdScratch ld_scratch(const ProblemPlan& q, char* ws) {
   return LdScratch{(uint32_t*)(ws + q.off_bm), q.bm_words, (uint32_t*)(ws + q.off_cnt),
@@ -378,7 +381,7 @@ int pg_batch_upload(pg_plan* plan, void* workspace, size_t workspace_bytes, void
                     (q.p.out_layout & ~PG_COUNTS_U16) == PG_FULL,
                     (q.p.out_layout & PG_COUNTS_U16) ? 1 : 0};
     } else {
-      it.E = q.off_e >= 0 ? (const uint32_t*)(ws + q.off_e) : nullptr;
+      it.E = nibbles(q, ws);
       it.window = q.p.window;
       it.n_band = q.n_band;
       it.nv = q.s.nv;
@@ -411,7 +414,7 @@ int pg_batch_upload(pg_plan* plan, void* workspace, size_t workspace_bytes, void
     if (q.p.kind != PG_KIND_LD) continue;
     uint32_t* X = (uint32_t*)(ws + q.off_x);
     if (ld_layout_job(q)) {
-      ld_jobs.push_back(LdLayoutJob{q.s, X, (uint32_t*)(ws + q.off_e), q.words, jb,
+      ld_jobs.push_back(LdLayoutJob{q.s, X, nibbles(q, ws), q.words, jb,
                                     ld_scratch(q, ws), rows_dword_aligned(q.s) ? 1 : 0});
       jb += ld_layout_blocks(q.rows_pad, q.words);
     }
@@ -494,12 +497,10 @@ int pg_batch_launch(const pg_plan* plan, void* workspace, size_t workspace_bytes
     if (q.p.kind != PG_KIND_LD || ld_layout_job(q)) continue;
     uint32_t* X = (uint32_t*)(ws + q.off_x);
     const LdScratch sc = ld_scratch(q, ws);
-    if (q.off_e >= 0) {
-      rc = launch_ld_layout(q.s, X, (uint32_t*)(ws + q.off_e), q.rows_pad, q.words, sc, side);
+    if (q.path == PG_PATH_MFMA) {
+      rc = launch_ld_layout(q.s, X, nibbles(q, ws), q.rows_pad, q.words, sc, LdCounts{}, side);
     } else {
-      rc = q.path == PG_PATH_MFMA
-               ? launch_variant_major_2bit(q.s, X, q.rows_pad, q.words, side)
-               : launch_ld_planes(q.s, X, q.rows_pad, q.words, side);
+      rc = launch_ld_planes(q.s, X, q.rows_pad, q.words, side);
       if (rc == PG_OK) rc = ld_clear(sc, q.rows_pad, side);
     }
     if (rc != PG_OK) return rc;

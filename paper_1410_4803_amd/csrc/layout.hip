@@ -543,20 +543,25 @@ __device__ __forceinline__ uint2 ld_nibbles(uint32_t w) {
 // group in order.  A block takes 64 variants x 32 words: 128-byte runs of a
 // row in, the same of D out, and whole 2 KB steps of E by way of LDS (a step's
 // halves lie 260 words apart there, so the 16 a half-wave writes fall in
-// different banks).  The blocks of a group also clear its rows of the emission
-// scratch.  kFromD: D is there already (a sample list's layout).
+// different banks).  E and cn.part may be NULL.  cn.part: per block and variant
+// the homozygous A2, homozygous A1 and missing calls of its 512 samples (padding
+// counts as missing), 10 bits each, from the nibbles in LDS.  The blocks of a
+// group also clear its rows of the emission scratch, the first one cn.any.
+// kFromD: D is there already (a sample list's layout).
 constexpr int kLyRows = 64, kLyWords = 32;
 
 template <bool kFromD>
 __device__ __forceinline__ void ld_layout_block(const Sel& s, uint32_t* __restrict__ D,
-                                                uint32_t* __restrict__ E, int64_t wn, bool aligned,
-                                                const LdScratch& sc, int64_t blk, uint32_t* s_e) {
+                                                uint32_t* __restrict__ E, int64_t rows_pad,
+                                                int64_t wn, bool aligned, const LdScratch& sc,
+                                                const LdCounts& cn, int64_t blk, uint32_t* s_e) {
   const int64_t nb_w = ceil_div(wn, kLyWords);
   const int64_t G = blk / nb_w, w0 = blk % nb_w * kLyWords;
   const int t = threadIdx.x, g = t & 31;
   const int64_t bits = kLyRows * sc.bm_words;
   for (int64_t i = blk % nb_w * 256 + t; i < bits; i += nb_w * 256) sc.bitmap[G * bits + i] = 0u;
   if (w0 == 0 && t < kLyRows) sc.rowcnt[G * kLyRows + t] = 0u;
+  if (cn.any && blk == 0 && t < 2) cn.any[t] = 0u;
   int64_t vr[8], gr[8];
   uint32_t x[8];
 #pragma unroll
@@ -580,28 +585,55 @@ __device__ __forceinline__ void ld_layout_block(const Sel& s, uint32_t* __restri
   }
   __syncthreads();
   const int64_t nsteps = wn / 4, step0 = w0 / 4;
+  if (E) {
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const int o = u * 256 + t;             // 16-byte piece: step o / 128 of the block's eight
+      const int64_t step = step0 + (o >> 7);
+      if (step < nsteps)
+        *reinterpret_cast<uint4*>(E + (G * nsteps + step) * 512 + 4 * (o & 127)) =
+            *reinterpret_cast<const uint4*>(&s_e[(o >> 6) * 260 + 4 * (o & 63)]);
+    }
+  }
+  if (!cn.part) return;
+  // a quarter of a variant's samples per thread (a wave: 64 variants)
+  uint32_t n3 = 0, n0 = 0, called = 0;
 #pragma unroll
   for (int u = 0; u < 4; ++u) {
-    const int o = u * 256 + t;             // 16-byte piece: step o / 128 of the block's eight
-    const int64_t step = step0 + (o >> 7);
-    if (step < nsteps)
-      *reinterpret_cast<uint4*>(E + (G * nsteps + step) * 512 + 4 * (o & 127)) =
-          *reinterpret_cast<const uint4*>(&s_e[(o >> 6) * 260 + 4 * (o & 63)]);
+    const uint4 q = *reinterpret_cast<const uint4*>(&s_e[(4 * (t >> 6) + u) * 260 + 4 * (t & 63)]);
+    const uint32_t n[4] = {q.x, q.y, q.z, q.w};
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      n3 += __popc(n[e] & 0x22222222u);
+      n0 += __popc(n[e] & 0x88888888u);
+      called += __popc(n[e] & 0x11111111u);
+    }
+  }
+  __syncthreads();
+  s_e[t] = n3 | n0 << 10 | (128 - called) << 20;
+  __syncthreads();
+  if (t < kLyRows) {
+    const int64_t words = wn - w0 < kLyWords ? wn - w0 : kLyWords;   // those past wn: missing
+    cn.part[w0 / kLyWords * rows_pad + G * kLyRows + t] =
+        s_e[t] + s_e[64 + t] + s_e[128 + t] + s_e[192 + t] -
+        ((uint32_t)(16 * (kLyWords - words)) << 20);
   }
 }
 
 template <bool kFromD>
 __global__ __launch_bounds__(256) void k_ld_layout(Sel s, uint32_t* __restrict__ D,
-                                                   uint32_t* __restrict__ E, int64_t wn,
-                                                   int aligned, LdScratch sc) {
-  __shared__ uint32_t s_e[16 * 260];
-  ld_layout_block<kFromD>(s, D, E, wn, aligned != 0, sc, xcd_swizzle(blockIdx.x, gridDim.x), s_e);
+                                                   uint32_t* __restrict__ E, int64_t rows_pad,
+                                                   int64_t wn, int aligned, LdScratch sc,
+                                                   LdCounts cn) {
+  __shared__ __attribute__((aligned(16))) uint32_t s_e[16 * 260];
+  ld_layout_block<kFromD>(s, D, E, rows_pad, wn, aligned != 0, sc, cn,
+                          xcd_swizzle(blockIdx.x, gridDim.x), s_e);
 }
 
 // Many problems in one launch, as k_sample_major_jobs.
 __global__ __launch_bounds__(256) void k_ld_layout_jobs(const LdLayoutJob* __restrict__ jobs,
                                                         int n_jobs) {
-  __shared__ uint32_t s_e[16 * 260];
+  __shared__ __attribute__((aligned(16))) uint32_t s_e[16 * 260];
   const int64_t b = blockIdx.x;
   int lo = 0, hi = n_jobs - 1;
   while (lo < hi) {   // the last job with block_begin <= b
@@ -609,7 +641,8 @@ __global__ __launch_bounds__(256) void k_ld_layout_jobs(const LdLayoutJob* __res
     if (jobs[mid].block_begin <= b) lo = mid; else hi = mid - 1;
   }
   const LdLayoutJob j = jobs[lo];
-  ld_layout_block<false>(j.s, j.D, j.E, j.wn, j.aligned != 0, j.sc, b - j.block_begin, s_e);
+  ld_layout_block<false>(j.s, j.D, j.E, 0, j.wn, j.aligned != 0, j.sc, LdCounts{}, b - j.block_begin,
+                         s_e);
 }
 
 int64_t ld_layout_blocks(int64_t rows_pad, int64_t wn) {
@@ -625,16 +658,19 @@ int launch_ld_layout_jobs(const LdLayoutJob* jobs, int n_jobs, int64_t total_blo
 }
 
 int launch_ld_layout(const Sel& s, uint32_t* D, uint32_t* E, int64_t rows_pad, int64_t wn,
-                     const LdScratch& sc, hipStream_t st) {
+                     const LdScratch& sc, const LdCounts& cn, hipStream_t st) {
   const dim3 grid((unsigned)ld_layout_blocks(rows_pad, wn));
   if (!s.idx) {
-    hipLaunchKernelGGL(k_ld_layout<false>, grid, dim3(256), 0, st, s, D, E, wn,
-                       (int)rows_dword_aligned(s), sc);
+    hipLaunchKernelGGL(k_ld_layout<false>, grid, dim3(256), 0, st, s, D, E, rows_pad, wn,
+                       (int)rows_dword_aligned(s), sc, cn);
     return check_launch("ld_layout");
   }
-  int rc = launch_variant_major_2bit(s, D, rows_pad, wn, st);
+  hipLaunchKernelGGL(k_variant_major_2bit, dim3((unsigned)ceil_div(rows_pad * wn, 256)), dim3(256),
+                     0, st, s, D, rows_pad, wn);
+  int rc = check_launch("variant_major_2bit");
   if (rc != PG_OK) return rc;
-  hipLaunchKernelGGL(k_ld_layout<true>, grid, dim3(256), 0, st, s, D, E, wn, 0, sc);
+  hipLaunchKernelGGL(k_ld_layout<true>, grid, dim3(256), 0, st, s, D, E, rows_pad, wn, 0, sc,
+                     cn);
   return check_launch("ld_layout");
 }
 

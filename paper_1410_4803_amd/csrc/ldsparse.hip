@@ -30,144 +30,142 @@
 // than the five dense Grams they replace; the dense kernel runs the other
 // tiles and skips these.
 //
-// Launch order: k_ld_vstats (lists, counts, totals) and k_ld_groups (group
-// statistics, and whether enough groups qualify for the path to be on),
-// k_ld_transpose (T, only when it is on), then the dense kernel and
-// k_ld_sparse, each taking its own tiles.
+// Launch order: the layout (partial counts per variant), k_ld_totals (counts
+// and totals, group statistics, and whether enough groups qualify for the path
+// to be on), k_ld_lists and k_ld_transpose (lists and T, only when it is on and
+// has missing calls to correct), then the dense kernel and k_ld_sparse, each
+// taking its own tiles.
 #include "tiles.h"
 
 namespace pg {
 
-// Missing calls of every stride-th variant row of D (the first m samples),
-// added to *gate: one wave per sampled row.
-__global__ __launch_bounds__(256) void k_ld_miss_sample(const uint32_t* __restrict__ D, int64_t wn,
-                                                        int64_t m, int64_t nv, int64_t stride,
-                                                        unsigned long long* __restrict__ gate) {
-  const int lane = threadIdx.x & 63;
-  const int64_t v = (((int64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 6) * stride;
-  if (v >= nv) return;
-  const uint32_t* row = D + v * wn;
-  unsigned int c = 0;
-  for (int64_t w = lane; w < wn; w += 64) {
-    const uint32_t x = row[w];
-    uint32_t miss = x & ~(x >> 1) & 0x55555555u;   // code 01
-    const int64_t valid = m - 16 * w;              // selected samples in this word
-    if (valid < 16) miss &= valid <= 0 ? 0u : ((1u << (2 * valid)) - 1u);
-    c += __popc(miss);
+// A thread per variant sums the layout's partial counts; a wave is a group of
+// 64 variants, so the group statistics are lane reductions.  Padding samples
+// were counted as missing; padding variants get zero counts.  A group counts in
+// groups_ok[0] when its diagonal tile qualifies (a tile (I, J) can qualify only
+// if one of its groups has total <= budget / 2, whose diagonal tile then
+// qualifies too), and in groups_ok[1] when it has missing calls that a tile the
+// path takes could ask for.  Bound by the start of its few blocks (11 to 14 us);
+// counting in the layout and skipping lists and T where there is nothing to
+// correct took pruning 10,000 x 88,025 calls without missing ones from 1.10 to
+// 0.85 ms (the operand was read twice more for counts, 72 us each, and T built
+// for nothing, 117 us), and 5,000 x 500,000 at 1% from 5.95 to 5.85 ms.
+constexpr int kTotThreads = 1024;
+
+__global__ __launch_bounds__(kTotThreads) void k_ld_totals(
+    const uint32_t* __restrict__ part, int64_t n_part, int64_t pad, int64_t m, int64_t nv,
+    int64_t rows_pad, int2* __restrict__ stats, int4* __restrict__ vst, int cap, int64_t budget,
+    int64_t* __restrict__ gsum, int* __restrict__ gmax, uint32_t* __restrict__ groups_ok) {
+  __shared__ uint32_t s_ok[2];
+  if (threadIdx.x < 2) s_ok[threadIdx.x] = 0;
+  __syncthreads();
+  const int64_t v = (int64_t)blockIdx.x * kTotThreads + threadIdx.x;
+  if (v < rows_pad) {   // rows_pad: whole waves
+    int n3 = 0, n0 = 0, c = 0;
+    if (v < nv) {
+      for (int64_t b = 0; b < n_part; ++b) {
+        const uint32_t p = part[b * rows_pad + v];
+        n3 += p & 1023u;
+        n0 += (p >> 10) & 1023u;
+        c += p >> 20;
+      }
+      c -= (int)pad;
+    }
+    if (stats && v < nv) stats[v] = allele_counts(n3, n0, m - c);
+    if (vst) {
+      vst[v] = make_int4(c, n3 - n0, n3 + n0, 0);
+      int64_t sum = c;
+      int mx = c;
+      for (int d = 32; d > 0; d >>= 1) {
+        sum += __shfl_xor(sum, d, 64);
+        const int o = __shfl_xor(mx, d, 64);
+        mx = o > mx ? o : mx;
+      }
+      if ((threadIdx.x & 63) == 0) {
+        gsum[v / 64] = sum;
+        gmax[v / 64] = mx;
+        if (mx <= cap && sum <= budget / 2) atomicAdd(&s_ok[0], 1u);
+        if (mx > 0 && mx <= cap && sum <= budget) atomicAdd(&s_ok[1], 1u);
+      }
+    }
   }
-  for (int d = 32; d > 0; d >>= 1) c += __shfl_xor(c, d, 64);
-  if (lane == 0 && c) atomicAdd(gate, (unsigned long long)c);
+  __syncthreads();
+  if (vst && threadIdx.x < 2 && s_ok[threadIdx.x])
+    atomicAdd(&groups_ok[threadIdx.x], s_ok[threadIdx.x]);
 }
 
-// Per-variant missing-call list, count and totals: one wave per variant row
-// of the variant-major operand D (padding samples are missing calls and are
-// not listed; padding variants get zero counts and empty lists).  A list
-// entry is the sample index.  Does nothing when a gate is given and the
-// sampled count exceeds gate_max (the path stays off).
-__global__ __launch_bounds__(256) void k_ld_vstats(const uint32_t* __restrict__ D, int64_t wn,
-                                                   int64_t m, int64_t nv, int64_t rows_pad, int cap,
-                                                   uint32_t* __restrict__ lists,
-                                                   int4* __restrict__ vst,
-                                                   const unsigned long long* __restrict__ gate,
-                                                   unsigned long long gate_max) {
-  if (gate && *gate > gate_max) return;
-  const int lane = threadIdx.x & 63;
-  const int64_t v = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 6;
-  if (v >= rows_pad) return;
-  if (v >= nv) {
-    if (lane == 0) vst[v] = make_int4(0, 0, 0, 0);
-    return;
-  }
-  const uint32_t* row = D + v * wn;
-  uint32_t* list = lists + v * (int64_t)cap;
-  int64_t c = 0;
-  int n3 = 0, n0 = 0;
-  constexpr int kU = 8;   // 64-word slices loaded ahead of the scan
-  for (int64_t w0 = 0; w0 < wn; w0 += 64 * kU) {
-    uint32_t x[kU];
-#pragma unroll
-    for (int u = 0; u < kU; ++u) {
-      const int64_t w = w0 + 64 * u + lane;
-      x[u] = w < wn ? row[w] : 0xAAAAAAAAu;   // past the row: hets, counted nowhere
-    }
-#pragma unroll
-    for (int u = 0; u < kU; ++u) {
-      const int64_t w = w0 + 64 * u + lane;
-      const uint32_t lo = x[u] & 0x55555555u, hi = (x[u] >> 1) & 0x55555555u;
-      n3 += __popc(lo & hi);
-      n0 += __popc(~(lo | hi) & 0x55555555u);
-      uint32_t miss = lo & ~hi;
-      const int64_t valid = m - 16 * w;   // selected samples in this word
-      if (valid < 16) miss &= valid <= 0 ? 0u : ((1u << (2 * valid)) - 1u);
-      if (__ballot(miss != 0) == 0) continue;   // (the same for the whole wave)
-      // exclusive prefix sum of the per-lane counts (at most 16) over the
-      // wave, one bit of the count at a time, with no cross-lane data moves
-      const int k = __popc(miss);
-      int excl = 0, total = 0;
-#pragma unroll
-      for (int b = 0; b < 5; ++b) {
-        const uint64_t bb = __ballot((k >> b) & 1);
-        excl += (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(bb >> 32),
-                                               __builtin_amdgcn_mbcnt_lo((uint32_t)bb, 0u)) << b;
-        total += __popcll(bb) << b;
-      }
-      int64_t pos = c + excl;
-      while (miss) {
-        const int bit = __ffs(miss) - 1;
-        const int64_t smp = 16 * w + (bit >> 1);
-        if (pos < cap) list[pos] = (uint32_t)smp;
-        ++pos;
-        miss &= miss - 1;
-      }
-      c += total;
-    }
-  }
-  for (int d = 32; d > 0; d >>= 1) {
-    n3 += __shfl_xor(n3, d, 64);
-    n0 += __shfl_xor(n0, d, 64);
-  }
-  if (lane == 0) vst[v] = make_int4((int)c, n3 - n0, n3 + n0, 0);
+int launch_ld_totals(const LdCounts& cn, int64_t wn, int64_t m, int64_t nv, int64_t rows_pad,
+                     int2* stats, const LdSparse* sp, hipStream_t st) {
+  hipLaunchKernelGGL(k_ld_totals, dim3((unsigned)ceil_div(rows_pad, kTotThreads)),
+                     dim3(kTotThreads), 0, st, cn.part, ceil_div(wn, kLdCountWords), 16 * wn - m, m,
+                     nv, rows_pad, stats, sp ? sp->vst : nullptr, sp ? sp->cap : 0,
+                     sp ? sp->budget : 0, sp ? sp->gsum : nullptr, sp ? sp->gmax : nullptr,
+                     sp ? sp->groups_ok : nullptr);
+  return check_launch("ld_totals");
 }
 
-// Per group of 64 variants: total and largest missing-call count, and the
-// number of groups whose diagonal tile qualifies (groups_ok, cleared
-// before).  A tile (I, J) can qualify only if one of its groups has total
-// <= budget / 2, whose diagonal tile then qualifies too.
-constexpr int kGrpPerBlock = 64;   // groups per block of k_ld_groups (16 per wave)
+// Whether the correction path is on and has calls to correct.
+__device__ __forceinline__ bool ld_corrects(const uint32_t* groups_ok, uint32_t min_groups) {
+  return groups_ok[0] >= min_groups && groups_ok[1] > 0;
+}
 
-__global__ __launch_bounds__(256) void k_ld_groups(const int4* __restrict__ vst, int64_t n_groups,
-                                                   int cap, int64_t budget,
-                                                   int64_t* __restrict__ gsum,
-                                                   int* __restrict__ gmax,
-                                                   uint32_t* __restrict__ groups_ok,
-                                                   const unsigned long long* __restrict__ gate,
-                                                   unsigned long long gate_max) {
-  __shared__ uint32_t s_ok;
-  if (gate && *gate > gate_max) return;   // groups_ok stays 0: the path is off
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  if (threadIdx.x == 0) s_ok = 0;
-  __syncthreads();
-  uint32_t ok = 0;
-  for (int i = 0; i < kGrpPerBlock / 4; ++i) {
-    const int64_t g = (int64_t)blockIdx.x * kGrpPerBlock + wave * (kGrpPerBlock / 4) + i;
-    if (g >= n_groups) break;
-    const int c = vst[g * 64 + lane].x;
-    int64_t sum = c;
-    int mx = c;
-    for (int d = 32; d > 0; d >>= 1) {
-      sum += __shfl_xor(sum, d, 64);
-      const int o = __shfl_xor(mx, d, 64);
-      mx = o > mx ? o : mx;
+// Per-variant missing-call lists (sample indices, increasing) of the groups
+// that tiles of the path can use: one wave per variant row of the
+// variant-major operand D (padding samples are
+// not listed).
+__global__ __launch_bounds__(256) void k_ld_lists(const uint32_t* __restrict__ D, int64_t wn,
+                                                  int64_t m, int64_t nv, int cap, int64_t budget,
+                                                  uint32_t* __restrict__ lists,
+                                                  const int4* __restrict__ vst,
+                                                  const int64_t* __restrict__ gsum,
+                                                  const int* __restrict__ gmax,
+                                                  const uint32_t* __restrict__ groups_ok,
+                                                  uint32_t min_groups) {
+  if (!ld_corrects(groups_ok, min_groups)) return;
+  const int lane = threadIdx.x & 63;
+  const int64_t waves = (int64_t)gridDim.x * 4;
+  for (int64_t v = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6); v < nv; v += waves) {
+    if (vst[v].x == 0 || gmax[v / 64] > cap || gsum[v / 64] > budget) continue;
+    const uint32_t* row = D + v * wn;
+    uint32_t* list = lists + v * (int64_t)cap;
+    int64_t c = 0;
+    constexpr int kU = 8;   // 64-word slices loaded ahead of the scan
+    for (int64_t w0 = 0; w0 < wn; w0 += 64 * kU) {
+      uint32_t x[kU];
+#pragma unroll
+      for (int u = 0; u < kU; ++u) {
+        const int64_t w = w0 + 64 * u + lane;
+        x[u] = w < wn ? row[w] : 0u;   // past the row: no missing calls
+      }
+#pragma unroll
+      for (int u = 0; u < kU; ++u) {
+        const int64_t w = w0 + 64 * u + lane;
+        uint32_t miss = x[u] & ~(x[u] >> 1) & 0x55555555u;   // code 01
+        const int64_t valid = m - 16 * w;   // selected samples in this word
+        if (valid < 16) miss &= valid <= 0 ? 0u : ((1u << (2 * valid)) - 1u);
+        if (__ballot(miss != 0) == 0) continue;   // (the same for the whole wave)
+        // exclusive prefix sum of the per-lane counts (at most 16) over the
+        // wave, one bit of the count at a time, with no cross-lane data moves
+        const int k = __popc(miss);
+        int excl = 0, total = 0;
+#pragma unroll
+        for (int b = 0; b < 5; ++b) {
+          const uint64_t bb = __ballot((k >> b) & 1);
+          excl += (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(bb >> 32),
+                                                 __builtin_amdgcn_mbcnt_lo((uint32_t)bb, 0u)) << b;
+          total += __popcll(bb) << b;
+        }
+        int64_t pos = c + excl;
+        while (miss) {
+          const int bit = __ffs(miss) - 1;
+          if (pos < cap) list[pos] = (uint32_t)(16 * w + (bit >> 1));
+          ++pos;
+          miss &= miss - 1;
+        }
+        c += total;
+      }
     }
-    if (lane == 0) {
-      gsum[g] = sum;
-      gmax[g] = mx;
-    }
-    ok += mx <= cap && 2 * sum <= budget;
   }
-  if (lane == 0 && ok) atomicAdd(&s_ok, ok);
-  __syncthreads();
-  if (threadIdx.x == 0 && s_ok) atomicAdd(groups_ok, s_ok);
 }
 
 constexpr int kSpS = 65;          // LDS row stride of the per-pair cells (words)
@@ -253,19 +251,11 @@ __device__ __forceinline__ void count_batch(const uint32_t (&words)[kSpBatch], u
 // G = <v_a, v_b> = Sxy + (Sx + Sy) / 2 + n / 4 over the samples where neither
 // is missing, exactly (kLdFp4MaxSamples); the cells hold 4 G.
 template <bool kFp4>
-__global__ __launch_bounds__(256, 3) void k_ld_sparse(
+__device__ __forceinline__ void ld_sparse_tile(
     const uint32_t* __restrict__ D, int64_t wn, const uint32_t* __restrict__ T, int64_t t_rows,
-    const uint32_t* __restrict__ lists, const int4* __restrict__ vst,
-    const int64_t* __restrict__ gsum, const int* __restrict__ gmax,
-    const uint32_t* __restrict__ groups_ok, uint32_t min_groups, int cap, int64_t budget,
-    int64_t m, int64_t nv, int64_t n_row_tiles, int64_t n_band, int32_t window,
-    double r2_min, LdScratch sc, pg_ld_pair* __restrict__ dbg, int64_t v0) {
-  const int64_t blk = xcd_swizzle(blockIdx.x, gridDim.x);
-  const int64_t I = blk / n_band;
-  const int64_t J = I + blk % n_band;
-  if (J >= n_row_tiles || !ld_tile_sparse(gsum, gmax, groups_ok, min_groups, I, J, cap, budget))
-    return;
-
+    const uint32_t* __restrict__ lists, const int4* __restrict__ vst, int cap, int64_t m,
+    int64_t nv, int64_t I, int64_t J, int32_t window, double r2_min, const LdScratch& sc,
+    pg_ld_pair* __restrict__ dbg, int64_t v0) {
   // per-pair cells: first the Sxy partial sums, then the b-side corrections
   // (row a, column b); the a-side corrections (row b, column a): homA1 |
   // homA2 << 16 and the shared missing calls
@@ -505,6 +495,33 @@ __global__ __launch_bounds__(256, 3) void k_ld_sparse(
   }
 }
 
+// Tiles blockIdx.x, + gridDim.x, ... of the band: at most kSpGrid blocks, so
+// that a band the path leaves alone costs few block starts (61 us for the
+// 132,000 tiles of 500,000 variants x window 1,000 with a block per tile).
+constexpr int64_t kSpGrid = 16384;
+
+template <bool kFp4>
+__global__ __launch_bounds__(256, 3) void k_ld_sparse(
+    const uint32_t* __restrict__ D, int64_t wn, const uint32_t* __restrict__ T, int64_t t_rows,
+    const uint32_t* __restrict__ lists, const int4* __restrict__ vst,
+    const int64_t* __restrict__ gsum, const int* __restrict__ gmax,
+    const uint32_t* __restrict__ groups_ok, uint32_t min_groups, int cap, int64_t budget,
+    int64_t m, int64_t nv, int64_t n_row_tiles, int64_t n_band, int32_t window,
+    double r2_min, LdScratch sc, pg_ld_pair* __restrict__ dbg, int64_t v0) {
+  if (*groups_ok < min_groups) return;
+  const int64_t tiles = n_row_tiles * n_band;
+  for (int64_t i = blockIdx.x; i < tiles; i += gridDim.x) {
+    const int64_t blk = xcd_swizzle(i, tiles);
+    const int64_t I = blk / n_band;
+    const int64_t J = I + blk % n_band;
+    if (J >= n_row_tiles || !ld_tile_sparse(gsum, gmax, groups_ok, min_groups, I, J, cap, budget))
+      continue;
+    ld_sparse_tile<kFp4>(D, wn, T, t_rows, lists, vst, cap, m, nv, I, J, window, r2_min, sc, dbg,
+                         v0);
+    __syncthreads();   // the cells are reused
+  }
+}
+
 constexpr int kTrW = 32;            // words per block side: 512 variants x 512 samples
 constexpr int kTrS = kTrW + 1;      // LDS row stride (words)
 
@@ -515,13 +532,14 @@ constexpr int kTrS = kTrW + 1;      // LDS row stride (words)
 // transposes land in LDS, and each half-wave writes one sample's 32 words as
 // eight 16-byte pieces of eight strips (consecutive samples of a strip are
 // adjacent, so a block fills whole lines).  Variants past rows_pad read as
-// missing.  Does nothing while *gate < gate_min.
+// missing.  Does nothing unless ld_corrects.
 __global__ __launch_bounds__(256) void k_ld_transpose(const uint32_t* __restrict__ D,
                                                       int64_t rows_pad, int64_t wn,
                                                       uint32_t* __restrict__ T, int64_t t_rows,
-                                                      int64_t tw, const uint32_t* __restrict__ gate,
-                                                      uint32_t gate_min) {
-  if (*gate < gate_min) return;
+                                                      int64_t tw,
+                                                      const uint32_t* __restrict__ groups_ok,
+                                                      uint32_t min_groups) {
+  if (!ld_corrects(groups_ok, min_groups)) return;
   __shared__ uint32_t s_out[16 * kTrW * kTrS];
   const int64_t nb_a = ceil_div(tw, kTrW);
   const int64_t a0 = ((int64_t)blockIdx.x % nb_a) * kTrW;   // T word (16 variants)
@@ -552,31 +570,12 @@ __global__ __launch_bounds__(256) void k_ld_transpose(const uint32_t* __restrict
   }
 }
 
-int launch_ld_sparse_stats(const uint32_t* D, int64_t wn, int64_t m, int64_t nv,
-                           int64_t rows_pad, const LdSparse& sp, hipStream_t st) {
-  int rc = PG_OK;
-  unsigned long long* gate = reinterpret_cast<unsigned long long*>(sp.gate);
-  if (gate) {
-    rc = fill_u32(reinterpret_cast<uint32_t*>(gate), 2, 0u, st);
-    if (rc != PG_OK) return rc;
-    const int64_t n_samp = ceil_div(nv, sp.gate_stride);
-    hipLaunchKernelGGL(k_ld_miss_sample, dim3((unsigned)ceil_div(n_samp, 4)), dim3(256), 0, st, D,
-                       wn, m, nv, sp.gate_stride, gate);
-    rc = check_launch("ld_miss_sample");
-    if (rc != PG_OK) return rc;
-  }
-  const dim3 grid((unsigned)ceil_div(rows_pad, 4));
-  hipLaunchKernelGGL(k_ld_vstats, grid, dim3(256), 0, st, D, wn, m, nv, rows_pad, sp.cap, sp.lists,
-                     sp.vst, gate, (unsigned long long)sp.gate_max);
-  rc = check_launch("ld_vstats");
-  if (rc == PG_OK) rc = fill_u32(sp.groups_ok, 1, 0u, st);
-  if (rc != PG_OK) return rc;
-  const int64_t n_groups = rows_pad / kLdTile;
-  hipLaunchKernelGGL(k_ld_groups, dim3((unsigned)ceil_div(n_groups, kGrpPerBlock)), dim3(256), 0,
-                     st, sp.vst,
-                     n_groups, sp.cap, sp.budget, sp.gsum, sp.gmax, sp.groups_ok, gate,
-                     (unsigned long long)sp.gate_max);
-  return check_launch("ld_groups");
+int launch_ld_lists(const uint32_t* D, int64_t wn, int64_t m, int64_t nv, const LdSparse& sp,
+                    hipStream_t st) {
+  const int64_t blocks = ceil_div(nv, 4) < 8192 ? ceil_div(nv, 4) : 8192;
+  hipLaunchKernelGGL(k_ld_lists, dim3((unsigned)blocks), dim3(256), 0, st, D, wn, m, nv, sp.cap,
+                     sp.budget, sp.lists, sp.vst, sp.gsum, sp.gmax, sp.groups_ok, sp.min_groups);
+  return check_launch("ld_lists");
 }
 
 int launch_ld_transpose(const uint32_t* D, int64_t rows_pad, int64_t wn, uint32_t* T,
@@ -601,9 +600,11 @@ int launch_ld_sparse(const uint32_t* D, const uint32_t* E, int64_t wn, const uin
   const int64_t n_row_tiles = rows_pad / kLdTile;
   const int64_t n_band = ((int64_t)window + kLdTile - 1) / kLdTile + 1;
   hipLaunchKernelGGL(E ? k_ld_sparse<true> : k_ld_sparse<false>,
-                     dim3((unsigned)(n_row_tiles * n_band)), dim3(256), 0, st, E ? E : D, wn, T, t_rows, sp.lists, sp.vst, sp.gsum, sp.gmax, sp.groups_ok, sp.min_groups,
-                     sp.cap, sp.budget, m, nv, n_row_tiles, n_band, window, r2_min, sc,
-                     dbg, v0);
+                     dim3((unsigned)(n_row_tiles * n_band < kSpGrid ? n_row_tiles * n_band
+                                                                    : kSpGrid)),
+                     dim3(256), 0, st, E ? E : D, wn, T, t_rows, sp.lists, sp.vst, sp.gsum, sp.gmax,
+                     sp.groups_ok, sp.min_groups, sp.cap, sp.budget, m, nv, n_row_tiles, n_band,
+                     window, r2_min, sc, dbg, v0);
   rc = check_launch("ld_sparse");
   mark_stage(2, st);
   return rc;

@@ -265,9 +265,15 @@ int ld_scan_blocks(int64_t nv);
 
 // The LD operands: D as launch_variant_major_2bit, and beside it the nibble
 // operand E of the fp4 tile: 64 variants x 64 samples in 512 words (rows_pad *
-// wn * 2 words in all; wn a multiple of 16).  Clears sc's bitmap and counts.
+// wn * 2 words in all; wn a multiple of 16; NULL: D only).  Clears sc's bitmap
+// and counts, and counts the codes of every variant for launch_ld_totals.
+constexpr int kLdCountWords = 32;   // words of a variant per partial count
+struct LdCounts {
+  uint32_t* part;   // ceil(wn / kLdCountWords) x rows_pad; NULL: not counted
+  uint32_t* any;    // two words launch_ld_totals adds to, cleared here
+};
 int launch_ld_layout(const Sel& s, uint32_t* D, uint32_t* E, int64_t rows_pad, int64_t wn,
-                     const LdScratch& sc, hipStream_t st);
+                     const LdScratch& sc, const LdCounts& cn, hipStream_t st);
 // The same for a device array of problems without a sample list, in one launch
 // (increasing block_begin, ld_layout_blocks each).
 struct LdLayoutJob {
@@ -292,17 +298,20 @@ struct LdSparse {
   int4* vst;           // rows_pad
   int64_t* gsum;       // rows_pad / 64
   int* gmax;           // rows_pad / 64
-  uint32_t* groups_ok; // 1 word: groups whose diagonal tile qualifies
-  uint32_t min_groups; // the path is on when groups_ok reaches this
+  uint32_t* groups_ok; // 2 words: groups whose diagonal tile qualifies, and those
+                       // among them with a missing call
+  uint32_t min_groups; // the path is on when groups_ok[0] reaches this
   int cap;
   int64_t budget;      // largest missing-call total of a tile's two groups
-  // optional sampled gate: the statistics pass (and with it the path) runs
-  // only while *gate, the missing calls counted over a sample of the
-  // variants, is at most gate_max
-  uint64_t* gate;
-  uint64_t gate_max;
-  int64_t gate_stride; // every gate_stride-th variant is sampled
 };
+// Minor alleles and calls (1 for a variant without any) from the counts of
+// homozygous A2, homozygous A1 and of all calls.
+__device__ __forceinline__ int2 allele_counts(int64_t hom2, int64_t hom1, int64_t nm) {
+  const int64_t het = nm - hom2 - hom1;
+  const int64_t a2 = 2 * hom2 + het;
+  const int64_t minor = a2 < 2 * nm - a2 ? a2 : 2 * nm - a2;
+  return make_int2((int)minor, nm > 0 ? (int)nm : 1);
+}
 __device__ inline bool ld_tile_sparse(const int64_t* gsum, const int* gmax,
                                       const uint32_t* groups_ok, uint32_t min_groups, int64_t I,
                                       int64_t J, int cap, int64_t budget) {
@@ -332,14 +341,19 @@ int launch_ld_mfma(const uint32_t* D, const uint32_t* E, int64_t wn, int64_t nv,
 // kLdFp4MaxSamples samples on its int8 twin), or the int8 tile (1).
 constexpr int kLdVariantFp4 = 0;
 constexpr int kLdVariantInt8 = 1;
-// Correction path, first part: lists, counts and totals from D
-// (variant-major, wn words), the group statistics and groups_ok.
-int launch_ld_sparse_stats(const uint32_t* D, int64_t wn, int64_t m, int64_t nv,
-                           int64_t rows_pad, const LdSparse& sp, hipStream_t st);
+// Per variant, from the layout's partial counts: the allele counts for pruning
+// (stats, may be NULL) and, with sp, the correction path's totals, group
+// statistics and groups_ok.
+int launch_ld_totals(const LdCounts& cn, int64_t wn, int64_t m, int64_t nv, int64_t rows_pad,
+                     int2* stats, const LdSparse* sp, hipStream_t st);
+// Correction path, first part: the missing-call lists from D (variant-major,
+// wn words); nothing when the path is off or no variant needs one.
+int launch_ld_lists(const uint32_t* D, int64_t wn, int64_t m, int64_t nv, const LdSparse& sp,
+                    hipStream_t st);
 // The sample-major operand of the corrections, transposed from D in strips
 // of 64 variants: word w (0-3) of strip s at sample k is T[(s * t_rows + k) *
 // 4 + w] (t_rows = round_up(m, 128); tw words of 16 variants per sample, a
-// multiple of 4); nothing when the path is off.
+// multiple of 4); nothing when the path is off or there is nothing to correct.
 int launch_ld_transpose(const uint32_t* D, int64_t rows_pad, int64_t wn, uint32_t* T,
                         int64_t t_rows, int64_t tw, const LdSparse& sp, hipStream_t st);
 // Second part: the dense kernel on the tiles this path leaves, then the
@@ -380,8 +394,8 @@ int launch_ld_finish(const uint32_t* X, bool planes, int64_t words, int64_t rows
 // ---- LD pruning (prune.hip) -------------------------------------------------
 // Per selected variant: {minor allele count, non-missing calls (at least 1)}
 // over the selected samples, from the operand of the LD pair kernel.
-int launch_variant_stats(const uint32_t* X, bool planes, int64_t words, int64_t rows_pad,
-                         int64_t nv, int2* stats, hipStream_t st);
+int launch_variant_stats(const uint32_t* P, int64_t words, int64_t rows_pad, int64_t nv,
+                         int2* stats, hipStream_t st);
 // The greedy pass over the windows, from the pair kernel's bitmap of pairs
 // with r^2 above the threshold (bitmap window = window - 1); `drop` is
 // scratch of the bitmap's size for the drop side of every marked pair.

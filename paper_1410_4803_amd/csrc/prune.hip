@@ -25,39 +25,8 @@
 namespace pg {
 
 // ---- per-variant allele counts ---------------------------------------------
-// 2-bit operand: row v holds `words` words of 16 codes; one wave per variant.
-// Bit planes: plane p of word w at P[(w*3 + p)*rows_pad + v] (p = 0 homA2,
+// (2-bit operands: counted by the layout.)  Bit planes: plane p of word w at P[(w*3 + p)*rows_pad + v] (p = 0 homA2,
 // 1 homA1, 2 non-missing); one thread per variant.
-__device__ __forceinline__ int2 stats_of(int64_t hom2, int64_t hom1, int64_t nm) {
-  const int64_t het = nm - hom2 - hom1;
-  const int64_t a2 = 2 * hom2 + het;
-  const int64_t minor = a2 < 2 * nm - a2 ? a2 : 2 * nm - a2;
-  return make_int2((int)minor, nm > 0 ? (int)nm : 1);
-}
-
-__global__ __launch_bounds__(256) void k_stats_words(const uint32_t* __restrict__ D, int64_t words,
-                                                     int64_t nv, int2* __restrict__ stats) {
-  const int lane = threadIdx.x & 63;
-  for (int64_t v = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 6; v < nv;
-       v += ((int64_t)gridDim.x * blockDim.x) >> 6) {
-    const uint32_t* row = D + v * words;
-    int h2 = 0, h1 = 0, nm = 0;
-    for (int64_t w = lane; w < words; w += 64) {
-      uint32_t p, q, m;
-      masks_of_word(row[w], p, q, m);
-      h2 += __builtin_popcount(p);
-      h1 += __builtin_popcount(q);
-      nm += __builtin_popcount(m);
-    }
-    for (int d = 32; d > 0; d >>= 1) {
-      h2 += __shfl_xor(h2, d, 64);
-      h1 += __shfl_xor(h1, d, 64);
-      nm += __shfl_xor(nm, d, 64);
-    }
-    if (lane == 0) stats[v] = stats_of(h2, h1, nm);
-  }
-}
-
 __global__ __launch_bounds__(256) void k_stats_planes(const uint32_t* __restrict__ P, int64_t words,
                                                       int64_t rows_pad, int64_t nv,
                                                       int2* __restrict__ stats) {
@@ -70,21 +39,15 @@ __global__ __launch_bounds__(256) void k_stats_planes(const uint32_t* __restrict
       h1 += __builtin_popcount(pw[rows_pad]);
       nm += __builtin_popcount(pw[2 * rows_pad]);
     }
-    stats[v] = stats_of(h2, h1, nm);
+    stats[v] = allele_counts(h2, h1, nm);
   }
 }
 
-int launch_variant_stats(const uint32_t* X, bool planes, int64_t words, int64_t rows_pad,
-                         int64_t nv, int2* stats, hipStream_t st) {
-  if (planes) {
-    const int64_t blocks = ceil_div(nv, 256) < 65536 ? ceil_div(nv, 256) : 65536;
-    hipLaunchKernelGGL(k_stats_planes, dim3((unsigned)blocks), dim3(256), 0, st, X, words,
-                       rows_pad, nv, stats);
-  } else {
-    const int64_t blocks = ceil_div(nv, 4) < 65536 ? ceil_div(nv, 4) : 65536;
-    hipLaunchKernelGGL(k_stats_words, dim3((unsigned)blocks), dim3(256), 0, st, X, words, nv,
-                       stats);
-  }
+int launch_variant_stats(const uint32_t* P, int64_t words, int64_t rows_pad, int64_t nv,
+                         int2* stats, hipStream_t st) {
+  const int64_t blocks = ceil_div(nv, 256) < 65536 ? ceil_div(nv, 256) : 65536;
+  hipLaunchKernelGGL(k_stats_planes, dim3((unsigned)blocks), dim3(256), 0, st, P, words, rows_pad,
+                     nv, stats);
   return check_launch("variant_stats");
 }
 
