@@ -561,7 +561,7 @@ __device__ __forceinline__ void ld_layout_block(const Sel& s, uint32_t* __restri
   const int64_t bits = kLyRows * sc.bm_words;
   for (int64_t i = blk % nb_w * 256 + t; i < bits; i += nb_w * 256) sc.bitmap[G * bits + i] = 0u;
   if (w0 == 0 && t < kLyRows) sc.rowcnt[G * kLyRows + t] = 0u;
-  if (cn.any && blk == 0 && t < 2) cn.any[t] = 0u;
+  if (cn.any && blk == 0 && t < 3) cn.any[t] = 0u;
   int64_t vr[8], gr[8];
   uint32_t x[8];
 #pragma unroll

@@ -72,13 +72,15 @@ __global__ __launch_bounds__(256, 2) void k_ld_mfma(const uint32_t* __restrict__
                                                     const int* __restrict__ gmax,
                                                     const uint32_t* __restrict__ groups_ok,
                                                     uint32_t min_groups, int cap, int64_t budget) {
+  __shared__ __attribute__((aligned(16))) uint32_t smem[kLdMfmaSmem];
+  // all of them the correction path's: decided by one word
+  if (gsum && groups_ok[0] >= min_groups && groups_ok[2] == 0) return;
   const int64_t b = xcd_swizzle(blockIdx.x, gridDim.x);
   const int64_t I = b / n_band;
   const int64_t J = I + b % n_band;
   if (J >= n_row_tiles) return;
   if (gsum && ld_tile_sparse(gsum, gmax, groups_ok, min_groups, I, J, cap, budget))
     return;   // the correction path's
-  __shared__ __attribute__((aligned(16))) uint32_t smem[kLdMfmaSmem];
   if constexpr (kFp4)   // the operand is E
     ld_nib_tile(D, wn / 4, nv, I, J, window, r2_min, sc, (lds_t*)smem);
   else

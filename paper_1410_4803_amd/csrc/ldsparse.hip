@@ -34,7 +34,7 @@
 // and totals, group statistics, and whether enough groups qualify for the path
 // to be on), k_ld_lists and k_ld_transpose (lists and T, only when it is on and
 // has missing calls to correct), then the dense kernel and k_ld_sparse, each
-// taking its own tiles.
+// taking its own tiles (k_ld_complete those without any missing call).
 #include "tiles.h"
 
 namespace pg {
@@ -45,7 +45,7 @@ namespace pg {
 // groups_ok[0] when its diagonal tile qualifies (a tile (I, J) can qualify only
 // if one of its groups has total <= budget / 2, whose diagonal tile then
 // qualifies too), and in groups_ok[1] when it has missing calls that a tile the
-// path takes could ask for.  Bound by the start of its few blocks (11 to 14 us);
+// path takes could ask for, in groups_ok[2] when it has any.  Bound by the start of its few blocks (11 to 14 us);
 // counting in the layout and skipping lists and T where there is nothing to
 // correct took pruning 10,000 x 88,025 calls without missing ones from 1.10 to
 // 0.85 ms (the operand was read twice more for counts, 72 us each, and T built
@@ -56,8 +56,8 @@ __global__ __launch_bounds__(kTotThreads) void k_ld_totals(
     const uint32_t* __restrict__ part, int64_t n_part, int64_t pad, int64_t m, int64_t nv,
     int64_t rows_pad, int2* __restrict__ stats, int4* __restrict__ vst, int cap, int64_t budget,
     int64_t* __restrict__ gsum, int* __restrict__ gmax, uint32_t* __restrict__ groups_ok) {
-  __shared__ uint32_t s_ok[2];
-  if (threadIdx.x < 2) s_ok[threadIdx.x] = 0;
+  __shared__ uint32_t s_ok[3];
+  if (threadIdx.x < 3) s_ok[threadIdx.x] = 0;
   __syncthreads();
   const int64_t v = (int64_t)blockIdx.x * kTotThreads + threadIdx.x;
   if (v < rows_pad) {   // rows_pad: whole waves
@@ -86,11 +86,12 @@ __global__ __launch_bounds__(kTotThreads) void k_ld_totals(
         gmax[v / 64] = mx;
         if (mx <= cap && sum <= budget / 2) atomicAdd(&s_ok[0], 1u);
         if (mx > 0 && mx <= cap && sum <= budget) atomicAdd(&s_ok[1], 1u);
+        if (mx > 0) atomicAdd(&s_ok[2], 1u);
       }
     }
   }
   __syncthreads();
-  if (vst && threadIdx.x < 2 && s_ok[threadIdx.x])
+  if (vst && threadIdx.x < 3 && s_ok[threadIdx.x])
     atomicAdd(&groups_ok[threadIdx.x], s_ok[threadIdx.x]);
 }
 
@@ -495,6 +496,145 @@ __device__ __forceinline__ void ld_sparse_tile(
   }
 }
 
+// ---- tiles without missing calls ---------------------------------------------
+// 128 x 128 variants whose four groups have no missing call: n, Sx, Sy, Sxx and
+// Syy are the variants' totals, and Sxy follows from the Gram of the whole
+// nibbles, 4 G = 4 Sxy + 2 (Sx + Sy) + m.  Four waves of 64 x 64; chunks of two
+// 64-sample steps (16 KB) reach LDS by direct loads two chunks ahead, three
+// buffers, three blocks a CU.  The 64 x 64 tiles of the correction kernel read
+// 4 KB from L2 per 16 matrix instructions, a tile here 8 KB per 64.
+// Bound: the latency of the operand loads (a chunk nearly always holds a line
+// that comes from HBM): 10,000 x 88,025, distance 699: 413 us at 37% matrix-core
+// occupancy, against 589 us for the 64 x 64 tiles.  Chunks of one step in six
+// buffers 442 us, two blocks a CU with 64 KB 458 to 500, four with 32 to 40 KB
+// 450 to 480.
+constexpr int kCtChunk = 2;                        // steps of 64 samples
+constexpr int kCtGroup = kCtChunk * 512;           // words of a group's chunk
+constexpr int kCtBuf = 4 * kCtGroup;               // two groups a side
+constexpr int64_t kCtGrid = 8192;
+
+// Whether the 128 x 128 tile (I2, J2) is one of these (n_groups of 64).
+__device__ __forceinline__ bool ld_tile_complete(const int* gmax, int64_t I2, int64_t J2,
+                                                 int64_t n_groups) {
+  const int64_t a = 2 * I2 + 1 < n_groups ? 2 * I2 + 1 : 2 * I2;
+  const int64_t b = 2 * J2 + 1 < n_groups ? 2 * J2 + 1 : 2 * J2;
+  return (gmax[2 * I2] | gmax[a] | gmax[2 * J2] | gmax[b]) == 0;
+}
+
+__device__ __forceinline__ void ld_complete_tile(const uint32_t* __restrict__ E, int64_t nsteps,
+                                                 const int4* __restrict__ vst, int64_t m,
+                                                 int64_t nv, int64_t n_groups, int64_t I2,
+                                                 int64_t J2, int32_t window, double r2_min,
+                                                 const LdScratch& sc, lds_t* smem) {
+  const int t = threadIdx.x, lane = t & 63;
+  const int wid = __builtin_amdgcn_readfirstlane(t >> 6);
+  const int wr = wid >> 1, wc = wid & 1;           // this wave's 64 x 64 quadrant
+  const int64_t ga = 2 * I2 + wr, gb = 2 * J2 + wc;   // its groups
+  const bool active = ga < n_groups && gb < n_groups && gb >= ga &&
+                      64 * (gb - ga) - 63 <= (int64_t)window;
+  // wave w stages group w of {2 I2, 2 I2 + 1, 2 J2, 2 J2 + 1} (the last one
+  // again where the tile reaches past it)
+  const int64_t gs = wid < 2 ? 2 * I2 + wid : 2 * J2 + (wid - 2);
+  const uint32_t* src = E + (gs < n_groups ? gs : n_groups - 1) * nsteps * 512 + 4 * lane;
+  const int64_t nch = nsteps / kCtChunk;
+  auto fetch = [&](int64_t c, int buf) {
+    const uint32_t* p = src + (c < nch ? c : nch - 1) * kCtGroup;
+    lds_t* const d = smem + buf * kCtBuf + wid * kCtGroup;
+#pragma unroll
+    for (int h = 0; h < kCtGroup / 256; ++h) lds_from_global(p + 256 * h, d + 256 * h);
+  };
+  v16f acc[2][2] = {{(v16f){0}, (v16f){0}}, {(v16f){0}, (v16f){0}}};
+  fetch(0, 0);
+  fetch(1, 1);
+  asm volatile("s_waitcnt vmcnt(4)\n\ts_barrier" ::: "memory");
+  int b0 = 0, b1 = 1, b2 = 2;
+  for (int64_t k = 0; k < nch; ++k) {
+    fetch(k + 2, b2);   // chunk k - 1's buffer: every wave is past it
+    if (active) {
+      const lds_t* ra = smem + b0 * kCtBuf + wr * kCtGroup + (lane >> 5) * 256 + (lane & 31) * 4;
+      const lds_t* rb = smem + b0 * kCtBuf + (2 + wc) * kCtGroup + (lane >> 5) * 256 +
+                        (lane & 31) * 4;
+#pragma unroll
+      for (int s = 0; s < kCtChunk; ++s) {
+        v8i a[2], b[2];
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+          a[h] = nib_mask(lds_ld4(ra + s * 512 + 128 * h), ~0u);
+          b[h] = nib_mask(lds_ld4(rb + s * 512 + 128 * h), ~0u);
+        }
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
+#pragma unroll
+          for (int j = 0; j < 2; ++j) acc[i][j] = mfma_fp4(a[i], b[j], acc[i][j]);
+      }
+    }
+    // chunk k + 1 has arrived, chunk k is used up
+    asm volatile("s_waitcnt vmcnt(4) lgkmcnt(0)\n\ts_barrier" ::: "memory");
+    const int b = b0;
+    b0 = b1;
+    b1 = b2;
+    b2 = b;
+  }
+  asm volatile("s_waitcnt vmcnt(0)\n\ts_barrier" ::: "memory");
+  // per row of the tile: Sx and r2_min Var_a (1 - 2^-16), as ld_r2_reaches
+  // forms it (m times the variances; the order of its nine roundings differs)
+  const bool narrow = m < (1 << 15) && r2_min > 0.0;
+  auto var_of = [&](const int4& s) {
+    return narrow ? (float)(__mul24((int)m, s.z) - __mul24(s.y, s.y)) : 0.0f;
+  };
+  if (t < 128) {
+    const int64_t a = 128 * I2 + t;
+    const int4 s = a < nv ? vst[a] : make_int4(0, 0, 0, 0);
+    smem[2 * t] = (uint32_t)s.y;
+    smem[2 * t + 1] =
+        __builtin_bit_cast(uint32_t, (float)r2_min * (1.0f - 0x1p-16f) * var_of(s));
+  }
+  asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+  if (!active) return;   // nothing after this point synchronises
+#pragma unroll
+  for (int j = 0; j < 2; ++j) {
+    const int64_t b = 64 * gb + 32 * j + (lane & 31);
+    const int4 sb = b < nv ? vst[b] : make_int4(0, 0, 0, 0);
+    const float vb = var_of(sb);
+    const unsigned lim = b < nv ? (unsigned)window : 0u;
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      const int r0 = 64 * wr + 32 * i + 4 * (lane >> 5);   // row of register 0 in the tile
+      const int d0 = (int)(b - 128 * I2) - r0;             // b - a of register 0
+#pragma unroll
+      for (int v = 0; v < 16; ++v) {
+        const int ar = 8 * (v >> 2) + (v & 3);
+        if ((unsigned)(d0 - ar - 1) >= lim) continue;
+        const int sx = (int)smem[2 * (r0 + ar)];
+        const int sxy = ((int)(4.0f * acc[i][j][v]) - 2 * (sx + sb.y) - (int)m) >> 2;
+        if (narrow) {
+          const float c = (float)(__mul24((int)m, sxy) - __mul24(sx, sb.y));
+          if (c * c < __builtin_bit_cast(float, (uint32_t)smem[2 * (r0 + ar) + 1]) * vb) continue;
+        }
+        const int64_t a = 128 * I2 + r0 + ar;
+        ld_mark(sc, a, b, r2_min, m, sx, sb.y, vst[a].z, sb.z, sxy);
+      }
+    }
+  }
+}
+
+__global__ __launch_bounds__(256, 3) void k_ld_complete(
+    const uint32_t* __restrict__ E, int64_t wn, const int4* __restrict__ vst,
+    const int* __restrict__ gmax, const uint32_t* __restrict__ groups_ok, uint32_t min_groups,
+    int64_t m, int64_t nv, int64_t n_groups, int64_t n_band, int32_t window, double r2_min,
+    LdScratch sc) {
+  __shared__ __attribute__((aligned(16))) uint32_t smem[3 * kCtBuf];
+  if (*groups_ok < min_groups) return;
+  const int64_t n_row = ceil_div(n_groups, 2), tiles = n_row * n_band;
+  for (int64_t i = blockIdx.x; i < tiles; i += gridDim.x) {
+    const int64_t blk = xcd_swizzle(i, tiles);
+    const int64_t I2 = blk / n_band, J2 = I2 + blk % n_band;
+    if (J2 >= n_row || !ld_tile_complete(gmax, I2, J2, n_groups)) continue;
+    ld_complete_tile(E, wn / 4, vst, m, nv, n_groups, I2, J2, window, r2_min, sc, (lds_t*)smem);
+    __syncthreads();   // the buffers are reused
+  }
+}
+
 // Tiles blockIdx.x, + gridDim.x, ... of the band: at most kSpGrid blocks, so
 // that a band the path leaves alone costs few block starts (61 us for the
 // 132,000 tiles of 500,000 variants x window 1,000 with a block per tile).
@@ -509,6 +649,7 @@ __global__ __launch_bounds__(256, 3) void k_ld_sparse(
     int64_t m, int64_t nv, int64_t n_row_tiles, int64_t n_band, int32_t window,
     double r2_min, LdScratch sc, pg_ld_pair* __restrict__ dbg, int64_t v0) {
   if (*groups_ok < min_groups) return;
+  if (kFp4 && !dbg && groups_ok[2] == 0) return;   // every tile is k_ld_complete's
   const int64_t tiles = n_row_tiles * n_band;
   for (int64_t i = blockIdx.x; i < tiles; i += gridDim.x) {
     const int64_t blk = xcd_swizzle(i, tiles);
@@ -516,6 +657,7 @@ __global__ __launch_bounds__(256, 3) void k_ld_sparse(
     const int64_t J = I + blk % n_band;
     if (J >= n_row_tiles || !ld_tile_sparse(gsum, gmax, groups_ok, min_groups, I, J, cap, budget))
       continue;
+    if (kFp4 && !dbg && ld_tile_complete(gmax, I >> 1, J >> 1, n_row_tiles)) continue;
     ld_sparse_tile<kFp4>(D, wn, T, t_rows, lists, vst, cap, m, nv, I, J, window, r2_min, sc, dbg,
                          v0);
     __syncthreads();   // the cells are reused
@@ -599,6 +741,15 @@ int launch_ld_sparse(const uint32_t* D, const uint32_t* E, int64_t wn, const uin
   }
   const int64_t n_row_tiles = rows_pad / kLdTile;
   const int64_t n_band = ((int64_t)window + kLdTile - 1) / kLdTile + 1;
+  if (E && !dbg) {
+    const int64_t n_row2 = ceil_div(n_row_tiles, 2), n_band2 = ((int64_t)window + 127) / 128 + 1;
+    hipLaunchKernelGGL(k_ld_complete,
+                       dim3((unsigned)(n_row2 * n_band2 < kCtGrid ? n_row2 * n_band2 : kCtGrid)),
+                       dim3(256), 0, st, E, wn, sp.vst, sp.gmax, sp.groups_ok, sp.min_groups, m, nv,
+                       n_row_tiles, n_band2, window, r2_min, sc);
+    rc = check_launch("ld_complete");
+    if (rc != PG_OK) return rc;
+  }
   hipLaunchKernelGGL(E ? k_ld_sparse<true> : k_ld_sparse<false>,
                      dim3((unsigned)(n_row_tiles * n_band < kSpGrid ? n_row_tiles * n_band
                                                                     : kSpGrid)),

@@ -270,7 +270,7 @@ int ld_scan_blocks(int64_t nv);
 constexpr int kLdCountWords = 32;   // words of a variant per partial count
 struct LdCounts {
   uint32_t* part;   // ceil(wn / kLdCountWords) x rows_pad; NULL: not counted
-  uint32_t* any;    // two words launch_ld_totals adds to, cleared here
+  uint32_t* any;    // three words launch_ld_totals adds to, cleared here
 };
 int launch_ld_layout(const Sel& s, uint32_t* D, uint32_t* E, int64_t rows_pad, int64_t wn,
                      const LdScratch& sc, const LdCounts& cn, hipStream_t st);
@@ -298,8 +298,8 @@ struct LdSparse {
   int4* vst;           // rows_pad
   int64_t* gsum;       // rows_pad / 64
   int* gmax;           // rows_pad / 64
-  uint32_t* groups_ok; // 2 words: groups whose diagonal tile qualifies, and those
-                       // among them with a missing call
+  uint32_t* groups_ok; // 3 words: groups whose diagonal tile qualifies, groups with
+                       // missing calls that some tile corrects, groups with any
   uint32_t min_groups; // the path is on when groups_ok[0] reaches this
   int cap;
   int64_t budget;      // largest missing-call total of a tile's two groups
