@@ -753,15 +753,13 @@ namespace {
 // per-marker term columns, the per-marker flags, the six sums and the runs'
 // partial sums.
 struct GenomePlan {
-  int64_t rows_pad, wn, off_D, off_terms, off_used, off_sums, bytes;
+  int64_t wn, off_D, off_counts, off_sums, bytes;
 };
 void plan_genome(const Sel& s, GenomePlan& p) {
-  p.rows_pad = round_up(s.nv, 64);
   p.wn = ceil_div(s.m, 16);
   Carve c;
-  p.off_D = c.take(p.rows_pad * p.wn * 4);
-  p.off_terms = c.take(5 * p.rows_pad * 8);
-  p.off_used = c.take(p.rows_pad * 4);
+  p.off_D = c.take(s.nv * p.wn * 4);   // with a sample list
+  p.off_counts = c.take(s.nv * (int64_t)sizeof(uint2));
   p.off_sums = c.take(8 * genome_sums_doubles(s.nv));
   p.bytes = c.off;
 }
@@ -800,11 +798,11 @@ int pg_ibs_genome(const pg_genotypes* g, const int32_t* sample_idx, int64_t n_se
   hipStream_t st = (hipStream_t)stream;
   mark_stage(0, st);
   uint32_t* D = (uint32_t*)(ws + p.off_D);
-  rc = launch_variant_major_2bit(s, D, p.rows_pad, p.wn, st);
+  uint2* counts = (uint2*)(ws + p.off_counts);
+  rc = launch_allele_counts(s, D, p.wn, counts, st);
   if (rc != PG_OK) return rc;
-  rc = launch_genome(D, p.wn, s.nv, p.rows_pad, (double*)(ws + p.off_terms),
-                     (uint32_t*)(ws + p.off_used), (double*)(ws + p.off_sums), ibs0, ibs1,
-                     nonmiss, count, z0, z1, z2, pi_hat, st);
+  rc = launch_genome(counts, s.nv, (double*)(ws + p.off_sums), ibs0, ibs1, nonmiss, count, z0, z1,
+                     z2, pi_hat, st);
   if (rc == PG_OK) mark_stage(2, st);
   return rc;
 }

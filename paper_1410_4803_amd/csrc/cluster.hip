@@ -99,68 +99,41 @@ int launch_ibs_similarity(const uint32_t* i1, const uint32_t* i2, const uint32_t
 // increasing marker order, so the results are the same doubles any
 // implementation of these formulas in that order gets.
 
-// One wave per marker row of the variant-major operand D (rows_pad x wn
-// words of 16 codes, padding codes missing): counts the calls and A2 alleles,
-// then writes the five terms (0 when n < 4) to terms[q * rows_pad + v] and
-// whether the marker counts to used[v].
-__global__ __launch_bounds__(256) void k_genome_terms(const uint32_t* __restrict__ D, int64_t wn,
-                                                      int64_t nv, int64_t rows_pad,
-                                                      double* __restrict__ terms,
-                                                      uint32_t* __restrict__ used) {
-  const int lane = threadIdx.x & 63;
-  const int64_t v = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 6;
-  if (v >= nv) return;
-  const uint32_t* row = D + v * wn;
-  int64_t calls = 0, a2 = 0;
-  for (int64_t w = lane; w < wn; w += 64) {
-    const uint32_t x = row[w];
-    const uint32_t lo = x & 0x55555555u, hi = (x >> 1) & 0x55555555u;
-    calls += __popc((hi | ~lo) & 0x55555555u);          // codes 00, 10, 11
-    a2 += 2 * __popc(hi & lo) + __popc(hi & ~lo);       // 11 twice, 10 once
-  }
-  for (int d = 32; d > 0; d >>= 1) {
-    calls += __shfl_xor(calls, d, 64);
-    a2 += __shfl_xor(a2, d, 64);
-  }
-  if (lane != 0) return;
-  double t[5] = {0.0, 0.0, 0.0, 0.0, 0.0};
-  const bool ok = 2 * calls >= 4;
-  if (ok) {
-    const double X = (double)a2, Y = (double)(2 * calls - a2), n = (double)(2 * calls);
-    const double d4 = __dmul_rn(__dmul_rn(__dmul_rn(n, __dsub_rn(n, 1.0)), __dsub_rn(n, 2.0)),
-                                __dsub_rn(n, 3.0));
-    const double d3 = __dmul_rn(__dmul_rn(n, __dsub_rn(n, 1.0)), __dsub_rn(n, 2.0));
-    const double x2 = __dmul_rn(X, __dsub_rn(X, 1.0)), y2 = __dmul_rn(Y, __dsub_rn(Y, 1.0));
-    const double x3 = __dmul_rn(x2, __dsub_rn(X, 2.0)), y3 = __dmul_rn(y2, __dsub_rn(Y, 2.0));
-    t[0] = __ddiv_rn(__dmul_rn(__dmul_rn(2.0, x2), y2), d4);
-    t[1] = __ddiv_rn(__dmul_rn(4.0, __dadd_rn(__dmul_rn(x3, Y), __dmul_rn(X, y3))), d4);
-    t[2] = __ddiv_rn(__dadd_rn(__dadd_rn(__dmul_rn(x3, __dsub_rn(X, 3.0)),
-                                         __dmul_rn(y3, __dsub_rn(Y, 3.0))),
-                               __dmul_rn(__dmul_rn(4.0, x2), y2)),
-                     d4);
-    t[3] = __ddiv_rn(__dmul_rn(2.0, __dadd_rn(__dmul_rn(x2, Y), __dmul_rn(X, y2))), d3);
-    t[4] = __ddiv_rn(__dadd_rn(__dadd_rn(__dadd_rn(x3, y3), __dmul_rn(x2, Y)), __dmul_rn(X, y2)),
-                     d3);
-  }
+// A marker's five terms from its {calls, A2 alleles}; whether it counts.
+__device__ __forceinline__ bool genome_terms(uint2 c, double (&t)[5]) {
 #pragma unroll
-  for (int q = 0; q < 5; ++q) terms[q * rows_pad + v] = t[q];
-  used[v] = ok ? 1u : 0u;
+  for (int q = 0; q < 5; ++q) t[q] = 0.0;
+  const int64_t calls = c.x, a2 = c.y;
+  if (2 * calls < 4) return false;
+  const double X = (double)a2, Y = (double)(2 * calls - a2), n = (double)(2 * calls);
+  const double d4 = __dmul_rn(__dmul_rn(__dmul_rn(n, __dsub_rn(n, 1.0)), __dsub_rn(n, 2.0)),
+                              __dsub_rn(n, 3.0));
+  const double d3 = __dmul_rn(__dmul_rn(n, __dsub_rn(n, 1.0)), __dsub_rn(n, 2.0));
+  const double x2 = __dmul_rn(X, __dsub_rn(X, 1.0)), y2 = __dmul_rn(Y, __dsub_rn(Y, 1.0));
+  const double x3 = __dmul_rn(x2, __dsub_rn(X, 2.0)), y3 = __dmul_rn(y2, __dsub_rn(Y, 2.0));
+  t[0] = __ddiv_rn(__dmul_rn(__dmul_rn(2.0, x2), y2), d4);
+  t[1] = __ddiv_rn(__dmul_rn(4.0, __dadd_rn(__dmul_rn(x3, Y), __dmul_rn(X, y3))), d4);
+  t[2] = __ddiv_rn(__dadd_rn(__dadd_rn(__dmul_rn(x3, __dsub_rn(X, 3.0)),
+                                       __dmul_rn(y3, __dsub_rn(Y, 3.0))),
+                             __dmul_rn(__dmul_rn(4.0, x2), y2)),
+                   d4);
+  t[3] = __ddiv_rn(__dmul_rn(2.0, __dadd_rn(__dmul_rn(x2, Y), __dmul_rn(X, y2))), d3);
+  t[4] = __ddiv_rn(__dadd_rn(__dadd_rn(__dadd_rn(x3, y3), __dmul_rn(x2, Y)), __dmul_rn(X, y2)),
+                   d3);
+  return true;
 }
 
 // The five sums and the count K of markers that count, in two levels: each
 // run of kSumRun consecutive markers is summed in increasing marker order
 // from 0, then the runs' sums are added in increasing run order from 0.
-// k_genome_run_sums: one block per run; all threads stage the run's five
-// term columns in LDS (coalesced loads), then threads 0..4 each add their
-// column in order; a marker that does not count, and the padding past the
-// last marker, add +0.0, which leaves a non-negative sum unchanged.  It
-// writes part[q * n_runs + r] (q < 5) and the run's count at q = 5.
+// k_genome_run_sums: one block per run; all threads evaluate their markers'
+// terms into LDS, then threads 0..4 each add their column in order; a marker
+// that does not count, and the padding past the last marker, add +0.0, which
+// leaves a non-negative sum unchanged.  It writes part[q * n_runs + r] (q < 5)
+// and the run's count at q = 5.
 constexpr int kSumRun = 1024;
-constexpr int kSumPer = 5 * kSumRun / 256;      // staged values per thread
-__global__ __launch_bounds__(256) void k_genome_run_sums(const double* __restrict__ terms,
-                                                         const uint32_t* __restrict__ used,
-                                                         int64_t nv, int64_t rows_pad,
-                                                         int64_t n_runs,
+__global__ __launch_bounds__(256) void k_genome_run_sums(const uint2* __restrict__ counts,
+                                                         int64_t nv, int64_t n_runs,
                                                          double* __restrict__ part) {
   __shared__ double buf[5][kSumRun + 1];
   __shared__ unsigned int kcount;
@@ -168,18 +141,17 @@ __global__ __launch_bounds__(256) void k_genome_run_sums(const double* __restric
   const int64_t r = blockIdx.x, c0 = r * kSumRun;
   const int64_t len = nv - c0 < kSumRun ? nv - c0 : kSumRun;
   if (t == 0) kcount = 0;
-  double v[kSumPer];
+  uint2 c[kSumRun / 256];
 #pragma unroll
-  for (int u = 0; u < kSumPer; ++u) {
-    const int i = t + 256 * u, q = i / kSumRun, j = i % kSumRun;
-    v[u] = j < len ? terms[q * rows_pad + c0 + j] : 0.0;
-  }
+  for (int u = 0; u < kSumRun / 256; ++u)
+    c[u] = t + 256 * u < len ? counts[c0 + t + 256 * u] : make_uint2(0, 0);
   unsigned int K = 0;
-  for (int64_t j = t; j < len; j += 256) K += used[c0 + j];
 #pragma unroll
-  for (int u = 0; u < kSumPer; ++u) {
-    const int i = t + 256 * u;
-    buf[i / kSumRun][i % kSumRun] = v[u];
+  for (int u = 0; u < kSumRun / 256; ++u) {
+    double v[5];
+    K += genome_terms(c[u], v);
+#pragma unroll
+    for (int q = 0; q < 5; ++q) buf[q][t + 256 * u] = v[q];
   }
   __syncthreads();
   if (K) atomicAdd(&kcount, K);
@@ -199,15 +171,19 @@ __global__ __launch_bounds__(256) void k_genome_run_sums(const double* __restric
   if (t == 0) part[5 * n_runs + r] = (double)kcount;
 }
 
-// out = {S00, S10, S20, S11, S21, K}: threads 0..4 add the runs' sums of
-// their column in run order; thread 5 adds the counts (integers, exact).
-__global__ __launch_bounds__(64) void k_genome_total(const double* __restrict__ part,
-                                                     int64_t n_runs, double* __restrict__ out) {
-  const int t = threadIdx.x;
-  if (t > 5) return;
+// out = {S00, S10, S20, S11, S21, K}: wave q adds the runs' sums of its column
+// in run order, 64 loaded at a time and taken from their lanes; column 5 holds
+// the counts (integers, exact).
+__global__ __launch_bounds__(384) void k_genome_total(const double* __restrict__ part,
+                                                      int64_t n_runs, double* __restrict__ out) {
+  const int lane = threadIdx.x & 63, q = threadIdx.x >> 6;
   double S = 0.0;
-  for (int64_t r = 0; r < n_runs; ++r) S = __dadd_rn(S, part[t * n_runs + r]);
-  out[t] = S;
+  for (int64_t r0 = 0; r0 < n_runs; r0 += 64) {
+    const double p = r0 + lane < n_runs ? part[q * n_runs + r0 + lane] : 0.0;
+    const int n = n_runs - r0 < 64 ? (int)(n_runs - r0) : 64;
+    for (int u = 0; u < n; ++u) S = __dadd_rn(S, __shfl(p, u));
+  }
+  if (lane == 0) out[q] = S;
 }
 
 __global__ __launch_bounds__(256) void k_genome_pairs(const double* __restrict__ sums,
@@ -244,21 +220,16 @@ __global__ __launch_bounds__(256) void k_genome_pairs(const double* __restrict__
   }
 }
 
-int launch_genome(const uint32_t* D, int64_t wn, int64_t nv, int64_t rows_pad, double* terms,
-                  uint32_t* used, double* sums, const uint32_t* i0, const uint32_t* i1,
-                  const uint32_t* nm, int64_t count, double* z0, double* z1, double* z2,
-                  double* pi, hipStream_t st) {
-  hipLaunchKernelGGL(k_genome_terms, dim3((unsigned)ceil_div(nv, 4)), dim3(256), 0, st, D, wn, nv,
-                     rows_pad, terms, used);
-  int rc = check_launch("genome_terms");
-  if (rc != PG_OK) return rc;
+int launch_genome(const uint2* counts, int64_t nv, double* sums, const uint32_t* i0,
+                  const uint32_t* i1, const uint32_t* nm, int64_t count, double* z0, double* z1,
+                  double* z2, double* pi, hipStream_t st) {
   const int64_t n_runs = genome_runs(nv);
   double* part = sums + 8;
-  hipLaunchKernelGGL(k_genome_run_sums, dim3((unsigned)n_runs), dim3(256), 0, st, terms, used, nv,
-                     rows_pad, n_runs, part);
-  rc = check_launch("genome_run_sums");
+  hipLaunchKernelGGL(k_genome_run_sums, dim3((unsigned)n_runs), dim3(256), 0, st, counts, nv,
+                     n_runs, part);
+  int rc = check_launch("genome_run_sums");
   if (rc != PG_OK) return rc;
-  hipLaunchKernelGGL(k_genome_total, dim3(1), dim3(64), 0, st, part, n_runs, sums);
+  hipLaunchKernelGGL(k_genome_total, dim3(1), dim3(384), 0, st, part, n_runs, sums);
   rc = check_launch("genome_total");
   mark_stage(1, st);
   if (rc != PG_OK || count <= 0) return rc;

@@ -119,10 +119,9 @@ int64_t sample_major_job_blocks(int64_t rows_pad, int64_t wp);
 // jobs: device array of n_jobs jobs in increasing block_begin.
 int launch_sample_major_jobs(const LayoutJob* jobs, int n_jobs, int64_t total_blocks,
                              hipStream_t st);
-// Variant-major 2-bit words over the selected samples: D[v*wn + w] holds
-// codes of samples 16w..16w+15 of selected variant v; rows_pad x wn.
-int launch_variant_major_2bit(const Sel& s, uint32_t* D, int64_t rows_pad, int64_t wn,
-                              hipStream_t st);
+// {calls, A2 alleles} of every selected variant; with a sample list by way of
+// D (nv x wn words of 16 samples, wn = ceil(m / 16)).
+int launch_allele_counts(const Sel& s, uint32_t* D, int64_t wn, uint2* counts, hipStream_t st);
 
 // Variant-major bit planes for the popcount LD path: for 32-sample word w,
 // plane p (0 = homozygous A2, 1 = homozygous A1, 2 = non-missing) of selected
@@ -263,7 +262,8 @@ struct LdScratch {
 // Number of per-block partial sums the row-offset scan needs.
 int ld_scan_blocks(int64_t nv);
 
-// The LD operands: D as launch_variant_major_2bit, and beside it the nibble
+// The LD operands: variant-major 2-bit words over the selected samples, D[v*wn
+// + w] holding samples 16w..16w+15 of selected variant v, and beside it the nibble
 // operand E of the fp4 tile: 64 variants x 64 samples in 512 words (rows_pad *
 // wn * 2 words in all; wn a multiple of 16; NULL: D only).  Clears sc's bitmap
 // and counts, and counts the codes of every variant for launch_ld_totals.
@@ -440,17 +440,15 @@ int launch_ibs_distance(const uint32_t* i0, const uint32_t* i1, const uint32_t* 
                         double* d, hipStream_t st);
 int launch_ibs_similarity(const uint32_t* i1, const uint32_t* i2, const uint32_t* nm,
                           int64_t count, double* s, hipStream_t st);
-// IBD report from the variant-major operand D of the selection (rows_pad x
-// wn words): terms 5 x rows_pad doubles, used rows_pad words, sums
-// genome_sums_doubles(nv) doubles of workspace (the six totals, padded to 8,
-// then six per run of 1,024 markers); then `count` pairs of IBS counts.
+// IBD report from the variants' {calls, A2 alleles}: sums genome_sums_doubles(nv)
+// doubles of workspace (the six totals, padded to 8, then six per run of 1,024
+// markers); then `count` pairs of IBS counts.
 // Stage 1 ends after the per-marker averages.
 inline int64_t genome_runs(int64_t nv) { return nv > 0 ? (nv + 1023) / 1024 : 1; }
 inline int64_t genome_sums_doubles(int64_t nv) { return 8 + 6 * genome_runs(nv); }
-int launch_genome(const uint32_t* D, int64_t wn, int64_t nv, int64_t rows_pad, double* terms,
-                  uint32_t* used, double* sums, const uint32_t* i0, const uint32_t* i1,
-                  const uint32_t* nm, int64_t count, double* z0, double* z1, double* z2,
-                  double* pi, hipStream_t st);
+int launch_genome(const uint2* counts, int64_t nv, double* sums, const uint32_t* i0,
+                  const uint32_t* i1, const uint32_t* nm, int64_t count, double* z0, double* z1,
+                  double* z2, double* pi, hipStream_t st);
 // D: m x m doubles; nn_d: m doubles; nn_j: m ints; ctl: 4 ints (the first two
 // count the rows to rescan); rows: m ints.  Where the merges do not run in
 // rounds: from kClusterSplitMin samples on, each merge runs as two launches
