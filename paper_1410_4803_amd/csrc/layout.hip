@@ -102,23 +102,29 @@ __device__ __forceinline__ void row_words16(const Sel& s, const int64_t (&v)[N],
 // The block's 34 KB of LDS let four blocks share a CU (512 x 512 blocks, 68
 // KB: two per CU, 17% slower at 10,000 x 100,000).
 // Samples past the matrix and variants past the selection are missing calls.
+// Where those blocks would leave CUs idle, blocks of 128 samples x 256 variants
+// by 128 threads, each with one word's sixteen loads: 500 x 5,000, 20 blocks in
+// two passes 14 us, 80 blocks 9 us.
 constexpr int kSmTG = 32;            // sample groups (16 samples) per block
+constexpr int kSmTGSmall = 8;
 constexpr int kSmTW = 16;            // T words (16 variants) per block
 constexpr int kSmTS = kSmTW + 1;     // LDS row stride (words)
 
-// Block `bid` of the tiled layout of one operand.
+// Block `bid` of the tiled layout of one operand: kTG sample groups, kThreads
+// threads.
+template <int kTG, int kThreads>
 __device__ __forceinline__ void sample_major_tiled_block(const Sel& s, uint32_t* __restrict__ T,
                                                          int64_t rows_pad, int64_t wp,
                                                          int aligned, int64_t bid,
                                                          uint32_t* s_out) {
-  const int64_t nb_g = ceil_div(rows_pad / 16, kSmTG);
-  const int64_t g0 = (bid % nb_g) * kSmTG;   // sample group (16 samples)
+  const int64_t nb_g = ceil_div(rows_pad / 16, kTG);
+  const int64_t g0 = (bid % nb_g) * kTG;     // sample group (16 samples)
   const int64_t a0 = (bid / nb_g) * kSmTW;   // T word (16 variants)
   const int t = threadIdx.x;
-  const int gl = t % kSmTG;
+  const int gl = t % kTG;
 #pragma unroll 1
-  for (int i = 0; i < kSmTW / 8; ++i) {
-    const int al = t / kSmTG + 8 * i;
+  for (int i = 0; i < kSmTW * kTG / kThreads; ++i) {
+    const int al = t / kTG + kThreads / kTG * i;
     const int64_t a = a0 + al, g = g0 + gl;
     int64_t vr[16], gr[16];
 #pragma unroll
@@ -127,25 +133,26 @@ __device__ __forceinline__ void sample_major_tiled_block(const Sel& s, uint32_t*
     row_words16(s, vr, gr, aligned != 0, x);
     transpose16_2bit(x);
 #pragma unroll
-    for (int c = 0; c < 16; ++c) s_out[(c * kSmTG + gl) * kSmTS + al] = x[c];
+    for (int c = 0; c < 16; ++c) s_out[(c * kTG + gl) * kSmTS + al] = x[c];
   }
   __syncthreads();
-  for (int e = t; e < 16 * kSmTG * kSmTW; e += 256) {
+  for (int e = t; e < 16 * kTG * kSmTW; e += kThreads) {
     const int row = e / kSmTW, col = e % kSmTW;
     const int64_t k = 16 * g0 + row, a = a0 + col;
-    if (k < rows_pad && a < wp)   // T row 16 gl + c is LDS row c * kSmTG + gl
-      T[k * wp + a] = s_out[((row & 15) * kSmTG + (row >> 4)) * kSmTS + col];
+    if (k < rows_pad && a < wp)   // T row 16 gl + c is LDS row c * kTG + gl
+      T[k * wp + a] = s_out[((row & 15) * kTG + (row >> 4)) * kSmTS + col];
   }
 }
 
-__global__ __launch_bounds__(256) void k_sample_major_tiled(Sel s, uint32_t* __restrict__ T,
-                                                            int64_t rows_pad, int64_t wp,
-                                                            int aligned) {
-  __shared__ uint32_t s_out[16 * kSmTG * kSmTS];
+template <int kTG, int kThreads>
+__global__ __launch_bounds__(kThreads) void k_sample_major_tiled(Sel s, uint32_t* __restrict__ T,
+                                                                 int64_t rows_pad, int64_t wp,
+                                                                 int aligned) {
+  __shared__ uint32_t s_out[16 * kTG * kSmTS];
   // blocks of one XCD take consecutive sample groups of the same variants, so
   // the row pieces that straddle two blocks' reads meet in that XCD's L2
-  sample_major_tiled_block(s, T, rows_pad, wp, aligned, xcd_swizzle(blockIdx.x, gridDim.x),
-                           s_out);
+  sample_major_tiled_block<kTG, kThreads>(s, T, rows_pad, wp, aligned,
+                                          xcd_swizzle(blockIdx.x, gridDim.x), s_out);
 }
 
 // Many operands in one launch: block b lays out block b - block_begin of the
@@ -160,7 +167,7 @@ __global__ __launch_bounds__(256) void k_sample_major_jobs(const LayoutJob* __re
     if (jobs[mid].block_begin <= b) lo = mid; else hi = mid - 1;
   }
   const LayoutJob j = jobs[lo];
-  sample_major_tiled_block(j.s, j.T, j.rows_pad, j.wp, j.aligned, b - j.block_begin, s_out);
+  sample_major_tiled_block<kSmTG, 256>(j.s, j.T, j.rows_pad, j.wp, j.aligned, b - j.block_begin, s_out);
 }
 
 int64_t sample_major_job_blocks(int64_t rows_pad, int64_t wp) {
@@ -445,8 +452,15 @@ int launch_sample_major_2bit(const Sel& s, uint32_t* T, int64_t rows_pad, int64_
                              hipStream_t st) {
   if (!s.idx) {
     const int64_t blocks = sample_major_job_blocks(rows_pad, wp);
-    hipLaunchKernelGGL(k_sample_major_tiled, dim3((unsigned)blocks), dim3(256), 0, st, s, T,
-                       rows_pad, wp, (int)rows_dword_aligned(s));
+    const int aligned = (int)rows_dword_aligned(s);
+    if (blocks >= 256) {
+      hipLaunchKernelGGL((k_sample_major_tiled<kSmTG, 256>), dim3((unsigned)blocks), dim3(256), 0,
+                         st, s, T, rows_pad, wp, aligned);
+    } else {
+      const int64_t small = ceil_div(wp, kSmTW) * ceil_div(rows_pad, 16 * kSmTGSmall);
+      hipLaunchKernelGGL((k_sample_major_tiled<kSmTGSmall, 128>), dim3((unsigned)small), dim3(128),
+                         0, st, s, T, rows_pad, wp, aligned);
+    }
     return check_launch("sample_major_tiled");
   }
   dim3 grid((unsigned)(ceil_div(rows_pad, kSmSamples) * ceil_div(wp, kSmWords)));
