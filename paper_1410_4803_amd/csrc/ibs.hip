@@ -247,6 +247,32 @@ IbsTail ibs_tail_plan(int64_t rows_pad, int64_t wp) {
   return t;
 }
 
+// The tail split a launch runs within the planned workspace: at most as many
+// ranges, and none where they do not pay for the parked sums -- 8 r S times
+// 196,608 bytes out and back at about 4 TB/s, which is 0.3 r S / chunks of a
+// round of 1.3 us per chunk -- by an eighth of a round.  The plan's ranges
+// always, and these: 4,548 samples x 5,000 variants 178 and 146 us, 6,000 x
+// 5,000 303 and 218, x 20,000 635 and 597, 10,000 x 10,000 907 and 893.
+static IbsTail ibs_tail_use(IbsTail t, int64_t chunks) {
+  constexpr int64_t kCusPerXcd = 32;
+  auto cost = [&](int64_t S) {
+    return (double)ceil_div(t.rmax * S, kCusPerXcd) / (double)S + 0.01 * (double)S +
+           0.3 * (double)(t.rmax * S) / (double)chunks;
+  };
+  double best = 1.0;
+  int64_t best_s = 1;
+  for (int64_t S = 2; t.tail && S <= t.n_split; ++S)
+    // (the planned number where it is as good as another)
+    if (cost(S) < best || (S == t.n_split && cost(S) < best + 0.05 && cost(S) < 1.0)) {
+      best = cost(S);
+      best_s = S;
+    }
+  t.tail = best_s > 1 && 1.0 - best >= 0.125;
+  t.cps = ceil_div(chunks, best_s);
+  t.n_split = ceil_div(chunks, t.cps);
+  return t;
+}
+
 // `variant` is resolved (resolve_ibs_variant): 1 .. kIbsVariants - 1.
 int launch_ibs_mfma(const uint32_t* T, int64_t wp, const IbsOut& o, int variant, hipStream_t st,
                     int32_t* part) {
@@ -256,7 +282,7 @@ int launch_ibs_mfma(const uint32_t* T, int64_t wp, const IbsOut& o, int variant,
   int64_t n_split = 1, cps = 0;
   if ((variant == kIbsVariantPipe || fp4) && part) ibs_split(nt * kT, wp, n_split, cps);
   if ((variant == kIbsVariantPipe || fp4) && part && n_split == 1) {
-    const IbsTail tl = ibs_tail_plan(nt * kT, wp);
+    const IbsTail tl = ibs_tail_use(ibs_tail_plan(nt * kT, wp), wp / kKW);
     if (tl.tail) {
       if (tl.head > 0) {
         hipLaunchKernelGGL(fp4 ? k_ibs_head<true> : k_ibs_head<false>,
