@@ -216,8 +216,10 @@ def bench_prune(torch, lib, hip, pg, wp, dev, steps):
 
 def bench_grm(torch, lib, hip, pg, wg, dev, steps, path="auto"):
     """Relationship matrix (full layout): whole-call time and its stages.
-    Algorithmic work: one fp64 multiply-add per (unique pair incl. the
-    diagonal) x variant, i.e. 2 * m(m+1)/2 * V flops."""
+    Algorithmic work per (unique pair incl. the diagonal) x variant: 16 int8
+    multiply-adds (15 digit places and the count) on the digit path, which the
+    default takes at these sizes, one fp64 multiply-add on the fp64 kernels
+    (path variants 1 to 3)."""
     n, V = wg["n"], wg["V"]
     c = pg.Cohort.from_numpy(wg["bed"], n, device=dev)
     A = torch.empty((n, n), dtype=torch.float64, device=dev)
@@ -225,7 +227,9 @@ def bench_grm(torch, lib, hip, pg, wg, dev, steps, path="auto"):
     ws = torch.empty(pg.grm_workspace_bytes(c), dtype=torch.uint8, device=dev)
     ms, st = timed_steps(torch, lib, hip, lambda: pg.grm_matrix(
         c, layout="full", path=path, out=(A, Nn), workspace=ws), steps, 2, 3)
-    flops = 2.0 * n * (n + 1) / 2 * V
+    fp64 = isinstance(path, int) and 1 <= path >> 8 & 0xFF <= 3
+    flops = 2.0 * n * (n + 1) / 2 * V * (1 if fp64 else 16)
+    peak = PEAK_FP64_TFLOPS if fp64 else PEAK_INT8_TOPS
     pair_ms = mean(st[1])
     ach = flops / (pair_ms * 1e-3) / 1e12
     torch.cuda.synchronize()
@@ -234,9 +238,9 @@ def bench_grm(torch, lib, hip, pg, wg, dev, steps, path="auto"):
             "value": round(n * (n - 1) / 2 * V / (ms * 1e-3) / 1e9, 1), "unit": "G/s",
             "stages_ms": {"layout_and_tables": round(mean(st[0]), 3),
                           "pair_kernel": round(pair_ms, 3)},
-            "roofline": {"bound": "mfma", "kernel": "k_grm_mfma", "unit": "TFLOP/s",
-                         "achieved": round(ach, 2), "peak": PEAK_FP64_TFLOPS,
-                         "frac": round(ach / PEAK_FP64_TFLOPS, 4)}}
+            "roofline": {"bound": "mfma", "kernel": "k_grm_mfma" if fp64 else "k_gi_pairs",
+                         "unit": "TFLOP/s" if fp64 else "TOP/s",
+                         "achieved": round(ach, 2), "peak": peak, "frac": round(ach / peak, 4)}}
 
 
 def bench_cluster(torch, lib, hip, pg, wc, dev, steps):
