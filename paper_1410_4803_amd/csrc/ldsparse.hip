@@ -511,7 +511,6 @@ __device__ __forceinline__ void ld_sparse_tile(
 constexpr int kCtChunk = 2;                        // steps of 64 samples
 constexpr int kCtGroup = kCtChunk * 512;           // words of a group's chunk
 constexpr int kCtBuf = 4 * kCtGroup;               // two groups a side
-constexpr int64_t kCtGrid = 8192;
 
 // Whether the 128 x 128 tile (I2, J2) is one of these (n_groups of 64).
 __device__ __forceinline__ bool ld_tile_complete(const int* gmax, int64_t I2, int64_t J2,
@@ -625,21 +624,16 @@ __global__ __launch_bounds__(256, 3) void k_ld_complete(
     LdScratch sc) {
   __shared__ __attribute__((aligned(16))) uint32_t smem[3 * kCtBuf];
   if (*groups_ok < min_groups) return;
-  const int64_t n_row = ceil_div(n_groups, 2), tiles = n_row * n_band;
-  for (int64_t i = blockIdx.x; i < tiles; i += gridDim.x) {
-    const int64_t blk = xcd_swizzle(i, tiles);
-    const int64_t I2 = blk / n_band, J2 = I2 + blk % n_band;
-    if (J2 >= n_row || !ld_tile_complete(gmax, I2, J2, n_groups)) continue;
-    ld_complete_tile(E, wn / 4, vst, m, nv, n_groups, I2, J2, window, r2_min, sc, (lds_t*)smem);
-    __syncthreads();   // the buffers are reused
-  }
+  const int64_t blk = xcd_swizzle(blockIdx.x, gridDim.x);
+  const int64_t I2 = blk / n_band, J2 = I2 + blk % n_band;
+  if (J2 >= ceil_div(n_groups, 2) || !ld_tile_complete(gmax, I2, J2, n_groups)) return;
+  ld_complete_tile(E, wn / 4, vst, m, nv, n_groups, I2, J2, window, r2_min, sc, (lds_t*)smem);
 }
 
-// Tiles blockIdx.x, + gridDim.x, ... of the band: at most kSpGrid blocks, so
-// that a band the path leaves alone costs few block starts (61 us for the
-// 132,000 tiles of 500,000 variants x window 1,000 with a block per tile).
-constexpr int64_t kSpGrid = 16384;
-
+// One tile per block, in the band's order: neighbours that run together share
+// their strips in L2 (blocks that walked several tiles each, for fewer block
+// starts where the path is off, took 12% longer at 5,000 x 300,000; starting
+// 132,000 blocks that leave at once takes 29 us).
 template <bool kFp4>
 __global__ __launch_bounds__(256, 3) void k_ld_sparse(
     const uint32_t* __restrict__ D, int64_t wn, const uint32_t* __restrict__ T, int64_t t_rows,
@@ -650,18 +644,13 @@ __global__ __launch_bounds__(256, 3) void k_ld_sparse(
     double r2_min, LdScratch sc, pg_ld_pair* __restrict__ dbg, int64_t v0) {
   if (*groups_ok < min_groups) return;
   if (kFp4 && !dbg && groups_ok[2] == 0) return;   // every tile is k_ld_complete's
-  const int64_t tiles = n_row_tiles * n_band;
-  for (int64_t i = blockIdx.x; i < tiles; i += gridDim.x) {
-    const int64_t blk = xcd_swizzle(i, tiles);
-    const int64_t I = blk / n_band;
-    const int64_t J = I + blk % n_band;
-    if (J >= n_row_tiles || !ld_tile_sparse(gsum, gmax, groups_ok, min_groups, I, J, cap, budget))
-      continue;
-    if (kFp4 && !dbg && ld_tile_complete(gmax, I >> 1, J >> 1, n_row_tiles)) continue;
-    ld_sparse_tile<kFp4>(D, wn, T, t_rows, lists, vst, cap, m, nv, I, J, window, r2_min, sc, dbg,
-                         v0);
-    __syncthreads();   // the cells are reused
-  }
+  const int64_t blk = xcd_swizzle(blockIdx.x, gridDim.x);
+  const int64_t I = blk / n_band;
+  const int64_t J = I + blk % n_band;
+  if (J >= n_row_tiles || !ld_tile_sparse(gsum, gmax, groups_ok, min_groups, I, J, cap, budget))
+    return;
+  if (kFp4 && !dbg && ld_tile_complete(gmax, I >> 1, J >> 1, n_row_tiles)) return;
+  ld_sparse_tile<kFp4>(D, wn, T, t_rows, lists, vst, cap, m, nv, I, J, window, r2_min, sc, dbg, v0);
 }
 
 constexpr int kTrW = 32;            // words per block side: 512 variants x 512 samples
@@ -744,16 +733,13 @@ int launch_ld_sparse(const uint32_t* D, const uint32_t* E, int64_t wn, const uin
   if (E && !dbg) {
     const int64_t n_row2 = ceil_div(n_row_tiles, 2), n_band2 = ((int64_t)window + 127) / 128 + 1;
     hipLaunchKernelGGL(k_ld_complete,
-                       dim3((unsigned)(n_row2 * n_band2 < kCtGrid ? n_row2 * n_band2 : kCtGrid)),
-                       dim3(256), 0, st, E, wn, sp.vst, sp.gmax, sp.groups_ok, sp.min_groups, m, nv,
+                       dim3((unsigned)(n_row2 * n_band2)), dim3(256), 0, st, E, wn, sp.vst, sp.gmax, sp.groups_ok, sp.min_groups, m, nv,
                        n_row_tiles, n_band2, window, r2_min, sc);
     rc = check_launch("ld_complete");
     if (rc != PG_OK) return rc;
   }
   hipLaunchKernelGGL(E ? k_ld_sparse<true> : k_ld_sparse<false>,
-                     dim3((unsigned)(n_row_tiles * n_band < kSpGrid ? n_row_tiles * n_band
-                                                                    : kSpGrid)),
-                     dim3(256), 0, st, E ? E : D, wn, T, t_rows, sp.lists, sp.vst, sp.gsum, sp.gmax,
+                     dim3((unsigned)(n_row_tiles * n_band)), dim3(256), 0, st, E ? E : D, wn, T, t_rows, sp.lists, sp.vst, sp.gsum, sp.gmax,
                      sp.groups_ok, sp.min_groups, sp.cap, sp.budget, m, nv, n_row_tiles, n_band,
                      window, r2_min, sc, dbg, v0);
   rc = check_launch("ld_sparse");
