@@ -591,11 +591,16 @@ struct ClRounds {
 // all of them afterwards.  Arrivals count in eight words (one per XCD, as
 // blocks are dealt round robin) and then in one, since 256 additions to one
 // word take 10 us; the last one raises the epoch that the others wait for.
+// Every wave waits for its own stores to be in L2 before the block's barrier
+// (which waits for LDS only), so that the write-back of the one wave that
+// signals the arrival covers them all.  A write-back by every wave costs more:
+// 10,000 samples 3.7 -> 5.4 ms, equal distances of 6,000 96 -> 278 ms.
 // nb may only fall from one barrier to the next.
 struct ClBarrier {
   unsigned* bar;
   unsigned group_target, root_target, epoch;
   __device__ __forceinline__ void wait(unsigned nb) {
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     __syncthreads();
     if (nb > 1) {
       const unsigned g = blockIdx.x & 7u;
@@ -613,8 +618,6 @@ struct ClBarrier {
           __builtin_amdgcn_s_sleep(1);
         __threadfence();
       }
-    } else {
-      __threadfence_block();
     }
     __syncthreads();
   }
