@@ -385,7 +385,9 @@ int pg_cluster_workspace_bytes(int64_t m, size_t* bytes);
 
 /*
  * Complete-linkage agglomerative clustering of m samples on the IBS
- * distance, from full-layout (m x m) pg_ibs_matrix output.  While more than
+ * distance, from full-layout (m x m) pg_ibs_matrix output, that is, symmetric
+ * counts (on others the m - 1 merges are some sequence of the same form, fixed
+ * by the counts).  While more than
  * one cluster remains, the two clusters with the smallest complete-linkage
  * distance (largest member-to-member distance) merge; ties go to the pair
  * with the smallest a, then the smallest b.  merges (device, m - 1 records)

@@ -1,0 +1,34 @@
+"""Clustering on counts that are not symmetric (nearest neighbours can form a
+cycle, so that no two samples are mutually nearest): every label retires once,
+whatever the workspace held before, and the same counts give the same merges."""
+import numpy as np
+import pytest
+import torch
+
+pytestmark = pytest.mark.gpu
+
+pg = pytest.importorskip("paper_1410_4803_amd")
+
+
+@pytest.mark.parametrize("m", [3, 40, 300, 1500])
+@pytest.mark.parametrize("kind", ["cycle", "random"])
+def test_asymmetric_counts_give_a_whole_sequence(m, kind):
+    N = 4096
+    if kind == "cycle":                   # the nearest of every k is k + 1
+        i = np.arange(m)
+        w = 7 + (i[None, :] - i[:, None]) % m
+    else:
+        w = np.random.default_rng(m).integers(0, N, (m, m))
+    i0, i1 = (w // 2).astype(np.int32), (w % 2).astype(np.int32)
+    dev = [torch.from_numpy(np.ascontiguousarray(x)).cuda()
+           for x in (i0, i1, np.full((m, m), N, np.int32))]
+    ws = torch.empty(pg.cluster_workspace_bytes(m), dtype=torch.uint8, device="cuda")
+    seen = []
+    for fill in (0, 0x3F, 0xFF):
+        ws.fill_(fill)
+        got = pg.merges_to_numpy(pg.ibs_cluster(dev[0], dev[1], None, dev[2], workspace=ws), m)
+        assert np.array_equal(np.sort(got["b"]), np.arange(1, m))
+        assert np.all((0 <= got["a"]) & (got["a"] < got["b"]))
+        assert np.all(np.diff(got["height"]) >= 0)
+        seen.append(got)
+    assert np.array_equal(seen[0], seen[1]) and np.array_equal(seen[0], seen[2])
