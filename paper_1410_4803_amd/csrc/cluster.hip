@@ -18,7 +18,7 @@
 // GPU plan: the working matrix D (m x m doubles) lives in the workspace.  Up
 // to kClMaxSlots samples the merges run in rounds of mutually nearest pairs,
 // in one cooperative launch (k_cl_rounds below).  Larger cohorts, and calls
-// that are captured into a graph, merge one pair at a time:
+// that cannot launch it (cluster_rounds_ok), merge one pair at a time:
 // for each active cluster k the cached nearest neighbour among l > k,
 // nn[k] = argmin over (D[k][l], l), is kept; the globally closest pair is the
 // argmin over k of (nn_d[k], k), which is exactly the lexicographic rule.
@@ -1005,25 +1005,35 @@ int64_t cluster_rounds_bytes(int64_t m) {
   return 2 * m * ld * 8 + 2 * round_up(m, 32) * (8 + 4 + 4) + round_up(m, 32) * 16 + kClBarWords * 4;
 }
 
-// Whether the rounds can run: the slots fit, the device launches
-// cooperatively, and the stream is not capturing (a captured call takes the
-// launches per merge, plain kernel nodes).  `blocks`: one per CU, or one
-// per kClPerBlock rows.
+// Whether the rounds can run: the slots fit, the stream is not capturing (a
+// captured call takes the launches per merge, plain kernel nodes) and has the
+// whole chip (no CU mask), and the device launches cooperatively and holds a
+// block per CU.  `blocks`: one per CU, or one per kClPerBlock rows.
 static bool cluster_rounds_ok(int64_t m, hipStream_t st, unsigned& blocks) {
   if (m > kClMaxSlots) return false;
   hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
-  if (hipStreamIsCapturing(st, &cap) != hipSuccess) {
+  int dev = 0, coop = 0, cus = 0, resident = 0;
+  if (hipStreamIsCapturing(st, &cap) != hipSuccess || hipGetDevice(&dev) != hipSuccess ||
+      hipDeviceGetAttribute(&coop, hipDeviceAttributeCooperativeLaunch, dev) != hipSuccess ||
+      hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
+      hipOccupancyMaxActiveBlocksPerMultiprocessor(
+          &resident, reinterpret_cast<const void*>(k_cl_rounds), kClT, 0) != hipSuccess) {
     (void)hipGetLastError();
     return false;
   }
-  int dev = 0, coop = 0, cus = 0;
-  if (cap != hipStreamCaptureStatusNone || hipGetDevice(&dev) != hipSuccess ||
-      dev < 0 || dev >= kMaxDevices ||
-      hipDeviceGetAttribute(&coop, hipDeviceAttributeCooperativeLaunch, dev) != hipSuccess ||
-      hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
+  if (cap != hipStreamCaptureStatusNone || dev < 0 || dev >= kMaxDevices || !coop || cus < 1 ||
+      resident < 1)
     return false;
+  uint32_t mask[32] = {};
+  if (hipExtStreamGetCUMask(st, 32, mask) == hipSuccess) {
+    int on = 0;
+    for (uint32_t w : mask) on += __builtin_popcount(w);
+    if (on < cus) return false;
+  } else {
+    (void)hipGetLastError();
+  }
   blocks = (unsigned)(ceil_div(m, kClPerBlock) < cus ? ceil_div(m, kClPerBlock) : cus);
-  return coop != 0 && cus > 0;
+  return true;
 }
 
 // The last launch of the rounds on each device, kept until the process ends.
@@ -1033,25 +1043,39 @@ static bool cluster_rounds_ok(int64_t m, hipStream_t st, unsigned& blocks) {
 static std::mutex g_rounds_mu;
 static hipEvent_t g_rounds_done[kMaxDevices] = {};
 
-static int launch_rounds_kernel(ClRounds& p, unsigned blocks, hipStream_t st) {
+// `launched`: whether the device took the grid; if not, nothing ran.
+static int launch_rounds_kernel(ClRounds& p, unsigned blocks, hipStream_t st, bool& launched) {
   std::lock_guard<std::mutex> lock(g_rounds_mu);
+  launched = false;
   int dev = 0;
   hipError_t e = hipGetDevice(&dev);
   if (e == hipSuccess && !g_rounds_done[dev])
     e = hipEventCreateWithFlags(&g_rounds_done[dev], hipEventDisableTiming);
   if (e == hipSuccess) e = hipStreamWaitEvent(st, g_rounds_done[dev], 0);
+  if (e != hipSuccess) {
+    (void)hipGetLastError();
+    return fail(PG_EDEVICE, "cluster_rounds: %s", hipGetErrorString(e));
+  }
   void* args[] = {&p};
-  if (e == hipSuccess)
-    e = hipLaunchCooperativeKernel(reinterpret_cast<const void*>(k_cl_rounds), dim3(blocks),
-                                   dim3(kClT), args, 0, st);
-  if (e == hipSuccess) e = hipEventRecord(g_rounds_done[dev], st);
-  if (e != hipSuccess) return fail(PG_EDEVICE, "cluster_rounds: %s", hipGetErrorString(e));
+  if (hipLaunchCooperativeKernel(reinterpret_cast<const void*>(k_cl_rounds), dim3(blocks),
+                                 dim3(kClT), args, 0, st) != hipSuccess) {
+    (void)hipGetLastError();
+    return PG_OK;
+  }
+  launched = true;
+  e = hipEventRecord(g_rounds_done[dev], st);
+  if (e != hipSuccess) {
+    (void)hipGetLastError();
+    return fail(PG_EDEVICE, "cluster_rounds: %s", hipGetErrorString(e));
+  }
   return PG_OK;
 }
 
+// `done` false: the rounds did not run, and the merges are still to be made.
 static int launch_cluster_rounds(const uint32_t* i0, const uint32_t* i1, const uint32_t* nm,
                                  int64_t m, char* ws, unsigned blocks, pg_merge* merges,
-                                 hipStream_t st) {
+                                 hipStream_t st, bool& done) {
+  done = true;
   const int64_t ld = round_up(m, 16), mp = round_up(m, 32);
   ClRounds p;
   char* at = ws;
@@ -1067,8 +1091,8 @@ static int launch_cluster_rounds(const uint32_t* i0, const uint32_t* i1, const u
   int rc = check_launch("cluster_start");
   mark_stage(1, st);
   if (rc != PG_OK || m < 2) return rc;
-  rc = launch_rounds_kernel(p, blocks, st);
-  if (rc != PG_OK) return rc;
+  rc = launch_rounds_kernel(p, blocks, st, done);
+  if (rc != PG_OK || !done) return rc;
   hipLaunchKernelGGL(k_cl_order, dim3((unsigned)ceil_div(m - 1, 64)), dim3(1024), 0, st, p.found,
                      (int)(m - 1), merges);
   rc = check_launch("cluster_order");
@@ -1080,9 +1104,12 @@ int launch_ibs_cluster(const uint32_t* i0, const uint32_t* i1, const uint32_t* n
                        double* D, double* nn_d, int* nn_j, int* ctl, int* rows,
                        pg_merge* merges, hipStream_t st) {
   unsigned round_blocks;
-  if (cluster_rounds_ok(m, st, round_blocks))
-    return launch_cluster_rounds(i0, i1, nm, m, reinterpret_cast<char*>(D), round_blocks, merges,
-                                 st);
+  if (cluster_rounds_ok(m, st, round_blocks)) {
+    bool done;
+    const int rc = launch_cluster_rounds(i0, i1, nm, m, reinterpret_cast<char*>(D), round_blocks,
+                                         merges, st, done);
+    if (rc != PG_OK || done) return rc;
+  }
   int rc = launch_ibs_distance(i0, i1, nm, m * m, D, st);
   if (rc != PG_OK) return rc;
   const int64_t blocks = ceil_div(m, 4) < 65536 ? ceil_div(m, 4) : 65536;
