@@ -25,7 +25,8 @@ struct GrmIntPlan {
   int64_t blocks32;         // 32-sample blocks of G
   int64_t head;             // tiles run whole; the others in n_split ranges
   int64_t n_split, cps;     //   of cps chunks
-  int64_t off_G, off_tab, off_cnt, off_stat, off_marks, off_top, off_part_s, off_part_n;
+  int64_t off_G, off_tab, off_cnt, off_stat, off_marks, off_panel, off_fine, off_part_s,
+      off_part_n;
   int64_t bytes;
 };
 // Plans the int8 path for m samples and nv variants over the sample-major

@@ -18,9 +18,23 @@
 // extended precision over 100 to 2,500 samples x 1,000 to 40,000 variants:
 // relative error 0.7-2.6e-16, the fp64 kernel's 2.9e-16 to 3.3e-15.
 //
+// Half of 2^-53 is too much for an increment that is small itself: two common
+// homozygotes' is 2p/(1-p), two heterozygotes' (1-2p)^2/(2p(1-p)), and equal
+// markers round alike.  So the markers of a chunk of 64 that holds one with
+// p < 1/256 are rounded to multiples of 2^-77, in three more digits of each
+// factor (a pass over these chunks alone), and those of every chunk where 15
+// of 16 markers have an increment below 1/8 (p < 1/16, or 1 - 2p < 1/8).  The
+// line: sums of equal increments at p of 1/256 to 1/192, relative error at
+// most 6.7e-15 (rms 3.8e-15) here, the fp64 product's 1.2e-14 (rms) over 800
+// to 2,000 markers and 3.7e-15 over 300.  10,000 samples x 1,000 alleles seen
+// once, a pair without one: 3.2e-13 without these digits, 1e-16 with them, the
+// fp64 kernel 6.1e-15.  What they cost: 10,000 x 71,307 at p from 0.0005 to
+// 0.005 56.2 -> 65.0 ms a call, 1,000 x 76,124 1.19 -> 1.35 ms (the fp64 kernel
+// 130 and 1.65); panels without such markers take no more passes.
+//
 // 16 products of 2 operations at the int8 rate replace one fp64 product at
-// 1/64 of it: 10,000 x 71,307 130 -> 42-43.6 ms (pair kernel 41.9), 1,000 x
-// 76,124 1.65 -> 0.81 ms.  The operand is never expanded in memory: the 2-bit codes of 64
+// 1/64 of it: 10,000 x 71,307 130 -> 40.4 ms, 1,000 x 76,124 1.65 -> 0.80 ms.
+// The operand is never expanded in memory: the 2-bit codes of 64
 // markers of a 32-sample block are 512 contiguous bytes (G), rows expand to x
 // and m in registers, and the digits of the block's columns are selected from
 // the markers' tables into LDS once for all its waves.
@@ -37,6 +51,23 @@ constexpr int kGiSeg = 128;                   // rows per counting segment
 constexpr int kGiQuadWords = 20;              // table words per four variants (18 used)
 constexpr int kGiTabWords = 16 * kGiQuadWords;   // table words per chunk and pass
 constexpr int kGiF2Digits = 7;
+constexpr int kGiFineSlot = 4;                // the fine pass's place among the tables
+constexpr int kGiFineDigits = 3;              // digits below 2^-53
+
+// What k_gi_stats finds over all markers.
+struct GiPanel {
+  unsigned long long counts;   // markers with defined increments; << 32 those of
+                               // them with an increment below 1/8
+  uint32_t top;                // largest ceil(n / a)
+};
+// Whether every chunk takes the fine digits, and whether chunk c does.
+__device__ __forceinline__ bool gi_fine_all(const GiPanel& p) {
+  const uint64_t used = p.counts & 0xFFFFFFFFu, coarse = p.counts >> 32;
+  return coarse > 0 && 16 * coarse >= 15 * used;
+}
+__device__ __forceinline__ bool gi_fine(const uint32_t* fine, bool all, int64_t c) {
+  return all || (fine[c >> 5] >> (c & 31) & 1u);
+}
 
 // Digit places of F1 for a panel whose largest n/a (alleles over minor
 // alleles) is at most `top`: |F1| 2^53 < 0.498 * 256^digits.
@@ -51,9 +82,11 @@ __device__ __forceinline__ int gi_digits(uint32_t top) {
 // byte fields.
 __global__ __launch_bounds__(256) void k_gi_counts(const uint32_t* __restrict__ T, int64_t wp,
                                                    uint32_t* __restrict__ cnt,
-                                                   uint32_t* __restrict__ top) {
+                                                   GiPanel* __restrict__ panel,
+                                                   uint32_t* __restrict__ fine) {
   const int64_t w = (int64_t)blockIdx.x * 256 + threadIdx.x, seg = blockIdx.y;
-  if (w == 0 && seg == 0) *top = 0u;
+  if (w == 0 && seg == 0) *panel = GiPanel{0ull, 0u};
+  if (seg == 0 && w < ceil_div(wp / 4, 32)) fine[w] = 0u;
   if (w >= wp) return;
   const uint32_t* src = T + seg * kGiSeg * wp + w;
   uint32_t c8[3][4] = {};
@@ -93,11 +126,13 @@ __global__ __launch_bounds__(256) void k_gi_counts(const uint32_t* __restrict__ 
 
 // Per variant: {alleles n = 2 calls, minor alleles a}, a = 0 for an undefined
 // marker; per 16 variants a word with the undefined ones in the low half and
-// those whose minor allele is A1 in the high half; the largest ceil(n / a).
+// those whose minor allele is A1 in the high half; the panel's figures; and a
+// bit per chunk (a wave's variants) that holds a rare allele.
 __global__ __launch_bounds__(256) void k_gi_stats(const uint32_t* __restrict__ cnt, int64_t nv_pad,
                                                   int segs, uint2* __restrict__ stat,
                                                   uint32_t* __restrict__ marks,
-                                                  uint32_t* __restrict__ top) {
+                                                  GiPanel* __restrict__ panel,
+                                                  uint32_t* __restrict__ fine) {
   const int64_t v = (int64_t)blockIdx.x * 256 + threadIdx.x;
   const bool in = v < nv_pad;
   uint32_t calls = 0, het = 0, h2 = 0;
@@ -121,27 +156,41 @@ __global__ __launch_bounds__(256) void k_gi_stats(const uint32_t* __restrict__ c
     const uint32_t o = __shfl_xor(r, d, 64);
     r = o > r ? o : r;
   }
-  // few waves raise it: most see a larger one and leave it
-  if (lane == 0 && r > __hip_atomic_load(top, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
-    atomicMax(top, r);
+  const uint64_t rare = __ballot(used && 256 * a < n);
+  const uint64_t coarse = __ballot(used && (16 * a < n || (2 * a < n && 8 * (n - 2 * a) < n)));
+  __shared__ uint32_t s_n[2];
+  if (threadIdx.x < 2) s_n[threadIdx.x] = 0u;
+  __syncthreads();
+  if (lane == 0) {
+    // few waves raise it: most see a larger one and leave it
+    if (r > __hip_atomic_load(&panel->top, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
+      atomicMax(&panel->top, r);
+    if (rare) atomicOr(&fine[v >> 11], 1u << (v >> 6 & 31));
+    atomicAdd(&s_n[0], (uint32_t)__popcll(~undef));
+    atomicAdd(&s_n[1], (uint32_t)__popcll(coarse));
+  }
+  __syncthreads();
+  // one addition per block: additions to one word queue up
+  if (threadIdx.x == 0) atomicAdd(&panel->counts, (unsigned long long)s_n[1] << 32 | s_n[0]);
 }
 
 // ---- digit tables --------------------------------------------------------------
-// num / den (den < 2^63) times 2^53, rounded to nearest, as a 128-bit
-// two's complement pair, negated if `neg`.
-__device__ __forceinline__ void gi_fixed(uint64_t num, uint64_t den, bool neg, uint64_t& lo,
-                                         uint64_t& hi) {
-  uint64_t q = num / den, r = num % den, f = 0;
-  for (int b = 0; b < 53; ++b) {
+// num / den (den < 2^63, num / den < 2^22) times 2^bits, rounded to nearest, as
+// a 128-bit two's complement pair, negated if `neg`.
+__device__ __forceinline__ void gi_fixed(uint64_t num, uint64_t den, int bits, bool neg,
+                                         uint64_t& lo, uint64_t& hi) {
+  uint64_t r = num % den;
+  lo = num / den;
+  hi = 0;
+  for (int b = 0; b < bits; ++b) {
     r <<= 1;
-    f <<= 1;
+    hi = hi << 1 | lo >> 63;
+    lo <<= 1;
     if (r >= den) {
       r -= den;
-      f |= 1;
+      lo |= 1;
     }
   }
-  lo = q << 53 | f;
-  hi = q >> 11;
   if ((r << 1) >= den) {
     ++lo;
     if (lo == 0) ++hi;
@@ -167,9 +216,11 @@ __device__ __forceinline__ int gi_digit(uint64_t& lo, uint64_t& hi) {
 // for a column call of class x = 0, 1, 2.  Pass t holds the digit places
 // 3t .. 3t + 2: planes 0-2 those of F1 (rows enter with x), 3-5 those of F2
 // (rows enter with m), where the place after F1's last holds the count of
-// pairs (1 in every class).
+// pairs (1 in every class).  Pass kGiFineSlot holds the three places below
+// 2^-53 of the chunks that take them.
 __global__ __launch_bounds__(256) void k_gi_tables(const uint2* __restrict__ stat, int64_t nch,
-                                                   const uint32_t* __restrict__ top,
+                                                   const GiPanel* __restrict__ panel,
+                                                   const uint32_t* __restrict__ fine,
                                                    uint32_t* __restrict__ tab) {
   const int64_t id = (int64_t)blockIdx.x * 256 + threadIdx.x;
   // four neighbouring lanes hold the four variants of a quad; a row of blocks
@@ -179,18 +230,19 @@ __global__ __launch_bounds__(256) void k_gi_tables(const uint2* __restrict__ sta
   if (c >= nch) return;
   const uint2 s = stat[c * kGiChunk + 16 * (quad >> 2) + 4 * b + (quad & 3)];
   const uint64_t n = s.x, a = s.y;
-  const int n1 = gi_digits(*top), passes = (n1 + 3) / 3;
+  const int n1 = gi_digits(panel->top), passes = (n1 + 3) / 3;
+  const bool more = gi_fine(fine, gi_fine_all(*panel), c);   // the same for the wave's chunk
   uint64_t lo = 0, hi = 0;
   if (a) {
     const uint64_t z = n - a, h = n - 2 * a;      // a <= n / 2
     const uint64_t num = k == 1 ? n * h : k == 3 ? 2 * a : k == 4 ? h : k == 5 ? 2 : n;
     const uint64_t den = k == 1 ? 2 * a * z : k == 2 ? a : k == 5 ? 1 : z;
     // F1: -1/(1-p), (1-2p)/(2p(1-p)), 1/p; F2: 2p/(1-p), -(1-2p)/(1-p), -2
-    gi_fixed(num, den, k == 0 || k >= 4, lo, hi);
+    gi_fixed(num, den, more ? 53 + 8 * kGiFineDigits : 53, k == 0 || k >= 4, lo, hi);
   }
   const int digits = k < 3 ? n1 : kGiF2Digits;
-  for (int t = 0; t < passes; ++t) {
-    uint32_t* out = tab + ((t * nch + c) * 16 + quad) * kGiQuadWords;
+  for (int t = more ? -1 : 0; t < passes; ++t) {
+    uint32_t* out = tab + (((t < 0 ? kGiFineSlot : t) * nch + c) * 16 + quad) * kGiQuadWords;
 #pragma unroll
     for (int q = 0; q < 3; ++q) {
       const int place = 3 * t + q;
@@ -307,15 +359,15 @@ __device__ __forceinline__ void gi_store(const GiOut& o, int64_t i, int64_t j, d
 
 // One pass's share S of entry (i, j), `n` its count with the last pass: parked
 // in the outputs (or the range's partial sums) until then.
-__device__ __forceinline__ void gi_put(const GiOut& o, int t, bool end, int64_t park, int64_t i,
-                                       int64_t j, double S, uint32_t n) {
+__device__ __forceinline__ void gi_put(const GiOut& o, bool begin, bool end, int64_t park,
+                                       int64_t i, int64_t j, double S, uint32_t n) {
   if (park >= 0) {
-    if (t) S += o.part_s[park];
+    if (!begin) S += o.part_s[park];
     o.part_s[park] = S;
     if (end) o.part_n[park] = n;
   } else if (j < o.m && i <= j && (o.full || i < j)) {
     double* at = o.full ? &o.grm[i * o.m + j] : &o.grm[i * o.m - i * (i + 1) / 2 + (j - i - 1)];
-    if (t) S += *at;
+    if (!begin) S += *at;
     if (end)
       gi_store(o, i, j, S, n);
     else
@@ -356,11 +408,27 @@ __device__ __forceinline__ void gi_to_lds(const uint32_t* src, uint32_t* dst) {
       (__attribute__((address_space(3))) void*)dst, 16, 0, 0);
 }
 
-template <int NR, int kPlanes>
+// The first chunk from c on that has its bit in `fine` set, c_end if none.
+__device__ __forceinline__ int gi_next(const uint32_t* __restrict__ fine, int c, int c_end) {
+  while (c < c_end) {
+    const uint32_t w = fine[c >> 5] >> (c & 31);
+    if (w) {
+      c += __builtin_ctz(w);
+      break;
+    }
+    c = (c | 31) + 1;
+  }
+  return c < c_end ? c : c_end;
+}
+
+// Chunks [c_begin, c_end), or (kListed, fine not NULL) those of them with a bit
+// in `fine`, at least one.
+template <int NR, int kPlanes, bool kListed>
 __device__ __forceinline__ void gi_pass(const uint32_t* __restrict__ G,
                                         const uint32_t* __restrict__ tab, int64_t nch, int64_t I,
                                         int64_t J, int c_begin, int c_end, GiLds<NR>& s,
-                                        v16i_t (&acc)[3][4]) {
+                                        v16i_t (&acc)[3][4],
+                                        const uint32_t* __restrict__ fine) {
   constexpr int kStrips = 4 / NR;
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -420,22 +488,28 @@ __device__ __forceinline__ void gi_pass(const uint32_t* __restrict__ G,
       }
   };
 
-  const int last = c_end - 1;
-  auto upto = [&](int c) { return c < last ? c : last; };
-  load_stage(c_begin, 0);
-  load_rows(c_begin, 0);
-  load_stage(upto(c_begin + 1), 1);
-  load_stage(upto(c_begin + 2), 2);
-  load_rows(upto(c_begin + 1), 1);
+  // the chunks after c, the last one again past the end
+  auto after = [&](int c) {
+    const int n = kListed && fine ? gi_next(fine, c + 1, c_end) : c + 1;
+    return n < c_end ? n : c;
+  };
+  int c = kListed && fine ? gi_next(fine, c_begin, c_end) : c_begin;
+  int c1 = after(c), c2 = after(c1);
+  load_stage(c, 0);
+  load_rows(c, 0);
+  load_stage(c1, 1);
+  load_stage(c2, 2);
+  load_rows(c1, 1);
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
   __syncthreads();
   generate(0, 0);
   __syncthreads();
-  int b0 = 0, b1 = 1, b2 = 2;   // buffers of chunks c, c + 1, c + 2
-  for (int c = c_begin; c < c_end; ++c) {
-    const int buf = (c - c_begin) & 1;
-    load_rows(upto(c + 2), b2);
-    load_stage(upto(c + 3), b0);   // chunk c's were used a chunk ago
+  int b0 = 0, b1 = 1, b2 = 2;   // buffers of chunks c, c1, c2
+  int buf = 0;
+  while (true) {
+    const int c3 = after(c2);
+    load_rows(c2, b2);
+    load_stage(c3, b0);   // chunk c's were used a chunk ago
 #pragma unroll
     for (int h = 0; h < 2; ++h) {
       v4i_t dig[6];
@@ -461,12 +535,17 @@ __device__ __forceinline__ void gi_pass(const uint32_t* __restrict__ G,
       }
     }
     generate(b1, buf ^ 1);
-    // rows of chunk c + 1 and tables of c + 2 have arrived
+    // rows of the next chunk and tables of the one after have arrived
     asm volatile("s_waitcnt vmcnt(3) lgkmcnt(0)\n\ts_barrier" ::: "memory");
     const int b = b0;
     b0 = b1;
     b1 = b2;
     b2 = b;
+    if (c1 == c) break;
+    c = c1;
+    c1 = c2;
+    c2 = c3;
+    buf ^= 1;
   }
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
 }
@@ -474,8 +553,9 @@ __device__ __forceinline__ void gi_pass(const uint32_t* __restrict__ G,
 template <int NR>
 __global__ __launch_bounds__(256, 2) void k_gi_pairs(const uint32_t* __restrict__ G,
                                                      const uint32_t* __restrict__ tab,
-                                                     const uint32_t* __restrict__ top, int64_t nch,
-                                                     GiOut o) {
+                                                     const GiPanel* __restrict__ panel,
+                                                     const uint32_t* __restrict__ fine,
+                                                     int64_t nch, GiOut o) {
   // the operands, or the sums on their way out (12 KB per wave)
   __shared__ __align__(16) union {
     GiLds<NR> in;
@@ -488,23 +568,27 @@ __global__ __launch_bounds__(256, 2) void k_gi_pairs(const uint32_t* __restrict_
   const int64_t split = whole ? 0 : tail_item / o.tail;
   int64_t I, J;
   gi_tile<NR>(tile, o.nj, I, J);
-  const int n1 = gi_digits(*top), passes = (n1 + 3) / 3;
+  const int n1 = gi_digits(panel->top), passes = (n1 + 3) / 3;
   const int c_begin = whole ? 0 : (int)(split * o.cps);
   const int c_end = whole || (split + 1) * o.cps > nch ? (int)nch : (int)((split + 1) * o.cps);
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int rb = (wave % NR) * 128 + 4 * (lane >> 5), cb = (wave / NR) * 32 + (lane & 31);
-  for (int t = 0; t < passes; ++t) {
+  // pass -1 takes the three places below 2^-53
+  const bool all = gi_fine_all(*panel);
+  const int t0 = all || gi_next(fine, c_begin, c_end) < c_end ? -1 : 0;
+  for (int t = t0; t < passes; ++t) {
     v16i_t acc[3][4];
 #pragma unroll
     for (int q = 0; q < 3; ++q)
 #pragma unroll
       for (int a = 0; a < 4; ++a) acc[q][a] = (v16i_t){0};
-    const uint32_t* tt = tab + (int64_t)t * nch * kGiTabWords;
+    const uint32_t* tt = tab + (int64_t)(t < 0 ? kGiFineSlot : t) * nch * kGiTabWords;
     // the last of the usual eight places: F1 and F2 at 6, F1 at 7, the count
     if (n1 == 8 && t == 2)
-      gi_pass<NR, 0x2B>(G, tt, nch, I, J, c_begin, c_end, s.in, acc);
+      gi_pass<NR, 0x2B, false>(G, tt, nch, I, J, c_begin, c_end, s.in, acc, nullptr);
     else
-      gi_pass<NR, 0x3F>(G, tt, nch, I, J, c_begin, c_end, s.in, acc);
+      gi_pass<NR, 0x3F, true>(G, tt, nch, I, J, c_begin, c_end, s.in, acc,
+                              t < 0 && !all ? fine : nullptr);
     // the places' sum is below 2^48 in magnitude: exact in double; the
     // passes before are read back from where they were parked
     const int count_at = n1 - 3 * t;
@@ -539,7 +623,7 @@ __global__ __launch_bounds__(256, 2) void k_gi_pairs(const uint32_t* __restrict_
         for (int r = 0; r < 4; ++r) {
           const double S = s0 * (double)x0[r] + s1 * (double)x1[r] + s2 * (double)x2[r];
           const int n = count_at == 0 ? x0[r] : count_at == 1 ? x1[r] : x2[r];
-          gi_put(o, t, end, park + (int64_t)(il + r) * (128 / NR), I * 128 * NR + il + r, j, S,
+          gi_put(o, t == t0, end, park + (int64_t)(il + r) * (128 / NR), I * 128 * NR + il + r, j, S,
                  (uint32_t)n);
         }
       }
@@ -631,11 +715,12 @@ bool grm_int_plan(int64_t m, int64_t nv, int64_t rows_pad, int64_t wp, int64_t b
   };
   // column strips reach past the last row tile only within its rows
   p.off_G = take(p.blocks32 * p.nch * kGiBlockWords * 4);
-  p.off_tab = take(4 * p.nch * kGiTabWords * 4);
+  p.off_tab = take((kGiFineSlot + 1) * p.nch * kGiTabWords * 4);
   p.off_cnt = take(ceil_div(rows_pad, kGiSeg) * wp * 16 * 4);
   p.off_stat = take(wp * 16 * 8);
   p.off_marks = take(wp * 4);
-  p.off_top = take(4);
+  p.off_panel = take(sizeof(GiPanel));
+  p.off_fine = take(ceil_div(p.nch, 32) * 4);
   p.off_part_s = take(parts * 16384 * 8);
   p.off_part_n = take(parts * 16384 * 4);
   p.bytes = at;
@@ -648,7 +733,8 @@ int gi_launch_pairs(const GrmIntPlan& p, char* ws, const GiOut& o, hipStream_t s
   hipLaunchKernelGGL((k_gi_pairs<NR>), dim3((unsigned)(o.head + o.tail * o.n_split)),
                      dim3(256), 0, st,
                      (const uint32_t*)(ws + p.off_G), (const uint32_t*)(ws + p.off_tab),
-                     (const uint32_t*)(ws + p.off_top), p.nch, o);
+                     (const GiPanel*)(ws + p.off_panel), (const uint32_t*)(ws + p.off_fine),
+                     p.nch, o);
   int rc = check_launch("grm_int_pairs");
   if (rc == PG_OK && p.n_split > 1) {
     const int64_t blocks = o.tail * 64;
@@ -665,18 +751,19 @@ int launch_grm_int(const GrmIntPlan& p, char* ws, const uint32_t* T, int64_t m, 
   uint32_t* cnt = (uint32_t*)(ws + p.off_cnt);
   uint2* stat = (uint2*)(ws + p.off_stat);
   uint32_t* marks = (uint32_t*)(ws + p.off_marks);
-  uint32_t* top = (uint32_t*)(ws + p.off_top);
+  GiPanel* panel = (GiPanel*)(ws + p.off_panel);
+  uint32_t* fine = (uint32_t*)(ws + p.off_fine);
   const int64_t segs = rows_pad / kGiSeg, nv_pad = wp * 16;
   hipLaunchKernelGGL(k_gi_counts, dim3((unsigned)ceil_div(wp, 256), (unsigned)segs), dim3(256), 0,
-                     st, T, wp, cnt, top);
+                     st, T, wp, cnt, panel, fine);
   int rc = check_launch("grm_int_counts");
   if (rc != PG_OK) return rc;
   hipLaunchKernelGGL(k_gi_stats, dim3((unsigned)ceil_div(nv_pad, 256)), dim3(256), 0, st, cnt,
-                     nv_pad, (int)segs, stat, marks, top);
+                     nv_pad, (int)segs, stat, marks, panel, fine);
   rc = check_launch("grm_int_stats");
   if (rc != PG_OK) return rc;
   hipLaunchKernelGGL(k_gi_tables, dim3((unsigned)ceil_div(nv_pad, 256), 6), dim3(256), 0, st, stat,
-                     p.nch, top, (uint32_t*)(ws + p.off_tab));
+                     p.nch, panel, fine, (uint32_t*)(ws + p.off_tab));
   rc = check_launch("grm_int_tables");
   if (rc != PG_OK) return rc;
   hipLaunchKernelGGL(k_gi_operand, dim3((unsigned)ceil_div(wp, 64), (unsigned)p.blocks32),
