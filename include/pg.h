@@ -129,7 +129,7 @@ enum pg_path {
                        0, +-1) and contracted on the matrix cores.  Default
                        kernels (variant 0): fp4 (e2m1) operands with fp32
                        sums while those are exact; beyond that (IBS: 2^24
-                       variants, LD: 2^24 / 9 samples) int8 operands with
+                       variants, LD: 2^24 samples) int8 operands with
                        int32 sums.  IBS variants: 1 int8 without
                        scheduling hints, 2 unpipelined reference, 3 fp4
                        unpipelined, 4 fp4 from a replicated operand, 5/6
@@ -240,7 +240,11 @@ typedef struct pg_ld_pair {
   double r2;
 } pg_ld_pair;
 
-/* Workspace bytes pg_ld_window needs for this shape, window and path. */
+/* Workspace bytes pg_ld_window needs for this shape, window and path: the 2-bit
+ * operand, on the fp4 kernels up to 16 GiB of it also its calls as nibbles (two
+ * more bytes per byte; larger panels expand the 2-bit words in the kernel), the
+ * emission scratch, and for PG_PATH_SPARSE the sample-major operand and the
+ * missing-call lists. */
 int pg_ld_workspace_bytes(const pg_genotypes* g, int64_t n_sel, int64_t v_begin, int64_t v_end,
                           int32_t window, int path, size_t* bytes);
 

@@ -214,7 +214,7 @@ int plan_ld(const Sel& s, int32_t window, int path_arg, LdPlan& p) {
     return fail(PG_EINVAL, "unknown path %d", path);
   p.path = path;
   // matrix-core kernel: fp4 by default, int8 as variant 1 or beyond 2^24
-  // samples (from kLdFp4MaxSamples on the default runs the int8 tile too)
+  // samples
   if (path == PG_PATH_MFMA && (p.variant != kLdVariantInt8 && s.m < kFp4MaxVariants))
     p.variant = kLdVariantFp4;
   else if (path == PG_PATH_MFMA)
@@ -231,9 +231,9 @@ int plan_ld(const Sel& s, int32_t window, int path_arg, LdPlan& p) {
   }
   Carve c;
   p.off_D = c.take(operand_bytes);
-  const bool fp4 = s.m < kLdFp4MaxSamples &&
+  const bool nibbles = ld_takes_nibbles(s.m, operand_bytes) &&
       (path == PG_PATH_SPARSE || (path == PG_PATH_MFMA && p.variant == kLdVariantFp4));
-  p.off_E = fp4 ? c.take(2 * operand_bytes) : -1;
+  p.off_E = nibbles ? c.take(2 * operand_bytes) : -1;
   p.off_part = path == PG_PATH_POPC
                    ? -1 : c.take(p.rows_pad * ceil_div(p.words, kLdCountWords) * 4);
   p.off_bm = c.take(p.rows_pad * p.bm_words * 4);
@@ -301,7 +301,8 @@ int ld_pairs(const Sel& s, const LdPlan& p, char* ws, int32_t window, double r2_
       rc = launch_ld_totals(cn, p.words, s.m, s.nv, p.rows_pad, stats, nullptr, st);
     mark_stage(1, st);
     if (rc != PG_OK) return rc;
-    return launch_ld_mfma(D, E, p.words, s.nv, p.rows_pad, window, r2_min, sc, st);
+    return launch_ld_mfma(D, E, p.variant == kLdVariantFp4, p.words, s.nv, p.rows_pad, window,
+                          r2_min, sc, st);
   }
   LdSparse sp{(uint32_t*)(ws + p.off_lists), (int4*)(ws + p.off_vst), (int64_t*)(ws + p.off_gsum),
               (int*)(ws + p.off_gmax), (uint32_t*)(ws + p.off_any), ld_sparse_min_groups(p),

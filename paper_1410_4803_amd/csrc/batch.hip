@@ -35,7 +35,7 @@ struct BatchItem {
   int64_t tile_begin;    // first global tile index
   int64_t ntiles;
   const uint32_t* X;     // operand layout in the workspace
-  const uint32_t* E;     // LD: nibble operand of the fp4 tile (NULL: the int8 tile)
+  const uint32_t* E;     // LD: nibble operand of the fp4 tile (NULL: the tiles on X)
   int64_t words;         // K words of the operand
   int64_t rows_pad;
   int64_t nt;            // IBS: tiles per side; LD: row tiles
@@ -126,6 +126,9 @@ __global__ __launch_bounds__(256, kPart == kPartIbs ? 1 : 2) void k_batch_persis
           if (it.E)
             ld_nib_tile(it.E, it.words / 4, it.nv, I, J, it.window, it.r2_min, it.sc,
                         (lds_t*)smem);
+          else if (it.variant == kLdVariantFp4)
+            ld_fp4_tile_pipe(it.X, it.words, it.nv, I, J, it.window, it.r2_min, it.sc,
+                             (lds_t*)smem);
           else
             ld_mfma_tile(it.X, it.words, it.nv, I, J, it.window, it.r2_min, it.sc, (lds_t*)smem);
         } else {
@@ -223,7 +226,7 @@ int pg_batch_plan(const pg_problem* probs, int n_probs, pg_plan** out) {
   if (!probs || n_probs < 1) return fail(PG_EINVAL, "no problems");
   pg_plan* plan = new (std::nothrow) pg_plan;
   if (!plan) return fail(PG_EINVAL, "host allocation failed");
-  int64_t off = 0;
+  int64_t off = 0, nibble_bytes = 0;
   for (int i = 0; i < n_probs; ++i) {
     ProblemPlan q{};
     q.p = probs[i];
@@ -262,10 +265,12 @@ int pg_batch_plan(const pg_problem* probs, int n_probs, pg_plan** out) {
         const int64_t bytes = q.path == PG_PATH_MFMA ? q.rows_pad * q.words * 4
                                                      : 3 * q.rows_pad * q.words * 4;
         q.off_x = take(off, bytes);
-        q.off_e = q.path == PG_PATH_MFMA && q.variant == kLdVariantFp4 &&
-                          q.s.m < kLdFp4MaxSamples
-                      ? take(off, 2 * bytes)
-                      : -1;
+        q.off_e = -1;
+        if (q.path == PG_PATH_MFMA && q.variant == kLdVariantFp4 &&
+            ld_takes_nibbles(q.s.m, bytes) && nibble_bytes + 2 * bytes <= kLdNibbleMaxBytes) {
+          q.off_e = take(off, 2 * bytes);
+          nibble_bytes += 2 * bytes;
+        }
         q.off_bm = take(off, q.rows_pad * q.bm_words * 4);
         q.off_cnt = take(off, q.rows_pad * 4);
         q.off_off = take(off, (q.rows_pad + 1) * 8);

@@ -64,7 +64,9 @@ int launch_ld_popc(const uint32_t* P, int64_t words_pad, int64_t nv, int64_t row
   return rc;
 }
 
-template <bool kFp4>
+constexpr int kLdTileNib = 0, kLdTileFp4 = 1, kLdTileInt8 = 2;
+
+template <int kTile>
 __global__ __launch_bounds__(256, 2) void k_ld_mfma(const uint32_t* __restrict__ D, int64_t wn,
                                                     int64_t nv, int64_t n_row_tiles, int64_t n_band,
                                                     int32_t window, double r2_min, LdScratch sc,
@@ -81,21 +83,24 @@ __global__ __launch_bounds__(256, 2) void k_ld_mfma(const uint32_t* __restrict__
   if (J >= n_row_tiles) return;
   if (gsum && ld_tile_sparse(gsum, gmax, groups_ok, min_groups, I, J, cap, budget))
     return;   // the correction path's
-  if constexpr (kFp4)   // the operand is E
+  if constexpr (kTile == kLdTileNib)   // the operand is E
     ld_nib_tile(D, wn / 4, nv, I, J, window, r2_min, sc, (lds_t*)smem);
+  else if constexpr (kTile == kLdTileFp4)
+    ld_fp4_tile_pipe(D, wn, nv, I, J, window, r2_min, sc, (lds_t*)smem);
   else
     ld_mfma_tile(D, wn, nv, I, J, window, r2_min, sc, (lds_t*)smem);
 }
 
-int launch_ld_mfma(const uint32_t* D, const uint32_t* E, int64_t wn, int64_t nv, int64_t rows_pad,
-                   int32_t window, double r2_min, const LdScratch& sc, hipStream_t st,
-                   const LdSparse* sp) {
+int launch_ld_mfma(const uint32_t* D, const uint32_t* E, bool fp4, int64_t wn, int64_t nv,
+                   int64_t rows_pad, int32_t window, double r2_min, const LdScratch& sc,
+                   hipStream_t st, const LdSparse* sp) {
   int rc;
   const int64_t n_row_tiles = rows_pad / kL;
   const int64_t n_band = ((int64_t)window + kL - 1) / kL + 1;
   const int64_t blocks = n_row_tiles * n_band;
-  hipLaunchKernelGGL(E ? k_ld_mfma<true> : k_ld_mfma<false>, dim3((unsigned)blocks), dim3(256),
-                     0, st, E ? E : D, wn, nv, n_row_tiles,
+  hipLaunchKernelGGL((E ? k_ld_mfma<kLdTileNib>
+                        : fp4 ? k_ld_mfma<kLdTileFp4> : k_ld_mfma<kLdTileInt8>),
+                     dim3((unsigned)blocks), dim3(256), 0, st, E ? E : D, wn, nv, n_row_tiles,
                      n_band, window, r2_min, sc, sp ? sp->gsum : nullptr,
                      sp ? sp->gmax : nullptr, sp ? sp->groups_ok : nullptr,
                      sp ? sp->min_groups : 0u, sp ? sp->cap : 0, sp ? sp->budget : 0);

@@ -725,7 +725,7 @@ int launch_ld_sparse(const uint32_t* D, const uint32_t* E, int64_t wn, const uin
   int rc;
   // the dense kernel takes the tiles this path leaves
   if (!dbg) {
-    rc = launch_ld_mfma(D, E, wn, nv, rows_pad, window, r2_min, sc, st, &sp);
+    rc = launch_ld_mfma(D, E, m < kFp4MaxVariants, wn, nv, rows_pad, window, r2_min, sc, st, &sp);
     if (rc != PG_OK) return rc;
   }
   const int64_t n_row_tiles = rows_pad / kLdTile;

@@ -331,14 +331,25 @@ int ld_clear(const LdScratch& sc, int64_t rows_pad, hipStream_t st);
 // Most selected samples whose sums the fp4 LD tile forms exactly (its
 // products are up to nine quarters).
 constexpr int64_t kLdFp4MaxSamples = ((int64_t)1 << 24) / 9;
+// Most bytes of nibble operand a call (or all problems of a batch) lays out, a
+// ninth of the card: with it a call takes six times its panel's bytes at the
+// largest, panel included, without it four, and the tiles that work on D alone
+// are 12% slower (5.9 and 5.2 ms at 5,000 x 500,000, window 1,000).
+// Panels from 16 GiB on keep the smaller footprint: a chromosome of 61 GB takes
+// 244 GB of 288.
+constexpr int64_t kLdNibbleMaxBytes = (int64_t)32 << 30;
+// Whether E goes with an operand D of `bytes` over m samples.
+inline bool ld_takes_nibbles(int64_t m, int64_t bytes) {
+  return m < kLdFp4MaxSamples && 2 * bytes <= kLdNibbleMaxBytes;
+}
 // Dense pair kernel over the band; with `sp`, tiles the correction path
 // takes are skipped (and stage 2 is left to that path).  With E the fp4 tile
-// on it, else (NULL) the int8 tile on D.
-int launch_ld_mfma(const uint32_t* D, const uint32_t* E, int64_t wn, int64_t nv, int64_t rows_pad, int32_t window,
-                   double r2_min, const LdScratch& sc, hipStream_t st,
-                   const LdSparse* sp = nullptr);
-// Kernel variants of the LD matrix-core path: 0 (default) the fp4 tile (from
-// kLdFp4MaxSamples samples on its int8 twin), or the int8 tile (1).
+// on it, else (NULL) the fp4 tile on D, or its int8 twin.
+int launch_ld_mfma(const uint32_t* D, const uint32_t* E, bool fp4, int64_t wn, int64_t nv,
+                   int64_t rows_pad, int32_t window, double r2_min, const LdScratch& sc,
+                   hipStream_t st, const LdSparse* sp = nullptr);
+// Kernel variants of the LD matrix-core path: 0 (default) an fp4 tile, 1 the
+// int8 tile (also the default from 2^24 samples on).
 constexpr int kLdVariantFp4 = 0;
 constexpr int kLdVariantInt8 = 1;
 // Per variant, from the layout's partial counts: the allele counts for pruning
@@ -362,8 +373,9 @@ int launch_ld_transpose(const uint32_t* D, int64_t rows_pad, int64_t wn, uint32_
 // the dense kernel is not run and each pair of a correction tile writes its
 // record to dbg[a * window + (b - a - 1)] (a, b local; the record holds
 // v0 + a, v0 + b) instead of the emission test.
-int launch_ld_sparse(const uint32_t* D, const uint32_t* E, int64_t wn, const uint32_t* T, int64_t t_rows, int64_t m,
-                     int64_t nv, int64_t rows_pad, int32_t window, double r2_min,
+int launch_ld_sparse(const uint32_t* D, const uint32_t* E, int64_t wn, const uint32_t* T,
+                     int64_t t_rows, int64_t m, int64_t nv, int64_t rows_pad, int32_t window,
+                     double r2_min,
                      const LdScratch& sc, const LdSparse& sp, hipStream_t st,
                      pg_ld_pair* dbg = nullptr, int64_t v0 = 0);
 int launch_ld_popc(const uint32_t* P, int64_t words_pad, int64_t nv, int64_t rows_pad,
