@@ -334,10 +334,10 @@ int pg_ld_prune(const pg_genotypes* g, const int32_t* sample_idx, int64_t n_sel,
  */
 
 /* Workspace bytes pg_grm_matrix needs for this shape: the operand (twice for
- * the int8 path), the per-marker tables, and the partial sums and counts of
- * the variant ranges that tiles are split into (196,608 bytes per tile of
- * 16,384 pairs and range): every tile on cohorts of fewer than 512, else, on
- * the int8 path, those of the last round of 512. */
+ * the int8 path, which takes panels up to about 28 GiB), the per-marker tables,
+ * and the partial sums and counts of the variant ranges that tiles are split
+ * into (196,608 bytes per tile of 16,384 pairs and range): every tile on cohorts
+ * of fewer than 512, else, on the int8 path, those of the last round of 512. */
 int pg_grm_workspace_bytes(const pg_genotypes* g, int64_t n_sel, int64_t v_begin,
                            int64_t v_end, size_t* bytes);
 

@@ -18,6 +18,11 @@ namespace pg {
 constexpr double kGrmIntMinWork = 8e9;
 constexpr int64_t kGrmIntLong = 32768;
 constexpr int64_t kGrmIntSmall = 1024, kGrmIntShortMin = 800, kGrmIntShortMax = 8192;
+// Its scratch beyond T: at most a ninth of the card, and the whole call (panel,
+// T, scratch, full results) at most 224 GiB of 268; the fp64 kernel, which
+// needs next to nothing beyond T, takes larger ones (100,000 samples x 3,000,000
+// variants: 270 GB there, 355 GB here).
+constexpr int64_t kGrmIntMaxBytes = (int64_t)32 << 30, kGrmIntMaxCall = (int64_t)224 << 30;
 
 struct GrmIntPlan {
   int64_t nch;              // chunks of 64 variants

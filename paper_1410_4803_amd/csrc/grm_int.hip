@@ -724,7 +724,8 @@ bool grm_int_plan(int64_t m, int64_t nv, int64_t rows_pad, int64_t wp, int64_t b
   p.off_part_s = take(parts * 16384 * 8);
   p.off_part_n = take(parts * 16384 * 4);
   p.bytes = at;
-  return true;
+  return p.bytes - base <= kGrmIntMaxBytes &&
+         p.bytes + nv * ceil_div(m, 4) + 12 * m * m <= kGrmIntMaxCall;
 }
 
 namespace {
