@@ -421,7 +421,7 @@ int64_t prune_cells_padded(int64_t nv, int64_t window, int64_t step) {
 // pairs that stay undecided, in three buffers taken in turn (this round's,
 // the next one's, the one cleared meanwhile).  Once at most kPFew pairs are
 // left, one block finishes with them in registers; if that point is not
-// reached in kPRounds rounds, that block finds a long chain, or the list
+// reached in the rounds launched, that block finds a long chain, or the list
 // overflows, the sequential kernels run instead (they return at once
 // otherwise).
 // Bound: launch latency (under 2 us a round, most of them empty).  Greedy pass
@@ -435,7 +435,18 @@ constexpr int kPRounds = 26;
 constexpr int kPFew = 8192;
 constexpr int kPTurns = 16;                // the last block gives up on a list that loses
                                            // less than an eighth in this many rounds
-constexpr int64_t kPRoundsMinPasses = 4;   // below: the sequential kernel is as fast
+// The launches: as many as a full list that keeps 7/8 of its pairs per round
+// takes to come down to kPFew (14 at 6,600 variants and window 50, 21 at 16,000,
+// 26 from 30,000 or from 6,600 at window 200).  The rounds take over from four
+// passes of the sequential kernel on; us a call, sequential / rounds, window 50,
+// step 5, 6,600 and 16,000 variants (5 and 10 passes):
+//   8 founders, t = 0.5  165 / 138,  329 / 133;  t = 0.2  634 / 288,  1448 / 350
+//   20 founders, t = 0.5 (2% dropped)  77 / 93,  131 / 116
+//   hardly a pair above t  51 / 88,  76 / 107;  window 200, 8,000 and 16,000
+//   variants  65 / 126,  94 / 128
+// (the last are the launches, which such a call mostly consists of; below four
+// passes the sequential kernel is as fast on every panel).
+constexpr int64_t kPRoundsMinPasses = 4;
 constexpr int kPBuildWords = 8;            // bitmap words per thread of the build
 constexpr uint32_t kPDropA = 1u << 17, kPDecided = 1u << 18;
 
@@ -449,6 +460,7 @@ struct PruneRounds {
   uint32_t* settled;          // T is final
   unsigned long long* kept;   // caller's count (NULL: none)
   int64_t nv, W, S;
+  int rounds;                 // launches of k_prune_round, at most kPRounds
 };
 
 __device__ __forceinline__ unsigned long long prune_key(const PruneRounds& p, int64_t a, int64_t b,
@@ -596,8 +608,8 @@ __global__ __launch_bounds__(256) void k_prune_round(PruneRounds p, int r) {
 // The last pairs, in one block: eight per thread.
 __global__ __launch_bounds__(1024) void k_prune_finish(PruneRounds p) {
   int r = 0;
-  while (r <= kPRounds && p.left[r] > (unsigned long long)kPFew) ++r;
-  if (r > kPRounds || (int64_t)p.left[0] > p.cap) return;      // not settled
+  while (r <= p.rounds && p.left[r] > (unsigned long long)kPFew) ++r;
+  if (r > p.rounds || (int64_t)p.left[0] > p.cap) return;      // not settled
   const uint32_t n = (uint32_t)p.left[r];
   unsigned long long* M = p.M[r % 3];
   constexpr int kPer = kPFew / 1024;
@@ -664,11 +676,10 @@ __global__ __launch_bounds__(256) void k_prune_keep(PruneRounds p, uint8_t* __re
 // Lays the rounds' scratch out in the count scratch; false when it is too
 // small (windows under 18 variants, or more than 3.5 million variants, leave
 // less than half an entry per variant for the list).
-static bool prune_rounds_plan(const LdScratch& sc, uint16_t* cc, int64_t cells, int64_t nv, int64_t window, int64_t step,
-                              int64_t* n_kept, PruneRounds& p) {
-  if (!cc || nv >= (int64_t)1 << 31 ||
-      prune_cells_padded(nv, window, step) < kPRoundsMinPasses * kPPass)
-    return false;
+static bool prune_rounds_plan(const LdScratch& sc, uint16_t* cc, int64_t cells, int64_t nv,
+                              int64_t window, int64_t step, int64_t* n_kept, PruneRounds& p) {
+  const int64_t passes = prune_cells_padded(nv, window, step) / kPPass;
+  if (!cc || nv >= (int64_t)1 << 31 || passes < kPRoundsMinPasses) return false;
   char* at = reinterpret_cast<char*>(cc);
   char* const end = at + cells * 2;
   auto take = [&](int64_t bytes) {
@@ -690,6 +701,8 @@ static bool prune_rounds_plan(const LdScratch& sc, uint16_t* cc, int64_t cells, 
   p.nv = nv;
   p.W = window;
   p.S = step;
+  p.rounds = 0;
+  for (int64_t left = p.cap; left > kPFew && p.rounds < kPRounds; left = left * 7 / 8) ++p.rounds;
   return p.cap >= nv / 2 && p.cap >= kPFew;
 }
 
@@ -700,7 +713,7 @@ static int launch_prune_rounds(const LdScratch& sc, const int2* stats, const Pru
   hipLaunchKernelGGL(k_prune_list,
                      dim3((unsigned)ceil_div(p.nv * sc.bm_words, 256 * kPBuildWords)), dim3(256), 0,
                      st, sc.bitmap, sc.bm_words, p, stats);
-  for (int r = 0; r < kPRounds; ++r)
+  for (int r = 0; r < p.rounds; ++r)
     hipLaunchKernelGGL(k_prune_round, dim3((unsigned)blocks), dim3(256), 0, st, p, r);
   hipLaunchKernelGGL(k_prune_finish, dim3(1), dim3(1024), 0, st, p);
   hipLaunchKernelGGL(k_prune_keep, dim3((unsigned)ceil_div(p.nv, 256)), dim3(256), 0, st, p, keep);
