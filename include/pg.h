@@ -325,7 +325,7 @@ int pg_ld_prune(const pg_genotypes* g, const int32_t* sample_idx, int64_t n_sel,
  * every pair.  For samples i, j of the selection:
  *   N[i,j] = markers counted,  A[i,j] = (sum of increments) / N[i,j]
  * (NaN when N[i,j] = 0).  The diagonal uses the same increments with i = j.
- * The sums are formed exactly from increments held to 2^-53, or to 2^-77
+ * The sums are formed exactly from increments held to 2^-53, or to 2^-69 or finer
  * around rare markers (int8 matrix cores, digit by digit), or in IEEE double
  * (fp64 matrix cores, increments factored as z_i z_j with z = (x - 2p) /
  * sqrt(2p(1-p))), by size; either way they match a sequential double sum of

@@ -7,14 +7,18 @@ namespace pg {
 
 // Where the int8 kernels are the path; elsewhere their fixed cost (the digit
 // tables and the operand, 120 us a call) is not earned back.  Measured, us
-// per call, int8 / fp64 (samples x variants):
-//   work (samples^2 x variants) from 8e9 on: 1,500 x 4,000 256 / 262, 800 x
-//   16,000 263 / 306, 2,500 x 2,000 273 / 335; below: 1,200 x 4,000 223 / 196,
-//   1,700 x 2,000 227 / 208, 500 x 16,000 228 / 194;
-//   long panels: 64 x 64,000 237 / 614, 300 x 64,000 295 / 638;
+// per call, int8 / fp64 (samples x variants), frequencies from 0.01 to 0.5, and in
+// brackets panels of rare alleles alone (0.0005 to 0.004, all on low places):
+//   work (samples^2 x variants) from 8e9 on: 2,000 x 2,000 244 / 337 (302), 1,500
+//   x 4,000 259 / 265 (317), 800 x 16,000 267 / 315 (326), 1,000 x 8,000 256 / 244
+//   (313), 1,500 x 8,000 319 / 464 (390); below: 1,200 x 4,000 223 / 196, 1,700 x
+//   2,000 227 / 208;
+//   long panels: 64 x 64,000 235 / 620, 300 x 64,000 295 / 638 (368);
 //   small cohorts on 800 to 8,192 variants, where the fp64 kernel's ranges of
-//   1,024 variants leave the chip idle: 100 x 1,000 122 / 171, 800 x 4,000
-//   181 / 186; shorter: 100 x 500 122 / 100.
+//   1,024 variants leave the chip idle: 100 x 1,000 128 / 176 (160), 400 x 8,000
+//   181 / 191 (225), 800 x 4,000 187 / 195 (234); shorter: 100 x 500 122 / 100.
+// From 4 million calls on the small cohorts lose a little (600 x 8,000 210 / 198,
+// 1,000 x 4,000 224 / 203) and keep the smaller error.
 constexpr double kGrmIntMinWork = 8e9;
 constexpr int64_t kGrmIntLong = 32768;
 constexpr int64_t kGrmIntSmall = 1024, kGrmIntShortMin = 800, kGrmIntShortMax = 8192;

@@ -9,7 +9,8 @@
 // The factors of sample i are small integers, those of sample j are one of
 // three rationals per marker.  Each is rounded once, from the exact rational,
 // to a multiple of 2^-53 and written in balanced base-256 digits, so S is a
-// sum over digit places of int8 products with int32 sums, all exact:
+// sum over digit places of int8 products with int32 sums, all exact (Ozaki's
+// splitting of a product, one factor being small integers already):
 //   S = 2^-53 sum_s 256^s (sum_v x_i F1_s(j) + m_i F2_s(j)).
 // |F2| <= 2 takes 7 digits; |F1| <= 1/p takes 8 down to p = 1/1019, and 7, 9
 // or 10 where the panel's smallest p asks for it.  The only roundings are
@@ -21,16 +22,16 @@
 // Half of 2^-53 is too much for an increment that is small itself: two common
 // homozygotes' is 2p/(1-p), two heterozygotes' (1-2p)^2/(2p(1-p)), and equal
 // markers round alike.  So the markers of a chunk of 64 that holds one with
-// p < 1/256 are rounded to multiples of 2^-77, in three more digits of each
-// factor (a pass over these chunks alone), and those of every chunk where 15
-// of 16 markers have an increment below 1/8 (p < 1/16, or 1 - 2p < 1/8).  The
-// line: sums of equal increments at p of 1/256 to 1/192, relative error at
-// most 6.7e-15 (rms 3.8e-15) here, the fp64 product's 1.2e-14 (rms) over 800
-// to 2,000 markers and 3.7e-15 over 300.  10,000 samples x 1,000 alleles seen
-// once, a pair without one: 3.2e-13 without these digits, 1e-16 with them, the
-// fp64 kernel 6.1e-15.  What they cost: 10,000 x 71,307 at p from 0.0005 to
-// 0.005 56.2 -> 65.0 ms a call, 1,000 x 76,124 1.19 -> 1.35 ms (the fp64 kernel
-// 130 and 1.65); panels without such markers take no more passes.
+// p < 1/512 are rounded to multiples of 2^-77, in three more digits of each
+// factor (a pass over the listed chunks alone); and where 15 of 16 markers have
+// an increment below 1/8 (p < 1/16, or 1 - 2p < 1/8) every chunk's are, to 2^-77,
+// 2^-69 or 2^-85, in the ordinary passes.  The line: sums of equal increments at p
+// of 1/512 to 1/256, relative error at most 1.3e-14 (rms 6e-15) here, the fp64
+// product's rms 1.2e-14 over 800 to 2,000 markers.  10,000 samples x 1,000 alleles
+// seen once, a pair without one: 3.2e-13 without these digits, 4e-17 with them,
+// the fp64 kernel 6.1e-15.  10,000 x 71,307, all p from 0.0005 to 0.005: 47.8 ms a
+// call, p from 0.001 to 0.5 57.7, from 0.01 on 40.0; 1,000 x 76,124 1.07, 0.91 from
+// 0.01 on (the fp64 kernel 130 and 1.65).
 //
 // 16 products of 2 operations at the int8 rate replace one fp64 product at
 // 1/64 of it: 10,000 x 71,307 130 -> 40.4 ms, 1,000 x 76,124 1.65 -> 0.80 ms.
@@ -50,9 +51,8 @@ constexpr int kGiBlockWords = 128;            // words of G per 32 samples and c
 constexpr int kGiSeg = 128;                   // rows per counting segment
 constexpr int kGiQuadWords = 20;              // table words per four variants (18 used)
 constexpr int kGiTabWords = 16 * kGiQuadWords;   // table words per chunk and pass
-constexpr int kGiF2Digits = 7;
-constexpr int kGiFineSlot = 4;                // the fine pass's place among the tables
-constexpr int kGiFineDigits = 3;              // digits below 2^-53
+constexpr int kGiListedSlot = 4;              // the listed chunks' low places among the
+                                              // tables (of passes 0-4)
 
 // What k_gi_stats finds over all markers.
 struct GiPanel {
@@ -60,19 +60,21 @@ struct GiPanel {
                                // them with an increment below 1/8
   uint32_t top;                // largest ceil(n / a)
 };
-// Whether every chunk takes the fine digits, and whether chunk c does.
-__device__ __forceinline__ bool gi_fine_all(const GiPanel& p) {
-  const uint64_t used = p.counts & 0xFFFFFFFFu, coarse = p.counts >> 32;
-  return coarse > 0 && 16 * coarse >= 15 * used;
-}
-__device__ __forceinline__ bool gi_fine(const uint32_t* fine, bool all, int64_t c) {
-  return all || (fine[c >> 5] >> (c & 31) & 1u);
-}
 
-// Digit places of F1 for a panel whose largest n/a (alleles over minor
-// alleles) is at most `top`: |F1| 2^53 < 0.498 * 256^digits.
-__device__ __forceinline__ int gi_digits(uint32_t top) {
-  return top <= 3u ? 7 : top <= 1019u ? 8 : top <= 261000u ? 9 : 10;
+// The digit places of a panel: F1's and F2's, `low` of them below 2^-53 in every
+// chunk; the count of pairs takes the place after F1's.  |F1| 2^53 < 0.498 *
+// 256^digits for n/a (alleles over minor alleles) up to top.  A panel that takes
+// its low places in every chunk takes so many that the last pass of three
+// places is filled (11 and 1 places in four passes, or 14 and 1 in five).
+struct GiPlaces {
+  int n1, n2, low, passes;
+};
+__device__ __forceinline__ GiPlaces gi_places(const GiPanel& p) {
+  const uint64_t used = p.counts & 0xFFFFFFFFu, coarse = p.counts >> 32;
+  const bool all = coarse > 0 && 16 * coarse >= 15 * used;
+  const int n1 = p.top <= 3u && !all ? 7 : p.top <= 1019u ? 8 : p.top <= 261000u ? 9 : 10;
+  const int low = !all ? 0 : n1 < 10 ? 11 - n1 : 4;
+  return GiPlaces{n1 + low, 7 + low, low, (n1 + low + 3) / 3};
 }
 
 // ---- per-marker counts ------------------------------------------------------
@@ -127,7 +129,7 @@ __global__ __launch_bounds__(256) void k_gi_counts(const uint32_t* __restrict__ 
 // Per variant: {alleles n = 2 calls, minor alleles a}, a = 0 for an undefined
 // marker; per 16 variants a word with the undefined ones in the low half and
 // those whose minor allele is A1 in the high half; the panel's figures; and a
-// bit per chunk (a wave's variants) that holds a rare allele.
+// bit per chunk (a wave's variants) that holds a rare allele (p < 1/512).
 __global__ __launch_bounds__(256) void k_gi_stats(const uint32_t* __restrict__ cnt, int64_t nv_pad,
                                                   int segs, uint2* __restrict__ stat,
                                                   uint32_t* __restrict__ marks,
@@ -156,7 +158,7 @@ __global__ __launch_bounds__(256) void k_gi_stats(const uint32_t* __restrict__ c
     const uint32_t o = __shfl_xor(r, d, 64);
     r = o > r ? o : r;
   }
-  const uint64_t rare = __ballot(used && 256 * a < n);
+  const uint64_t rare = __ballot(used && 512 * a < n);
   const uint64_t coarse = __ballot(used && (16 * a < n || (2 * a < n && 8 * (n - 2 * a) < n)));
   __shared__ uint32_t s_n[2];
   if (threadIdx.x < 2) s_n[threadIdx.x] = 0u;
@@ -216,8 +218,8 @@ __device__ __forceinline__ int gi_digit(uint64_t& lo, uint64_t& hi) {
 // for a column call of class x = 0, 1, 2.  Pass t holds the digit places
 // 3t .. 3t + 2: planes 0-2 those of F1 (rows enter with x), 3-5 those of F2
 // (rows enter with m), where the place after F1's last holds the count of
-// pairs (1 in every class).  Pass kGiFineSlot holds the three places below
-// 2^-53 of the chunks that take them.
+// pairs (1 in every class).  Pass kGiListedSlot holds three places below 2^-53
+// for the chunks that are listed in `fine`, where not every chunk has them.
 __global__ __launch_bounds__(256) void k_gi_tables(const uint2* __restrict__ stat, int64_t nch,
                                                    const GiPanel* __restrict__ panel,
                                                    const uint32_t* __restrict__ fine,
@@ -230,23 +232,23 @@ __global__ __launch_bounds__(256) void k_gi_tables(const uint2* __restrict__ sta
   if (c >= nch) return;
   const uint2 s = stat[c * kGiChunk + 16 * (quad >> 2) + 4 * b + (quad & 3)];
   const uint64_t n = s.x, a = s.y;
-  const int n1 = gi_digits(panel->top), passes = (n1 + 3) / 3;
-  const bool more = gi_fine(fine, gi_fine_all(*panel), c);   // the same for the wave's chunk
+  const GiPlaces at = gi_places(*panel);
+  const bool listed = at.low == 0 && (fine[c >> 5] >> (c & 31) & 1u);   // the wave's chunk
   uint64_t lo = 0, hi = 0;
   if (a) {
     const uint64_t z = n - a, h = n - 2 * a;      // a <= n / 2
     const uint64_t num = k == 1 ? n * h : k == 3 ? 2 * a : k == 4 ? h : k == 5 ? 2 : n;
     const uint64_t den = k == 1 ? 2 * a * z : k == 2 ? a : k == 5 ? 1 : z;
     // F1: -1/(1-p), (1-2p)/(2p(1-p)), 1/p; F2: 2p/(1-p), -(1-2p)/(1-p), -2
-    gi_fixed(num, den, more ? 53 + 8 * kGiFineDigits : 53, k == 0 || k >= 4, lo, hi);
+    gi_fixed(num, den, 53 + (listed ? 24 : 8 * at.low), k == 0 || k >= 4, lo, hi);
   }
-  const int digits = k < 3 ? n1 : kGiF2Digits;
-  for (int t = more ? -1 : 0; t < passes; ++t) {
-    uint32_t* out = tab + (((t < 0 ? kGiFineSlot : t) * nch + c) * 16 + quad) * kGiQuadWords;
+  const int digits = k < 3 ? at.n1 : at.n2;
+  for (int t = listed ? -1 : 0; t < at.passes; ++t) {
+    uint32_t* out = tab + (((t < 0 ? kGiListedSlot : t) * nch + c) * 16 + quad) * kGiQuadWords;
 #pragma unroll
     for (int q = 0; q < 3; ++q) {
       const int place = 3 * t + q;
-      const int d = place < digits ? gi_digit(lo, hi) : a && k >= 3 && place == n1 ? 1 : 0;
+      const int d = place < digits ? gi_digit(lo, hi) : a && k >= 3 && place == at.n1 ? 1 : 0;
       uint32_t x = (uint32_t)d & 0xFFu;
       x |= __shfl_xor(x, 1, 64) << 8;
       x |= __shfl_xor(x, 2, 64) << 16;
@@ -568,34 +570,35 @@ __global__ __launch_bounds__(256, 2) void k_gi_pairs(const uint32_t* __restrict_
   const int64_t split = whole ? 0 : tail_item / o.tail;
   int64_t I, J;
   gi_tile<NR>(tile, o.nj, I, J);
-  const int n1 = gi_digits(panel->top), passes = (n1 + 3) / 3;
+  const GiPlaces at = gi_places(*panel);
   const int c_begin = whole ? 0 : (int)(split * o.cps);
   const int c_end = whole || (split + 1) * o.cps > nch ? (int)nch : (int)((split + 1) * o.cps);
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int rb = (wave % NR) * 128 + 4 * (lane >> 5), cb = (wave / NR) * 32 + (lane & 31);
-  // pass -1 takes the three places below 2^-53
-  const bool all = gi_fine_all(*panel);
-  const int t0 = all || gi_next(fine, c_begin, c_end) < c_end ? -1 : 0;
-  for (int t = t0; t < passes; ++t) {
+  // pass -1: the low places of the listed chunks
+  const int t0 = at.low == 0 && gi_next(fine, c_begin, c_end) < c_end ? -1 : 0;
+  for (int t = t0; t < at.passes; ++t) {
     v16i_t acc[3][4];
 #pragma unroll
     for (int q = 0; q < 3; ++q)
 #pragma unroll
       for (int a = 0; a < 4; ++a) acc[q][a] = (v16i_t){0};
-    const uint32_t* tt = tab + (int64_t)(t < 0 ? kGiFineSlot : t) * nch * kGiTabWords;
-    // the last of the usual eight places: F1 and F2 at 6, F1 at 7, the count
-    if (n1 == 8 && t == 2)
+    const uint32_t* tt = tab + (int64_t)(t < 0 ? kGiListedSlot : t) * nch * kGiTabWords;
+    const bool end = t == at.passes - 1;
+    // the last of the usual eight places (and of eleven): F1 and F2 at the first,
+    // F1 at the second, the count at the third
+    if (end && at.n1 % 3 == 2)
       gi_pass<NR, 0x2B, false>(G, tt, nch, I, J, c_begin, c_end, s.in, acc, nullptr);
     else
       gi_pass<NR, 0x3F, true>(G, tt, nch, I, J, c_begin, c_end, s.in, acc,
-                              t < 0 && !all ? fine : nullptr);
+                              t < 0 ? fine : nullptr);
     // the places' sum is below 2^48 in magnitude: exact in double; the
     // passes before are read back from where they were parked
-    const int count_at = n1 - 3 * t;
-    const double scale = __longlong_as_double((int64_t)(1023 - 53 + 24 * t) << 52);
+    const int count_at = at.n1 - 3 * t;
+    const double scale =
+        __longlong_as_double((int64_t)(1023 - 53 - 8 * at.low + 24 * t) << 52);
     const double s0 = count_at > 0 ? scale : 0.0, s1 = count_at > 1 ? 256.0 * scale : 0.0,
                  s2 = count_at > 2 ? 65536.0 * scale : 0.0;
-    const bool end = t == passes - 1;
     const int64_t park =
         whole || o.n_split == 1 ? -((int64_t)1 << 60) : tail_item * 16384 + cb;
     const int64_t j = J * (128 / NR) + cb;
@@ -623,8 +626,8 @@ __global__ __launch_bounds__(256, 2) void k_gi_pairs(const uint32_t* __restrict_
         for (int r = 0; r < 4; ++r) {
           const double S = s0 * (double)x0[r] + s1 * (double)x1[r] + s2 * (double)x2[r];
           const int n = count_at == 0 ? x0[r] : count_at == 1 ? x1[r] : x2[r];
-          gi_put(o, t == t0, end, park + (int64_t)(il + r) * (128 / NR), I * 128 * NR + il + r, j, S,
-                 (uint32_t)n);
+          gi_put(o, t == t0, end, park + (int64_t)(il + r) * (128 / NR), I * 128 * NR + il + r, j,
+                 S, (uint32_t)n);
         }
       }
     }
@@ -659,7 +662,7 @@ constexpr int64_t kGiAlign = 256;
 
 // Rows per tile: 512 (NR = 4) or 256 (2).  The larger tile generates its
 // digits for twice the rows, but fills the diagonal worse: 1,000 samples take
-// 0.81 ms with 256, 0.86 ms with 512.
+// 0.80 ms with 256, 0.86 ms with 512.
 int gi_shape(int64_t m) { return m > 1536 ? 4 : 2; }
 
 int64_t gi_tile_count(int64_t m, int64_t& ni, int64_t& nj) {
@@ -715,7 +718,7 @@ bool grm_int_plan(int64_t m, int64_t nv, int64_t rows_pad, int64_t wp, int64_t b
   };
   // column strips reach past the last row tile only within its rows
   p.off_G = take(p.blocks32 * p.nch * kGiBlockWords * 4);
-  p.off_tab = take((kGiFineSlot + 1) * p.nch * kGiTabWords * 4);
+  p.off_tab = take((kGiListedSlot + 1) * p.nch * kGiTabWords * 4);
   p.off_cnt = take(ceil_div(rows_pad, kGiSeg) * wp * 16 * 4);
   p.off_stat = take(wp * 16 * 8);
   p.off_marks = take(wp * 4);

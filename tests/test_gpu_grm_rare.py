@@ -2,9 +2,9 @@
 once or three times, samples that have calls at rare markers only, and markers
 all but at p = 1/2 with a sample that is heterozygous throughout.
 
-The int8 path rounds such a marker's class factors to a multiple of 2^-77
-(error at most 2^-78; x <= 2 and m <= 1 bring in at most three of them), other
-markers' to 2^-53.  The up to five digit passes and 64 ranges are added in
+The int8 path rounds such a marker's class factors to a multiple of 2^-69 or
+finer (error at most 2^-70; x <= 2 and m <= 1 bring in at most three of them),
+other markers' to 2^-53.  The up to five digit passes and 64 ranges are added in
 double, each addition rounding a partial sum of at most D = sum of |x F1| +
 |m F2|, and the division rounds once more.  The reference is numpy's extended
 precision (2^-64) on a few of the samples, with the frequencies of all."""
@@ -28,7 +28,7 @@ def _bed(x):
 
 
 def _check(x, some, fine):
-    """fine: which markers' factors are held to 2^-77."""
+    """fine: which markers' factors are held to 2^-69 or finer."""
     V, n = x.shape
     A, N = pg.grm_matrix(pg.Cohort.from_numpy(_bed(x), n), layout="full")
     torch.cuda.synchronize()
@@ -44,7 +44,7 @@ def _check(x, some, fine):
     f2 = -2 * p * f1
     S = x.T.astype(L) @ f1 + m.T.astype(L) @ f2
     D = x.T.astype(L) @ abs(f1) + m.T.astype(L) @ abs(f2)
-    unit = np.where(fine, 2.0 ** -78, 2.0 ** -54)
+    unit = np.where(fine, 2.0 ** -70, 2.0 ** -54)
     r = (2 * m * unit[:, None]).T @ m.astype(float) + (m * unit[:, None]).T @ m.astype(float)
     Nr = m.T.astype(np.int64) @ m.astype(np.int64)
     assert np.array_equal(N, Nr)
