@@ -259,12 +259,17 @@ int plan_ld(const Sel& s, int32_t window, int path_arg, LdPlan& p) {
 // Band tiles take the correction path when their two 64-variant groups hold
 // at most m/4 missing calls (m selected samples), and only once a quarter
 // of the groups have a diagonal tile that does, so that the sample-major
-// operand is worth building.  Whole calls on 300,000 variants, window 1,000,
-// every tile forced onto the correction kernel, against 3.5-3.6 ms for the
-// dense kernel at 5,000 samples: 2.36 ms without missing calls, 3.45 at 0.15%
-// (0.19m per tile), 3.68 at 0.25% (0.32m), 4.13 at 0.5%.  10,000 samples x
-// 100,000 variants, window 500: 0.99, 1.33, 1.44, 1.62 ms against 1.40-1.44.
-// The lines cross between 0.25m and 0.32m.
+// operand is worth building.  Whole calls, ms, every tile forced onto the
+// correction kernels, by missing calls (and per tile), against the dense kernel:
+//                          0    0.0001%  0.01%  0.1%  0.15%  0.25%  0.5%  dense
+//                                               0.13m 0.19m  0.32m  0.64m
+//   5,000 x 300,000, 1,000 1.37   2.46   2.83   3.32  3.43   3.65   4.12  3.5-3.7
+//   10,000 x 100,000, 500  0.66   1.01   1.09   1.26  1.32   1.42   1.61  1.40
+// The lines cross between 0.19m and 0.32m.  The step after 0 is k_ld_complete's:
+// a missing call in any of its four groups sends a 128 x 128 tile to the 64 x 64
+// kernel.  The default takes the forced figures up to 0.15% and the dense
+// kernel's, 3.60 and 1.38, from 0.2%; at 0.2%, where half of the tiles are on
+// either side, the quarter rule (4.43) loses to the default's half.
 int64_t ld_sparse_budget(const LdPlan& p, int64_t m) {
   return p.variant & (kLdAllTiles | kLdDiag) ? INT64_MAX : m / 4;
 }
@@ -750,9 +755,8 @@ int pg_ibs_similarity(const uint32_t* ibs1, const uint32_t* ibs2, const uint32_t
 }
 
 namespace {
-// Variant-major operand of the selection (rows_pad x wn words), the five
-// per-marker term columns, the per-marker flags, the six sums and the runs'
-// partial sums.
+// The selection's calls, nv x wn words (written only with a sample list), every
+// variant's {calls, A2 alleles}, and the six sums with the runs' partial sums.
 struct GenomePlan {
   int64_t wn, off_D, off_counts, off_sums, bytes;
 };

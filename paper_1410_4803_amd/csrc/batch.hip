@@ -493,7 +493,9 @@ int pg_batch_launch(const pg_plan* plan, void* workspace, size_t workspace_bytes
   // the persistent kernels, the scans and emissions.  Layouts, scans and
   // emissions are one launch each for all problems: 16 problems (8 LD of
   // 200-5,000 x 2,000-20,000) took 1.04 ms with four launches of 4 to 14 us per
-  // problem after the tiles, and takes 0.72 ms with two in all.
+  // problem after the tiles, and takes 0.72 ms with two in all, 0.83 ms once the
+  // process has launched a cooperative kernel (the clustering's), after which the
+  // two streams hand over more slowly.
   rc = launch_ld_layout_jobs((const LdLayoutJob*)(ws + plan->off_ld_jobs), plan->n_ld_jobs,
                              plan->ld_job_blocks, side);
   if (rc != PG_OK) return rc;

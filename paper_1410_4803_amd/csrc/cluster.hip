@@ -545,13 +545,16 @@ __global__ __launch_bounds__(kClT) void k_cl_rescan(const double* __restrict__ D
 // pairs the sequential rule merges come in increasing order, since a merged
 // cluster's pairs are no smaller than the pairs they replace.  So every
 // mutually nearest pair of a round can merge at once, and the sequence is the
-// list of all merges sorted by (height, a, b).  About 50-65 rounds for 1,000
-// to 10,000 samples, each merging 5-20% of the clusters.
+// list of all merges sorted by (height, a, b) (reciprocal nearest neighbours, a
+// known form of agglomerative clustering).  47 rounds for 1,000 samples of
+// independent variants, 77 for 10,000 of a founder mosaic, each merging 5-20% of
+// the clusters.
 //
 // Active clusters occupy slots in increasing label, so the nearest neighbour
 // of slot k is argmin over l of (d, l).  A round, in every block alike:
 //   1. the neighbours of all slots go to LDS; slot k merges with l = nn[k]
-//      when nn[l] = k; block 0 records the pairs;
+//      when nn[l] = k.  The wave that writes a pair's row records the merge,
+//      block 0 the last one;
 //   2. with at least 1 pair per kClFew slots (or a quarter of the slots
 //      retired) the matrix is rebuilt without the retired slots into the
 //      other buffer: entry (i, j) is the maximum over the members of both
@@ -567,9 +570,10 @@ __global__ __launch_bounds__(kClT) void k_cl_rescan(const double* __restrict__ D
 // form a cycle, the slot with the smallest distance merges with its neighbour,
 // so that every call writes m - 1 merges.
 //
-// Measured: 10,000 samples 155 -> 3.7 ms (0.6 ms of it the distances, 2.4 ms
-// the rebuilds), 1,000 samples 7.6 -> 0.42 ms (45 rounds of about 8 us); one
-// pair per round and step, 6,000 samples at equal distances, 73 -> 96 ms.
+// Measured: 10,000 samples 155 -> 3.7 ms (0.4 ms of it the distances), 1,000
+// samples 7.6 -> 0.43 ms (47 rounds of about 8 us).  What it costs where a round
+// finds one pair: equal distances, 6,000 samples 73 -> 93 to 96 ms, 1,000 samples
+// 7.8 ms either way.
 constexpr int kClMaxSlots = 24576;   // 6 bytes of LDS per slot
 constexpr int kClFew = 32;
 constexpr int kClWaves = kClT / 64;
@@ -1002,7 +1006,8 @@ __global__ __launch_bounds__(256) void k_cl_start(const uint32_t* __restrict__ i
 int64_t cluster_rounds_bytes(int64_t m) {
   if (m > kClMaxSlots) return 0;
   const int64_t ld = round_up(m, 16);
-  return 2 * m * ld * 8 + 2 * round_up(m, 32) * (8 + 4 + 4) + round_up(m, 32) * 16 + kClBarWords * 4;
+  return 2 * m * ld * 8 + 2 * round_up(m, 32) * (8 + 4 + 4) + round_up(m, 32) * 16 +
+         kClBarWords * 4;
 }
 
 // Whether the rounds can run: the slots fit, the stream is not capturing (a

@@ -167,7 +167,8 @@ __global__ __launch_bounds__(256) void k_sample_major_jobs(const LayoutJob* __re
     if (jobs[mid].block_begin <= b) lo = mid; else hi = mid - 1;
   }
   const LayoutJob j = jobs[lo];
-  sample_major_tiled_block<kSmTG, 256>(j.s, j.T, j.rows_pad, j.wp, j.aligned, b - j.block_begin, s_out);
+  sample_major_tiled_block<kSmTG, 256>(j.s, j.T, j.rows_pad, j.wp, j.aligned, b - j.block_begin,
+                                       s_out);
 }
 
 int64_t sample_major_job_blocks(int64_t rows_pad, int64_t wp) {

@@ -403,15 +403,15 @@ int launch_ld_finish_jobs(const LdFinishJob* jobs, int n_words, int n_planes,
   };
   constexpr int kMaxY = 32768;   // table slices a launch's grid takes
   for (int i = 0; rc == PG_OK && max_capacity[0] > 0 && i < n_words; i += kMaxY) {
-    hipLaunchKernelGGL(k_ld_emit_jobs<false>,
-                       dim3(gx(max_capacity[0]), (unsigned)(n_words - i < kMaxY ? n_words - i : kMaxY)),
-                       dim3(256), 0, st, jobs + i);
+    const unsigned gy = (unsigned)(n_words - i < kMaxY ? n_words - i : kMaxY);
+    hipLaunchKernelGGL(k_ld_emit_jobs<false>, dim3(gx(max_capacity[0]), gy), dim3(256), 0, st,
+                       jobs + i);
     rc = check_launch("ld_emit_jobs");
   }
   for (int i = 0; rc == PG_OK && max_capacity[1] > 0 && i < n_planes; i += kMaxY) {
-    hipLaunchKernelGGL(k_ld_emit_jobs<true>,
-                       dim3(gx(max_capacity[1]), (unsigned)(n_planes - i < kMaxY ? n_planes - i : kMaxY)),
-                       dim3(256), 0, st, jobs + n_words + i);
+    const unsigned gy = (unsigned)(n_planes - i < kMaxY ? n_planes - i : kMaxY);
+    hipLaunchKernelGGL(k_ld_emit_jobs<true>, dim3(gx(max_capacity[1]), gy), dim3(256), 0, st,
+                       jobs + n_words + i);
     rc = check_launch("ld_emit_jobs");
   }
   return rc;

@@ -45,7 +45,8 @@ namespace pg {
 // groups_ok[0] when its diagonal tile qualifies (a tile (I, J) can qualify only
 // if one of its groups has total <= budget / 2, whose diagonal tile then
 // qualifies too), and in groups_ok[1] when it has missing calls that a tile the
-// path takes could ask for, in groups_ok[2] when it has any.  Bound by the start of its few blocks (11 to 14 us);
+// path takes could ask for, in groups_ok[2] when it has any.  Bound by the start
+// of its few blocks (11 to 14 us);
 // counting in the layout and skipping lists and T where there is nothing to
 // correct took pruning 10,000 x 88,025 calls without missing ones from 1.10 to
 // 0.85 ms (the operand was read twice more for counts, 72 us each, and T built
@@ -732,16 +733,16 @@ int launch_ld_sparse(const uint32_t* D, const uint32_t* E, int64_t wn, const uin
   const int64_t n_band = ((int64_t)window + kLdTile - 1) / kLdTile + 1;
   if (E && !dbg) {
     const int64_t n_row2 = ceil_div(n_row_tiles, 2), n_band2 = ((int64_t)window + 127) / 128 + 1;
-    hipLaunchKernelGGL(k_ld_complete,
-                       dim3((unsigned)(n_row2 * n_band2)), dim3(256), 0, st, E, wn, sp.vst, sp.gmax, sp.groups_ok, sp.min_groups, m, nv,
-                       n_row_tiles, n_band2, window, r2_min, sc);
+    hipLaunchKernelGGL(k_ld_complete, dim3((unsigned)(n_row2 * n_band2)), dim3(256), 0, st, E, wn,
+                       sp.vst, sp.gmax, sp.groups_ok, sp.min_groups, m, nv, n_row_tiles, n_band2,
+                       window, r2_min, sc);
     rc = check_launch("ld_complete");
     if (rc != PG_OK) return rc;
   }
   hipLaunchKernelGGL(E ? k_ld_sparse<true> : k_ld_sparse<false>,
-                     dim3((unsigned)(n_row_tiles * n_band)), dim3(256), 0, st, E ? E : D, wn, T, t_rows, sp.lists, sp.vst, sp.gsum, sp.gmax,
-                     sp.groups_ok, sp.min_groups, sp.cap, sp.budget, m, nv, n_row_tiles, n_band,
-                     window, r2_min, sc, dbg, v0);
+                     dim3((unsigned)(n_row_tiles * n_band)), dim3(256), 0, st, E ? E : D, wn, T,
+                     t_rows, sp.lists, sp.vst, sp.gsum, sp.gmax, sp.groups_ok, sp.min_groups,
+                     sp.cap, sp.budget, m, nv, n_row_tiles, n_band, window, r2_min, sc, dbg, v0);
   rc = check_launch("ld_sparse");
   mark_stage(2, st);
   return rc;

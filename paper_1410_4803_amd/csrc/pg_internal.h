@@ -382,7 +382,10 @@ int launch_ld_popc(const uint32_t* P, int64_t words_pad, int64_t nv, int64_t row
                    int32_t window, double r2_min, const LdScratch& sc, hipStream_t st);
 // Row-offset scan, *n_out, and the emit kernel.  X is the operand the pair
 // kernel used: 2-bit words (rows x words) or bit planes (planes == true).
-// `marks` records stage events 3 and 4 (one-problem calls only).
+// Records stage events 3 and 4.
+int launch_ld_finish(const uint32_t* X, bool planes, int64_t words, int64_t rows_pad, int64_t nv,
+                     int64_t v0, const LdScratch& sc, pg_ld_pair* out, int64_t capacity,
+                     int64_t* n_out, hipStream_t st);
 // Scan and emission of many problems at once: a device array of them, the
 // first n_words on 2-bit words and the rest on bit planes; max_capacity[] of
 // the two parts.  Rows up to kLdScanJobRows; the others need scan_ld_rows
@@ -399,9 +402,6 @@ constexpr int64_t kLdScanJobRows = 131072;
 int scan_ld_rows(const LdScratch& sc, int64_t nv, int64_t* n_out, hipStream_t st);
 int launch_ld_finish_jobs(const LdFinishJob* jobs, int n_words, int n_planes,
                           const int64_t* max_capacity, hipStream_t st);
-int launch_ld_finish(const uint32_t* X, bool planes, int64_t words, int64_t rows_pad, int64_t nv,
-                     int64_t v0, const LdScratch& sc, pg_ld_pair* out, int64_t capacity,
-                     int64_t* n_out, hipStream_t st);
 
 // ---- LD pruning (prune.hip) -------------------------------------------------
 // Per selected variant: {minor allele count, non-missing calls (at least 1)}

@@ -8,7 +8,8 @@
 //
 // GPU plan.  The pass runs in rounds that decide every pair whose earlier
 // rivals are decided (below); what follows is the sequential form, which
-// small calls take and the rounds fall back to.  The LD pair kernel (window W - 1, emission test r^2 > t) marks
+// small calls take and the rounds fall back to.  The LD pair kernel (window
+// W - 1, emission test r^2 > t) marks
 // every pair above the threshold in its per-row bitmap.  A pair (a, b) first
 // shares a window in window w(b) -- the first window whose end passes b --
 // and is then visited there if a >= w(b)*S; in later windows both variants
@@ -25,8 +26,9 @@
 namespace pg {
 
 // ---- per-variant allele counts ---------------------------------------------
-// (2-bit operands: counted by the layout.)  Bit planes: plane p of word w at P[(w*3 + p)*rows_pad + v] (p = 0 homA2,
-// 1 homA1, 2 non-missing); one thread per variant.
+// (2-bit operands: counted by the layout.)  Bit planes: plane p of word w at
+// P[(w*3 + p)*rows_pad + v] (p = 0 homA2, 1 homA1, 2 non-missing); one thread per
+// variant.
 __global__ __launch_bounds__(256) void k_stats_planes(const uint32_t* __restrict__ P, int64_t words,
                                                       int64_t rows_pad, int64_t nv,
                                                       int2* __restrict__ stats) {
