@@ -241,9 +241,9 @@ typedef struct pg_ld_pair {
 } pg_ld_pair;
 
 /* Workspace bytes pg_ld_window needs for this shape, window and path: the 2-bit
- * operand, on the fp4 kernels up to 16 GiB of it also its calls as nibbles (two
- * more bytes per byte; larger panels expand the 2-bit words in the kernel), the
- * emission scratch, and for PG_PATH_SPARSE the sample-major operand and the
+ * operand, on the fp4 kernels also its calls as nibbles (two more bytes per byte)
+ * where that is the faster and the operand at most 16 GiB (the kernel expands the
+ * 2-bit words elsewhere), the emission scratch, and for PG_PATH_SPARSE the sample-major operand and the
  * missing-call lists. */
 int pg_ld_workspace_bytes(const pg_genotypes* g, int64_t n_sel, int64_t v_begin, int64_t v_end,
                           int32_t window, int path, size_t* bytes);

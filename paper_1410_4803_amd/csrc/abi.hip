@@ -231,8 +231,12 @@ int plan_ld(const Sel& s, int32_t window, int path_arg, LdPlan& p) {
   }
   Carve c;
   p.off_D = c.take(operand_bytes);
-  const bool nibbles = ld_takes_nibbles(s.m, operand_bytes) &&
-      (path == PG_PATH_SPARSE || (path == PG_PATH_MFMA && p.variant == kLdVariantFp4));
+  // (the correction path's kernels read them whatever the window)
+  const bool nibbles =
+      path == PG_PATH_SPARSE
+          ? ld_takes_nibbles(s.m, operand_bytes, s.m)
+          : path == PG_PATH_MFMA && p.variant == kLdVariantFp4 &&
+                ld_takes_nibbles(s.m, operand_bytes, window);
   p.off_E = nibbles ? c.take(2 * operand_bytes) : -1;
   p.off_part = path == PG_PATH_POPC
                    ? -1 : c.take(p.rows_pad * ceil_div(p.words, kLdCountWords) * 4);

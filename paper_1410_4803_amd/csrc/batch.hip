@@ -267,7 +267,7 @@ int pg_batch_plan(const pg_problem* probs, int n_probs, pg_plan** out) {
         q.off_x = take(off, bytes);
         q.off_e = -1;
         if (q.path == PG_PATH_MFMA && q.variant == kLdVariantFp4 &&
-            ld_takes_nibbles(q.s.m, bytes) && nibble_bytes + 2 * bytes <= kLdNibbleMaxBytes) {
+            ld_takes_nibbles(q.s.m, bytes, q.p.window) && nibble_bytes + 2 * bytes <= kLdNibbleMaxBytes) {
           q.off_e = take(off, 2 * bytes);
           nibble_bytes += 2 * bytes;
         }

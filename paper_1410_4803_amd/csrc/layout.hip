@@ -699,6 +699,7 @@ int launch_ld_layout(const Sel& s, uint32_t* D, uint32_t* E, int64_t rows_pad, i
                      0, st, s, D, rows_pad, wn);
   int rc = check_launch("variant_major_2bit");
   if (rc != PG_OK) return rc;
+  if (!E && !cn.part) return ld_clear(sc, rows_pad, st);
   hipLaunchKernelGGL(k_ld_layout<true>, grid, dim3(256), 0, st, s, D, E, rows_pad, wn, 0, sc,
                      cn);
   return check_launch("ld_layout");

@@ -338,9 +338,20 @@ constexpr int64_t kLdFp4MaxSamples = ((int64_t)1 << 24) / 9;
 // Panels from 16 GiB on keep the smaller footprint: a chromosome of 61 GB takes
 // 244 GB of 288.
 constexpr int64_t kLdNibbleMaxBytes = (int64_t)32 << 30;
-// Whether E goes with an operand D of `bytes` over m samples.
-inline bool ld_takes_nibbles(int64_t m, int64_t bytes) {
-  return m < kLdFp4MaxSamples && 2 * bytes <= kLdNibbleMaxBytes;
+// Whether E goes with an operand D of `bytes` over m samples, for the band of
+// `window`.  Writing it has to pay: narrow windows over many samples read it too
+// seldom, and its two bytes more per byte of D cost the tiles of large cohorts
+// what its ready operands save.  Whole calls, us, with E / without it (D of 500
+// MB; of 20 MB the two are within 3%):
+//   2,500 samples   window 20 845 / 829      100 1128 / 1172   1,000 4636 / 5447
+//   5,000                  20 818 / 744      100 1073 / 1033   200 1469 / 1529
+//   10,000                 20 802 / 694      200 1439 / 1411   350 1901 / 1931
+//   20,000                 20 837 / 698      350 1915 / 1887   500 2449 / 2454
+//   50,000                 20 801 / 682      700 3231 / 3220   1,000 4454 / 4460
+constexpr int64_t kLdNibbleFewSamples = 3000, kLdNibbleSmall = (int64_t)16 << 20;
+inline bool ld_takes_nibbles(int64_t m, int64_t bytes, int64_t window) {
+  return m < kLdFp4MaxSamples && 2 * bytes <= kLdNibbleMaxBytes &&
+         (m <= kLdNibbleFewSamples || window >= m / 40 || bytes < kLdNibbleSmall);
 }
 // Dense pair kernel over the band; with `sp`, tiles the correction path
 // takes are skipped (and stage 2 is left to that path).  With E the fp4 tile

@@ -1639,7 +1639,7 @@ __device__ __forceinline__ void ld_nib_tile(const uint32_t* __restrict__ E, int6
 }
 
 // ---- banded fp4 matrix-core kernel without the nibble operand ------------------------
-// Where E is not laid out (kLdNibbleMaxBytes, kLdFp4MaxSamples): the same six
+// Where E is not laid out (ld_takes_nibbles): the same six
 // Grams on e2m1 operands expanded from the 2-bit words of D (m, x, h are 0 or
 // +-1, exact; fp32 sums exact below 2^24 samples), and the chunk schedule of
 // ibs_fp4_tile_pipe: a chunk of 256 samples is four steps of 64 per MFMA lane

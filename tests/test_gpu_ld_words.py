@@ -1,6 +1,7 @@
 """LD without the nibble operand (cohorts whose sums do not fit its fp4 form,
-1,864,135 samples and more): the fp4 tile on the 2-bit words, the correction
-path beside it, pruning and batches, over more than one tile of variants."""
+1,864,135 samples and more, and narrow windows over many samples): the fp4 tile
+on the 2-bit words, the correction path beside it, pruning and batches, over more
+than one tile of variants."""
 import numpy as np
 import pytest
 import torch
@@ -73,3 +74,20 @@ def test_words_in_a_batch():
         got = pg.records_to_numpy(p.out, int(p.n_out.item()))
         assert len(got) > 0
         assert got.tobytes() == _records(p.cohort, p.window, 0.0, MFMA).tobytes()
+
+
+@pytest.mark.parametrize("n,V,W", [(3001, 23000, 74), (5003, 14001, 20), (10000, 7000, 1),
+                                   (20011, 3500, 130)])
+def test_narrow_windows(n, V, W):
+    """Operands from 16 MiB on."""
+    c = pg.Cohort.from_numpy(_bed(V, n, True, W), n)
+    assert pg.ld_workspace_bytes(c, W, path=MFMA) < 1.6 * V * n / 4
+    for r2_min in (0.0, 0.05):   # linked neighbours: about 0.1
+        got = _records(c, W, r2_min, MFMA)
+        assert len(got) > 0 and got.tobytes() == _records(c, W, r2_min, POPC).tobytes()
+    idx = torch.randperm(n, generator=torch.Generator().manual_seed(2)).to(torch.int32).cuda()
+    got = _records(c, W, 0.0, MFMA, idx)
+    assert len(got) > 0 and got.tobytes() == _records(c, W, 0.0, POPC, idx).tobytes()
+    keep, n_kept = pg.ld_prune(c, W + 1, max(1, W // 10), 0.05, path="mfma")
+    ref, n_ref = pg.ld_prune(c, W + 1, max(1, W // 10), 0.05, path="popc")
+    assert torch.equal(keep, ref) and torch.equal(n_kept, n_ref)

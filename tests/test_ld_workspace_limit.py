@@ -1,6 +1,6 @@
-"""The nibble operand of LD is laid out only while it is a small part of the
-card: large panels keep the workspace of the tiles that work on the 2-bit words
-alone."""
+"""The nibble operand of LD is laid out only where the window reads it often
+enough, and while it is a small part of the card: other calls keep the workspace
+of the tiles that work on the 2-bit words alone."""
 import ctypes
 
 import pytest
@@ -37,9 +37,18 @@ def test_largest_nibble_operand():
     """32 GiB of nibbles are 16 GiB of words: 131,072 samples x 524,288 variants."""
     n, V = 131072, 524288
     assert _words(n, V) == 16 * GIB
-    assert _bytes(n, V, 10, N.PG_PATH_MFMA) > 3 * 16 * GIB
+    W = 4000
+    assert _bytes(n, V, W, N.PG_PATH_MFMA) > 3 * 16 * GIB
     for n, V in ((131072, 524289), (131073, 524288)):
-        assert _bytes(n, V, 10, N.PG_PATH_MFMA) < 1.1 * _words(n, V)
+        assert _bytes(n, V, W, N.PG_PATH_MFMA) < 1.1 * _words(n, V)
+
+
+@pytest.mark.parametrize("n,V,W,nibbles", [(3000, 100000, 1, True), (3001, 100000, 74, False),
+                                           (3001, 100000, 75, True), (20000, 50000, 499, False),
+                                           (20000, 50000, 500, True), (20000, 3000, 1, True)])
+def test_narrow_windows_over_many_samples(n, V, W, nibbles):
+    got = _bytes(n, V, W, N.PG_PATH_MFMA) / _words(n, V)
+    assert (got > 3) == nibbles and (nibbles or got < 1.6)
 
 
 def test_a_batch_shares_the_limit():
@@ -52,7 +61,7 @@ def test_a_batch_shares_the_limit():
         for p in probs:
             p.kind = N.PG_KIND_LD
             p.g = N.Genotypes(0x1000, n, V, 0, None)
-            p.window, p.r2_min, p.capacity = 10, 0.5, 16
+            p.window, p.r2_min, p.capacity = 4000, 0.5, 16
             p.out = p.n_out = 0x1000
         plan, b = ctypes.c_void_p(), ctypes.c_size_t(0)
         assert lib.pg_batch_plan(probs, k, ctypes.byref(plan)) == 0, N.last_error()
