@@ -396,9 +396,9 @@ int pg_cluster_workspace_bytes(int64_t m, size_t* bytes);
  * distance (largest member-to-member distance) merge; ties go to the pair
  * with the smallest a, then the smallest b.  merges (device, m - 1 records)
  * receives the merge sequence in order; the result is exactly determined by
- * the counts.  Up to 24,576 samples all mutually nearest pairs merge in a
+ * the counts.  From 10 to 24,576 samples all mutually nearest pairs merge in a
  * round, and one cooperative launch runs the rounds; it waits for the one
- * before it on the same device, whatever their streams.  Larger cohorts, calls
+ * before it on the same device, whatever their streams.  Other cohorts, calls
  * on a stream that is being captured or has a CU mask, and calls whose
  * cooperative launch the device turns down merge one pair at a time: below
  * 3,200 samples in one block's loop, from 3,200 on in two kernel launches per

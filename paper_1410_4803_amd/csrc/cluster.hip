@@ -15,9 +15,9 @@
 // doubles that are maxima of the input doubles, so the merge sequence is
 // exactly determined.
 //
-// GPU plan: the working matrix D (m x m doubles) lives in the workspace.  Up
-// to kClMaxSlots samples the merges run in rounds of mutually nearest pairs,
-// in one cooperative launch (k_cl_rounds below).  Larger cohorts, and calls
+// GPU plan: the working matrix D (m x m doubles) lives in the workspace.  From
+// kClMinSlots to kClMaxSlots samples the merges run in rounds of mutually
+// nearest pairs, in one cooperative launch (k_cl_rounds below).  Other cohorts, and calls
 // that cannot launch it (cluster_rounds_ok), merge one pair at a time:
 // for each active cluster k the cached nearest neighbour among l > k,
 // nn[k] = argmin over (D[k][l], l), is kept; the globally closest pair is the
@@ -575,6 +575,9 @@ __global__ __launch_bounds__(kClT) void k_cl_rescan(const double* __restrict__ D
 // finds one pair: equal distances, 6,000 samples 73 -> 93 to 96 ms, 1,000 samples
 // 7.8 ms either way.
 constexpr int kClMaxSlots = 24576;   // 6 bytes of LDS per slot
+// Below, the one block's loop is as fast as the rounds' three launches (us a
+// call, loop / rounds: 2 samples 23 / 42, 5 41 / 56, 10 72 / 66, 20 129 / 105).
+constexpr int kClMinSlots = 10;
 constexpr int kClFew = 32;
 constexpr int kClWaves = kClT / 64;
 constexpr unsigned kClNone = 0xFFFFu;
@@ -1010,12 +1013,12 @@ int64_t cluster_rounds_bytes(int64_t m) {
          kClBarWords * 4;
 }
 
-// Whether the rounds can run: the slots fit, the stream is not capturing (a
+// Whether the rounds can run and pay: the slots fit, the stream is not capturing (a
 // captured call takes the launches per merge, plain kernel nodes) and has the
 // whole chip (no CU mask), and the device launches cooperatively and holds a
 // block per CU.  `blocks`: one per CU, or one per kClPerBlock rows.
 static bool cluster_rounds_ok(int64_t m, hipStream_t st, unsigned& blocks) {
-  if (m > kClMaxSlots) return false;
+  if (m < kClMinSlots || m > kClMaxSlots) return false;
   hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
   int dev = 0, coop = 0, cus = 0, resident = 0;
   if (hipStreamIsCapturing(st, &cap) != hipSuccess || hipGetDevice(&dev) != hipSuccess ||

@@ -32,9 +32,14 @@ def _calls(fake, case, m=100):
     return fakehip.launches(fake, case, CHILD, _native.LIB_PATH, m)
 
 
-@pytest.mark.parametrize("m,blocks", [(100, 13), (10000, 256)])
+@pytest.mark.parametrize("m,blocks", [(10, 2), (100, 13), (10000, 256), (24576, 256)])
 def test_rounds_run(fake, m, blocks):
     assert _calls(fake, "", m) == ["plain", f"cooperative {blocks}", "plain"]
+
+
+@pytest.mark.parametrize("m", [2, 9])
+def test_few_samples_merge_one_pair_at_a_time(fake, m):
+    assert _calls(fake, "", m) == ["plain"] * 3
 
 
 @pytest.mark.parametrize("case", ["capturing", "occupancy", "masked"])
