@@ -341,17 +341,23 @@ constexpr int64_t kLdNibbleMaxBytes = (int64_t)32 << 30;
 // Whether E goes with an operand D of `bytes` over m samples, for the band of
 // `window`.  Writing it has to pay: narrow windows over many samples read it too
 // seldom, and its two bytes more per byte of D cost the tiles of large cohorts
-// what its ready operands save.  Whole calls, us, with E / without it (D of 500
-// MB; of 20 MB the two are within 3%):
+// what its ready operands save, the more the further D is beyond the caches.
+// Whole calls, us, with E / without it, D of 500 MB:
 //   2,500 samples   window 20 845 / 829      100 1128 / 1172   1,000 4636 / 5447
 //   5,000                  20 818 / 744      100 1073 / 1033   200 1469 / 1529
 //   10,000                 20 802 / 694      200 1439 / 1411   350 1901 / 1931
 //   20,000                 20 837 / 698      350 1915 / 1887   500 2449 / 2454
 //   50,000                 20 801 / 682      700 3231 / 3220   1,000 4454 / 4460
-constexpr int64_t kLdNibbleFewSamples = 3000, kLdNibbleSmall = (int64_t)16 << 20;
+// and of 60 MB:
+//   10,000                 20 114 / 106      100 151 / 146     200 203 / 204
+//   20,000                 20 127 / 121      200 207 / 200     350 272 / 278
+// (of 20 MB the two are within 3% at window 20 and the same from 100 on).
+constexpr int64_t kLdNibbleFewSamples = 3000;
+constexpr int64_t kLdNibbleSmall = (int64_t)16 << 20, kLdNibbleMedium = (int64_t)128 << 20;
 inline bool ld_takes_nibbles(int64_t m, int64_t bytes, int64_t window) {
   return m < kLdFp4MaxSamples && 2 * bytes <= kLdNibbleMaxBytes &&
-         (m <= kLdNibbleFewSamples || window >= m / 40 || bytes < kLdNibbleSmall);
+         (m <= kLdNibbleFewSamples || bytes < kLdNibbleSmall ||
+          window >= m / (bytes < kLdNibbleMedium ? 64 : 40));
 }
 // Dense pair kernel over the band; with `sp`, tiles the correction path
 // takes are skipped (and stage 2 is left to that path).  With E the fp4 tile

@@ -76,7 +76,7 @@ def test_words_in_a_batch():
         assert got.tobytes() == _records(p.cohort, p.window, 0.0, MFMA).tobytes()
 
 
-@pytest.mark.parametrize("n,V,W", [(3001, 23000, 74), (5003, 14001, 20), (10000, 7000, 1),
+@pytest.mark.parametrize("n,V,W", [(3001, 23000, 45), (5003, 14001, 20), (10000, 7000, 1),
                                    (20011, 3500, 130)])
 def test_narrow_windows(n, V, W):
     """Operands from 16 MiB on."""

@@ -43,9 +43,10 @@ def test_largest_nibble_operand():
         assert _bytes(n, V, W, N.PG_PATH_MFMA) < 1.1 * _words(n, V)
 
 
-@pytest.mark.parametrize("n,V,W,nibbles", [(3000, 100000, 1, True), (3001, 100000, 74, False),
-                                           (3001, 100000, 75, True), (20000, 50000, 499, False),
-                                           (20000, 50000, 500, True), (20000, 3000, 1, True)])
+@pytest.mark.parametrize("n,V,W,nibbles", [(3000, 400000, 1, True), (3001, 200000, 74, False),
+                                           (3001, 200000, 75, True), (20000, 50000, 499, False),
+                                           (20000, 50000, 500, True), (20000, 20000, 311, False),
+                                           (20000, 20000, 312, True), (20000, 3000, 1, True)])
 def test_narrow_windows_over_many_samples(n, V, W, nibbles):
     got = _bytes(n, V, W, N.PG_PATH_MFMA) / _words(n, V)
     assert (got > 3) == nibbles and (nibbles or got < 1.6)
